@@ -1,38 +1,36 @@
-// Matrix-core kernel for Y = A * Omega(seed) with a wide sketch (k > 16) on gfx950.
+// Matrix-core kernels for Y = A * Omega(seed) with a wide sketch on gfx950.
 //
-// Once k is large the product is a dense contraction (2k flops per A element;
-// non-packed FP32 VALU FMAs reach their ridge near k = 20), so the local
-// multiplication of Alg. 1 runs on the MFMA units: v_mfma_f32_16x16x4f32,
-// FP32 in, FP32 accumulate.
+// FP32 A (k > 8).  The product is a dense contraction (2k flops per A element);
+// it runs on the FP16 matrix cores with both operands split into FP16 terms
+// (sk_split.hpp: four v_mfma_f32_16x16x32_f16 per 32 contraction columns, FP32
+// sums), whose error against FP64 is below that of an FP32 chain.
 //
-// Tile of one workgroup (512 threads = 8 waves): 512 rows of A x a strip of
+// Tile of one workgroup (64 W threads = W waves): 64 W rows of A x a strip of
 // kMfmaStrip contraction columns x BN = 16*NT sketch columns.  Each wave owns
-// 64 rows (4 M-tiles of 16) x NT N-tiles, i.e. 4*NT accumulator tiles.  Eight
-// waves share each generated Omega chunk, which halves the generation work per
-// A element against four (measured: 109 vs 75 TFLOP/s at k = 256).
+// 64 rows (4 row tiles of 16) x NT N-tiles, i.e. 4*NT accumulator tiles of
+// Y^T (Omega is the A operand, A the B operand, so a lane's accumulators belong
+// to one row of each row tile and the row's scale is the lane's own).
 //
-// Contraction in chunks of KC = 32 columns:
-//   * A goes straight from HBM into the MFMA A-operand layout: lane (g, i)
-//     (g = lane/16, i = lane%16) loads the KC/4 contiguous floats
-//     A[row i][kc + g*KC/4 ...] of each M-tile as KC/16 back-to-back 16-byte
-//     loads, so each 128-byte line of a row is requested at once; component s of
-//     load v feeds one MFMA, whose contraction index g then stands for column
-//     kc + g*KC/4 + 4v + s.  Any order of the contraction is a valid product, so
-//     no shuffle is needed.  Plain (temporal) loads: the lines of a row are
-//     shared by the four lanes of a row (measured faster than nontemporal).
-//   * Omega for the chunk (KC x BN) is generated from the seed into one half of
-//     a double-buffered LDS tile, laid out [column][KC + 4 pad] so that lane
-//     (g, j) reads Omega[kc + g*KC/4 ...][j] as ds_read_b128s: exactly the B
-//     operands of the same MFMAs.
-//   * The next chunk's Omega is generated while this chunk's MFMAs run (VALU
-//     and matrix cores work in parallel); one LDS-only barrier per chunk.
+// Contraction in chunks of KC = 32 columns, one MFMA step each:
+//   * A goes straight from HBM into the operand layout: lane (g, i) (g = lane/16,
+//     i = lane%16) loads the 8 contiguous floats A[row i][kc + 8 g ...] of each
+//     row tile as two back-to-back 16-byte loads, so each 128-byte line of a row is
+//     requested at once, and splits them in registers.  Plain (temporal) loads:
+//     the lines of a row are shared by the four lanes of a row.
+//   * Omega's three terms for the chunk sit in one half of a double-buffered LDS
+//     tile, laid out [column][b0 | b1 | b2], so that lane (g, j) reads the 8
+//     contraction columns 8g .. 8g + 7 of column j as 16-byte operands.
+//   * The next chunk's Omega is generated (or copied from the call's packed Omega)
+//     and split while this chunk's MFMAs run; one LDS-only barrier per chunk.
 // Strip partials are FP32 in [S][m][k]; the FP64 strip sum is the shared
 // reduction kernel.  The order of every sum depends only on the strip
 // boundaries, so results are layout independent and reproducible.
 #include <algorithm>
+#include <type_traits>
 
 #include "sk_device.hpp"
 #include "sk_internal.hpp"
+#include "sk_split.hpp"
 
 #pragma clang fp contract(off)
 
@@ -47,15 +45,11 @@ constexpr int kWaves = 8;               // waves per workgroup
 constexpr int kThreads = 64 * kWaves;
 constexpr int kBM = kWaves * kTM * 16;  // rows per workgroup
 static_assert(kBM == kMfmaRows, "tile rows");
-// contraction columns per chunk, and floats per LDS column (chunk + 4 pad):
-// 32 at every N-tile count, so a chunk takes 128 bytes of each row (with 16
-// columns every 128-byte line of A was fetched twice: 16 GiB instead of 8 for
-// a two-block k = 256 sketch of 32768^2, rocprofv3 FETCH_SIZE).  With 8
-// N-tiles the A operands are single-buffered (the accumulators take 128
-// registers): a chunk's 256 MFMAs cover the next chunk's load.
-constexpr int chunk_cols(int) { return 32; }
+// With 8 N-tiles the raw A values are single-buffered (the accumulators take 128
+// registers): they are split before a chunk's 128 MFMAs, which cover the next
+// chunk's load.
+constexpr int chunk_cols(int) { return kSplitKC; }
 constexpr bool single_a(int nt) { return nt >= 8; }
-constexpr int lds_row(int nt) { return chunk_cols(nt) + 4; }
 
 struct MArgs {
     int64_t m;
@@ -83,14 +77,16 @@ struct MArgs {
 
 // Tile of this workgroup in a one-dimensional grid of 8 * ceil(T / 8)
 // workgroups over T = nblk * S_total * nrt tiles.
-// XCD (low-precision kernel): workgroups are handed to the 8 XCDs
+// XCD: workgroups are handed to the 8 XCDs
 // round-robin, so XCD x runs ids x, x + 8, ...; mapping them to the contiguous
 // tile range [x * T8, (x + 1) * T8), ordered sketch-column block fastest, then
 // strip, then row tile, makes each XCD read whole rows of A (every strip of a
 // row tile at once) and keeps the column blocks of one (strip, row tile) in
 // one L2.  Measured on 32768^2 FP8 at k = 64: 290 us against 371 with the
 // strip index fastest across XCDs.
-// Otherwise (FP32 kernel, measured 2-3% faster so at k = 64): the id is the
+// The FP32 kernel with split operands gains as well: k = 64 on 65536 x 16384 850 us
+// against 876, k = 256 on 32768^2 (two column blocks) 2.23 ms against 2.43.
+// Otherwise (FP32 kernel with one N-tile, the same either way): the id is the
 // tile, strip fastest, then row tile, then column block.
 // Returns false for the padding ids past T.
 struct TileId {
@@ -209,94 +205,68 @@ __device__ __forceinline__ void store_tile(const MTile& t, const v4f (&acc)[kTM]
     }
 }
 
-// Columns past k of both LDS halves (BN sketch columns x KC + 4 floats) are
-// zeroed once: generation never writes them.
-template <int BN, int KC>
-__device__ __forceinline__ void omega_zero_pad(float (*om)[BN][KC + 4], int kb) {
-    for (int it = threadIdx.x; it < 2 * BN * (KC + 4); it += kThreads) {
-        const int n = (it / (KC + 4)) % BN;
-        if (n >= kb) (&om[0][0][0])[it] = 0.0f;
+// Columns past k of an LDS ring of `slots` chunks are zeroed once: generation never
+// writes them.
+template <int BN, int TH>
+__device__ __forceinline__ void omega_zero_pad(_Float16 (*om)[BN][kSplitRow], int slots, int kb) {
+    for (int it = threadIdx.x; it < slots * BN * (kSplitRow / 8); it += TH) {
+        const int n = (it / (kSplitRow / 8)) % BN;
+        if (n >= kb) reinterpret_cast<v4u*>(&om[0][0][0])[it] = v4u{0u, 0u, 0u, 0u};
     }
 }
 
-// Omega rows of chunk c of the tile's strip (kvalid of them; zeros past the
-// strip's end) for sketch columns n_base .. n_base + kb - 1 -> LDS half c & 1,
-// laid out [column][contraction]; generated from the seed, or read from a
-// stored Omega.
-template <int BN, int kKC, bool GEN>
-__device__ __forceinline__ void omega_chunk(const MTile& t, float (*om)[BN][kKC + 4], int c, int w,
-                                            int kb) {
-    const int tid = threadIdx.x;
-    const int nthr = kThreads;
-    const int buf = c & 1;
-    const int kvalid = min(kKC, w - c * kKC);
+// Chunks c0 .. c0 + G - 1 (those below nchunks) of the tile's strip, sketch columns
+// n_base .. n_base + kb - 1, split into LDS slots slot0 .. (slot0 + G - 1); zeros past
+// the strip's end.  Generated from the seed, or read from a stored Omega (scaled by
+// 2^-ecol).  With few sketch columns one chunk has too few Philox quads to occupy the
+// workgroup, G of them do.  A chunk's first Omega row is aligned as the strip's (chunk
+// widths are multiples of 4), so every chunk has the same quad count.
+template <int BN, int TH, int G, bool GEN>
+__device__ __forceinline__ void omega_group(const MTile& t, _Float16 (*om)[BN][kSplitRow],
+                                            int slot0, int c0, int nchunks, int w, int kb,
+                                            const int* ecol) {
+    constexpr int KC = kSplitKC;
+    const int cnt = min(G, nchunks - c0);
     if constexpr (GEN) {
-        const int64_t g0 = t.row0 + t.col_begin + (int64_t)c * kKC;  // global Omega row of local 0
-        const int64_t q_lo = g0 >> 2;
-        const int nq = (int)(((g0 + kKC - 1) >> 2) - q_lo + 1);       // KC/4, or one more if unaligned
-        const int items = nq * kb;
-        for (int it = tid; it < items; it += nthr) {
-            const int qi = it / kb;
-            const int n = it - qi * kb;
-            const float4 z = omega4_dist((uint64_t)(q_lo + qi), t.col0 + (uint32_t)(t.n_base + n),
-                                         t.key0, t.key1, t.dist);
-            const int kl0 = (int)(4 * (q_lo + qi) - g0);
+        const int64_t gb = t.row0 + t.col_begin;                     // Omega row of strip column 0
+        const int nq = (int)(((gb + KC - 1) >> 2) - (gb >> 2) + 1);   // KC/4, or one more if unaligned
+        const int per = nq * kb;
+        const float sc = __builtin_ldexpf(1.0f, kOmegaExp);
+        for (int it = threadIdx.x; it < cnt * per; it += TH) {
+            const int ci = it / per;
+            const int r = it - ci * per;
+            const int qi = r / kb;
+            const int n = r - qi * kb;
+            const int c = c0 + ci;
+            const int64_t g0 = gb + (int64_t)c * KC;
+            const int kvalid = min(KC, w - c * KC);
+            const int64_t q = (g0 >> 2) + qi;
+            const float4 z = omega4_dist((uint64_t)q, t.col0 + (uint32_t)(t.n_base + n), t.key0,
+                                         t.key1, t.dist);
+            const int kl0 = (int)(4 * q - g0);
+            _Float16* dst = om[slot0 + ci][n];
             if (kl0 >= 0 && (kl0 & 3) == 0 && kl0 + 3 < kvalid) {
-                *reinterpret_cast<float4*>(&om[buf][n][kl0]) = z;
+                split_store4(dst, kl0, f32x4{z.x, z.y, z.z, z.w}, sc);
             } else {
                 const float zz[4] = {z.x, z.y, z.z, z.w};
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int kl = kl0 + u;
-                    if (kl >= 0 && kl < kKC) om[buf][n][kl] = (kl < kvalid) ? zz[u] : 0.0f;
+                    if (kl >= 0 && kl < KC) split_store1(dst, kl, (kl < kvalid) ? zz[u] : 0.0f, sc);
                 }
             }
         }
     } else {
-        for (int it = tid; it < kKC * kb; it += nthr) {
-            const int kl = it / kb;
-            const int n = it - kl * kb;
-            om[buf][n][kl] = (kl < kvalid)
-                                 ? t.omega[(t.col_begin + (int64_t)c * kKC + kl) * t.ldo + t.n_base + n]
-                                 : 0.0f;
-        }
-    }
-}
-
-// Chunks c0 .. c0 + G - 1 (those below nchunks) of the tile's strip, generated
-// together into LDS slots slot0 .. slot0 + G - 1 (each laid out as above): with
-// few sketch columns one chunk has too few Philox quads to occupy the
-// workgroup, G of them do.  A chunk's first Omega row is aligned as the strip's
-// (chunk widths are multiples of 4), so every chunk has the same quad count.
-template <int BN, int kKC, int G>
-__device__ __forceinline__ void omega_group(const MTile& t, float (*om)[BN][kKC + 4], int slot0,
-                                            int c0, int nchunks, int w, int kb) {
-    const int64_t gb = t.row0 + t.col_begin;                       // Omega row of strip column 0
-    const int nq = (int)(((gb + kKC - 1) >> 2) - (gb >> 2) + 1);   // quads per chunk
-    const int per = nq * kb;
-    const int cnt = min(G, nchunks - c0);
-    for (int it = threadIdx.x; it < cnt * per; it += kThreads) {
-        const int ci = it / per;
-        const int r = it - ci * per;
-        const int qi = r / kb;
-        const int n = r - qi * kb;
-        const int c = c0 + ci;
-        const int64_t g0 = gb + (int64_t)c * kKC;
-        const int kvalid = min(kKC, w - c * kKC);
-        const int64_t q = (g0 >> 2) + qi;
-        const float4 z = omega4_dist((uint64_t)q, t.col0 + (uint32_t)(t.n_base + n), t.key0, t.key1,
-                                     t.dist);
-        const int kl0 = (int)(4 * q - g0);
-        float* dst = om[slot0 + ci][n];
-        if (kl0 >= 0 && (kl0 & 3) == 0 && kl0 + 3 < kvalid) {
-            *reinterpret_cast<float4*>(&dst[kl0]) = z;
-        } else {
-            const float zz[4] = {z.x, z.y, z.z, z.w};
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int kl = kl0 + u;
-                if (kl >= 0 && kl < kKC) dst[kl] = (kl < kvalid) ? zz[u] : 0.0f;
-            }
+        for (int it = threadIdx.x; it < cnt * KC * kb; it += TH) {
+            const int ci = it / (KC * kb);
+            const int r = it - ci * (KC * kb);
+            const int kl = r / kb;
+            const int n = r - kl * kb;
+            const int c = c0 + ci;
+            float z = 0.0f;
+            if (c * KC + kl < w)
+                z = t.omega[(t.col_begin + (int64_t)c * KC + kl) * t.ldo + t.n_base + n];
+            split_store1(om[slot0 + ci][n], kl, z, __builtin_ldexpf(1.0f, kOmegaExp - ecol[n]));
         }
     }
 }
@@ -390,63 +360,160 @@ __global__ __launch_bounds__(256) void k_f32_pack(const PackArgs a) {
     }
 }
 
-// FULL: every chunk of the launch is whole (block widths multiples of the chunk
-// width).  Then every lane issues the same A loads every chunk, unconditionally
-// (a load past the strip's end re-reads its last chunk, never used), and the
-// compiler waits for the chunk being multiplied alone; with the per-lane tail
-// path present it waits for every load in flight, including the next chunk's,
-// which undoes the double buffering.
-// PK: Omega chunks copied from the call's packed Omega (k_f32_pack); the copy of
-// chunk c + 2 is issued ahead of the A loads issued after it, so waiting for
-// it leaves those in flight.
-template <int NT, bool GEN, bool FULL = false, bool PK = false>
-__device__ __forceinline__ void mfma_tile(const MTile& t, float (*om)[16 * NT][lds_row(NT)]) {
-    constexpr int BN = 16 * NT;
-    constexpr int kKC = chunk_cols(NT);
-    constexpr int kLV = kKC / 16;   // 16-byte A loads per lane per M-tile per chunk
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int g = lane >> 4;      // contraction group of the lane (A and B operands)
-    const int i16 = lane & 15;    // row (A operand) / column (B operand) within a tile
-
-    const int w = (int)min<int64_t>(kMfmaStrip, t.n - t.col_begin);
-    const int nchunks = (w + kKC - 1) / kKC;
-    const int64_t row_base = t.block_row + wave * (kTM * 16);
-    const int n_base = t.n_base;
-    const int kb = (int)min<int64_t>(BN, t.k - n_base);
-
-    // ---- A operand loads ----------------------------------------------------------
-    const int64_t lda4 = t.lda * 4;
-    const unsigned char* arow[kTM];
-#pragma unroll
-    for (int tm = 0; tm < kTM; ++tm) {
-        const int64_t r = min<int64_t>(row_base + tm * 16 + i16, t.m - 1);
-        arow[tm] = t.A + r * lda4 + (t.col_begin + 4 * kLV * g) * 4;
+// Write v as the strip sum (row, col) of a tile: scaled, to the partials, or to Y of a
+// single-strip call (old Y added in FP64).
+struct TileOut {
+    const float* scales;
+    float* partials;          // strip's first partial, or nullptr: single strip
+    void* Y;
+    int64_t k, ldy;
+    int y_trans, y_f64, beta;
+};
+__device__ __forceinline__ void emit(const TileOut& o, int64_t row, int64_t col, float v) {
+    if (o.scales) v *= o.scales[row >> 7];
+    if (o.partials) {
+        o.partials[row * o.k + col] = v;
+        return;
     }
-    auto load_a = [&](v4f (*a)[kLV], int c) {
-        if constexpr (FULL) {
-            const int cc = c < nchunks ? c : nchunks - 1;
+    const int64_t off = o.y_trans ? col * o.ldy + row : row * o.ldy + col;
+    double y = (double)v;
+    if (o.y_f64) {
+        double* Yp = static_cast<double*>(o.Y) + off;
+        if (o.beta) y += *Yp;
+        *Yp = y;
+    } else {
+        float* Yp = static_cast<float*>(o.Y) + off;
+        if (o.beta) y += (double)*Yp;
+        *Yp = (float)y;
+    }
+}
+
+// Sketch columns col .. col + 3 of a row, those below `end` (the lane's accumulator of
+// one 16 x 16 tile of Y^T).
+__device__ __forceinline__ void emit4(const TileOut& o, int64_t row, int64_t col, int64_t end,
+                                      const v4f v, float s, const int* ecol) {
+    v4f u;
 #pragma unroll
-            for (int tm = 0; tm < kTM; ++tm) {
-                const unsigned char* p = arow[tm] + (int64_t)cc * kKC * 4;
+    for (int r = 0; r < 4; ++r) u[r] = unscale(v[r], s, ecol ? ecol[r] : 0);
+    if (o.partials && !o.scales && (o.k & 3) == 0 && col + 3 < end) {
+        *reinterpret_cast<v4f*>(o.partials + row * o.k + col) = u;   // k, col multiples of 4
+        return;
+    }
 #pragma unroll
-                for (int v = 0; v < kLV; ++v) a[tm][v] = *reinterpret_cast<const v4f*>(p + 16 * v);
-            }
-            return;
+    for (int r = 0; r < 4; ++r)
+        if (col + r < end) emit(o, row, col + r, u[r]);
+}
+
+// Omega(j, c) of the tile's strip (j its column, c below 16 NT), wherever the tile
+// takes it from.
+template <bool GEN, bool PK>
+__device__ __forceinline__ float omega_at(const MTile& t, int j, int c) {
+    if constexpr (PK) {
+        constexpr int CPS = kMfmaStrip / kSplitKC;
+        return t.fpack[((t.strip * CPS + j / kSplitKC) * t.kpad + t.n_base + c) * kSplitKC +
+                       j % kSplitKC];
+    } else if constexpr (GEN) {
+        const int64_t g = t.row0 + t.col_begin + j;
+        const float4 z = omega4_dist((uint64_t)(g >> 2), t.col0 + (uint32_t)(t.n_base + c), t.key0,
+                                     t.key1, t.dist);
+        const int u = (int)(g & 3);
+        return u == 0 ? z.x : u == 1 ? z.y : u == 2 ? z.z : z.w;
+    } else {
+        return t.omega[(t.col_begin + j) * t.ldo + t.n_base + c];
+    }
+}
+
+// Strip sums whose row of A holds an infinity, or whose column of a stored Omega holds
+// an infinity or NaN, once more with FP32 products (the FP16 terms of an infinity
+// would meet zeros and the other sign): row `row` (its first strip element at `a`, the
+// next `stride` further), sketch columns lane, lane + 64, ... below kb that `want` picks.
+template <bool GEN, bool PK, typename Want>
+__device__ __forceinline__ void fix_row(const MTile& t, const TileOut& o, const float* a,
+                                        int64_t stride, int64_t row, int w, int kb, Want want) {
+    for (int c = threadIdx.x & 63; c < kb; c += 64) {
+        if (!want(c)) continue;
+        float v = 0.0f;
+        for (int j = 0; j < w; ++j) v = __builtin_fmaf(a[j * stride], omega_at<GEN, PK>(t, j, c), v);
+        emit(o, row, t.n_base + c, v);
+    }
+}
+
+// Exponents of a stored Omega's columns in the tile's strip: ecol[n] scales column n
+// into FP16's range (0 for |omega| <= 6 down to 2^-25, which every generated strip has,
+// so that a stored copy of it multiplies with the same bits); kBadCol marks an
+// infinity or NaN.
+constexpr int kBadCol = 0x7FFF;
+template <int BN, int TH, bool PK>
+__device__ __forceinline__ void omega_exponents(const MTile& t, int* ecol, int w, int kb) {
+    for (int n = threadIdx.x; n < BN; n += TH) ecol[n] = 0;
+    __syncthreads();
+    for (int64_t it = threadIdx.x; it < (int64_t)w * kb; it += TH) {
+        const int j = (int)(it / kb);
+        const int n = (int)(it - (int64_t)j * kb);
+        atomicMax(&ecol[n], __float_as_int(omega_at<false, PK>(t, j, n)) & 0x7FFFFFFF);
+    }
+    __syncthreads();
+    for (int n = threadIdx.x; n < BN; n += TH) {
+        const int b = ecol[n];
+        int e = 0;
+        if (b >= 0x7F800000) {
+            e = kBadCol;
+        } else if (b > __float_as_int(6.0f) || (b != 0 && b < __float_as_int(0x1p-25f))) {
+            int x;
+            (void)frexpf(__int_as_float(b), &x);   // amax in [2^(x-1), 2^x) -> [2, 4)
+            e = max(x - 2, -110);                   // 2^(13 - e) stays an FP32 number
         }
-        if (c >= nchunks) return;
-        const int kl = c * kKC + 4 * kLV * g;               // local column of component 0
+        ecol[n] = e;
+    }
+    __syncthreads();
+}
+
+// A operand loads of a wave: chunk c of rows row_base .. row_base + 63, lane (g, i) the 8
+// floats at columns 8 g .. of row (tm, i).
+// FULL: every block of the launch has at least one whole chunk of columns.  Then every
+// lane issues the same loads every chunk, unconditionally (a load past the strip's
+// whole chunks re-reads the last of them, or the one before the strip), and the
+// compiler waits for the chunk being multiplied alone; with a per-lane tail path in
+// the loop it waits for every load in flight, including the next chunk's, which
+// undoes the double buffering.  A ragged last chunk is loaded behind a wave-uniform
+// branch that waits for its own loads.  Narrower blocks take the per-lane path.
+template <bool FULL>
+struct ALoads {
+    const unsigned char* arow[kTM];
+    int g, w;
+    __device__ __forceinline__ ALoads(const MTile& t, int64_t row_base, int g_, int i16, int w_)
+        : g(g_), w(w_) {
 #pragma unroll
         for (int tm = 0; tm < kTM; ++tm) {
-            const unsigned char* p = arow[tm] + (int64_t)c * kKC * 4;
-            if (kl + 4 * kLV - 1 < w) {
+            const int64_t r = min<int64_t>(row_base + tm * 16 + i16, t.m - 1);
+            arow[tm] = t.A + r * (t.lda * 4) + (t.col_begin + 8 * g) * 4;
+        }
+    }
+    __device__ __forceinline__ void load(v4f (*a)[2], int c) const {
+        constexpr int KC = kSplitKC;
+        const int nfull = w / KC;
+        if constexpr (FULL) {
+            const int cc = c < nfull ? c : nfull - 1;
 #pragma unroll
-                for (int v = 0; v < kLV; ++v) a[tm][v] = *reinterpret_cast<const v4f*>(p + 16 * v);
+            for (int tm = 0; tm < kTM; ++tm) {
+                const unsigned char* p = arow[tm] + (int64_t)cc * KC * 4;
+#pragma unroll
+                for (int v = 0; v < 2; ++v) a[tm][v] = *reinterpret_cast<const v4f*>(p + 16 * v);
+            }
+            if (c != nfull) return;
+        }
+        const int kl = c * KC + 8 * g;                      // strip column of component 0
+        if (c * KC >= w) return;
+#pragma unroll
+        for (int tm = 0; tm < kTM; ++tm) {
+            const unsigned char* p = arow[tm] + (int64_t)c * KC * 4;
+            if (kl + 7 < w) {
+#pragma unroll
+                for (int v = 0; v < 2; ++v) a[tm][v] = *reinterpret_cast<const v4f*>(p + 16 * v);
             } else {
                 const float* pf = reinterpret_cast<const float*>(p);
 #pragma unroll
-                for (int v = 0; v < kLV; ++v) {
+                for (int v = 0; v < 2; ++v) {
                     v4f x = {0.f, 0.f, 0.f, 0.f};
                     for (int e = 0; e < 4; ++e)
                         if (kl + 4 * v + e < w) x[e] = pf[4 * v + e];
@@ -454,33 +521,169 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, float (*om)[16 * NT][l
                 }
             }
         }
+        if constexpr (FULL) {
+#pragma unroll
+            for (int tm = 0; tm < kTM; ++tm) asm volatile("" : "+v"(a[tm][0]), "+v"(a[tm][1]));
+        }
+    }
+};
+
+// k <= 16 (one N-tile): v_mfma_f32_16x16x4f32.  Reading A bounds these sketches, and
+// this tile's few registers (no terms to hold) keep more loads in flight: 65536 x 16384 at
+// k = 16 takes 767 us here and 800 us with split operands.  Same tile, loads and barriers as
+// mfma_tile; A is the A operand, 8 MFMAs per chunk and row tile: component s of 16-byte load
+// v is contraction index g of MFMA 4v + s.  FULL as for mfma_tile.
+constexpr int kF32Row = kSplitKC + 4;   // floats per LDS column of a chunk
+struct F32Lds {
+    float om[2][16][kF32Row];
+};
+
+template <int TH, bool GEN>
+__device__ __forceinline__ void omega_chunk_f32(const MTile& t, float (*om)[kF32Row], int c, int w,
+                                                int kb) {
+    constexpr int KC = kSplitKC;
+    const int kvalid = min(KC, w - c * KC);
+    if constexpr (GEN) {
+        const int64_t g0 = t.row0 + t.col_begin + (int64_t)c * KC;   // global Omega row of local 0
+        const int64_t q_lo = g0 >> 2;
+        const int nq = (int)(((g0 + KC - 1) >> 2) - q_lo + 1);        // KC/4, or one more if unaligned
+        for (int it = threadIdx.x; it < nq * kb; it += TH) {
+            const int qi = it / kb;
+            const int n = it - qi * kb;
+            const float4 z = omega4_dist((uint64_t)(q_lo + qi), t.col0 + (uint32_t)(t.n_base + n),
+                                         t.key0, t.key1, t.dist);
+            const int kl0 = (int)(4 * (q_lo + qi) - g0);
+            if (kl0 >= 0 && (kl0 & 3) == 0 && kl0 + 3 < kvalid) {
+                *reinterpret_cast<float4*>(&om[n][kl0]) = z;
+            } else {
+                const float zz[4] = {z.x, z.y, z.z, z.w};
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int kl = kl0 + u;
+                    if (kl >= 0 && kl < KC) om[n][kl] = (kl < kvalid) ? zz[u] : 0.0f;
+                }
+            }
+        }
+    } else {
+        for (int it = threadIdx.x; it < KC * kb; it += TH) {
+            const int kl = it / kb;
+            const int n = it - kl * kb;
+            om[n][kl] = (kl < kvalid)
+                            ? t.omega[(t.col_begin + (int64_t)c * KC + kl) * t.ldo + t.n_base + n]
+                            : 0.0f;
+        }
+    }
+}
+
+template <int W, bool GEN, bool FULL>
+__device__ __forceinline__ void mfma_tile_f32(const MTile& t, F32Lds& L) {
+    constexpr int TH = 64 * W;
+    constexpr int KC = kSplitKC;
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const int g = lane >> 4;
+    const int i16 = lane & 15;
+
+    const int w = (int)min<int64_t>(kMfmaStrip, t.n - t.col_begin);
+    const int nchunks = (w + KC - 1) / KC;
+    const int nfull = w / KC;
+    const int64_t row_base = t.block_row + wave * (kTM * 16);
+    const int kb = (int)min<int64_t>(16, t.k - t.n_base);
+    const ALoads<FULL> A(t, row_base, g, i16, w);
+
+    // columns past k of both halves are zeroed once: generation never writes them
+    for (int it = threadIdx.x; it < 2 * 16 * kF32Row; it += TH)
+        if ((it / kF32Row) % 16 >= kb) (&L.om[0][0][0])[it] = 0.0f;
+    auto make_chunk = [&](int c) { omega_chunk_f32<TH, GEN>(t, L.om[c & 1], c, w, kb); };
+
+    v4f acc[kTM][1];
+#pragma unroll
+    for (int tm = 0; tm < kTM; ++tm) acc[tm][0] = v4f{0.f, 0.f, 0.f, 0.f};
+    v4f a0[kTM][2], a1[kTM][2];
+    A.load(a0, 0);
+    A.load(a1, 1);
+    make_chunk(0);
+    lds_barrier_m();
+    auto step = [&](v4f (*a)[2], int c) {
+        if (c + 1 < nchunks) make_chunk(c + 1);
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+            const v4f bop = *reinterpret_cast<const v4f*>(&L.om[c & 1][i16][8 * g + 4 * v]);
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int tm = 0; tm < kTM; ++tm)
+                    acc[tm][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[tm][v][s], bop[s], acc[tm][0],
+                                                                      0, 0, 0);
+        }
+        A.load(a, c + 2);
+        if constexpr (FULL) __builtin_amdgcn_sched_barrier(0);
+        lds_barrier_m();
     };
+    for (int c = 0; c < nchunks; c += 2) {
+        step(a0, c);
+        if (c + 1 < nchunks) step(a1, c + 1);
+    }
+    store_tile<1>(t, acc, row_base, kb, g, i16);
+}
+
+// Split operands (two or more N-tiles).
+// PK: Omega chunks copied from the call's packed Omega (k_f32_pack) and split on the
+// way to LDS; the copy of chunk c + 2 is issued ahead of the A loads issued after it,
+// so waiting for it leaves those in flight.
+template <int NT>
+struct SplitLds {
+    _Float16 om[2][16 * NT][kSplitRow];
+    int ecol[16 * NT];
+};
+
+template <int NT, int W, bool GEN, bool FULL = false, bool PK = false>
+__device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT>& L) {
+    constexpr int BN = 16 * NT;
+    constexpr int TH = 64 * W;
+    constexpr int KC = kSplitKC;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
+    const int g = lane >> 4;      // contraction group of the lane (both operands)
+    const int i16 = lane & 15;    // A row / sketch column within a tile
+    _Float16 (*om)[BN][kSplitRow] = L.om;
+
+    const int w = (int)min<int64_t>(kMfmaStrip, t.n - t.col_begin);
+    const int nchunks = (w + KC - 1) / KC;
+    const int64_t row_base = t.block_row + wave * (kTM * 16);
+    const int n_base = t.n_base;
+    const int kb = (int)min<int64_t>(BN, t.k - n_base);
+    const bool stored = (PK || !GEN) && t.omega != nullptr;   // uniform across the launch
+
+    const ALoads<FULL> A(t, row_base, g, i16, w);
 
     // ---- Omega chunk -> LDS ----------------------------------------------------------
-    if constexpr (!PK) omega_zero_pad<BN, kKC>(om, kb);
-    auto make_chunk = [&](int c) { omega_chunk<BN, kKC, GEN>(t, om, c, w, kb); };
+    if constexpr (!PK) omega_zero_pad<BN, TH>(om, 2, kb);
+    if (stored) omega_exponents<BN, TH, PK>(t, L.ecol, w, kb);
+    auto make_chunk = [&](int c) {
+        omega_group<BN, TH, 1, GEN>(t, om, c & 1, c, nchunks, w, kb, L.ecol);
+    };
     // packed route: 16-byte pieces of the tile's run of a chunk, OPT per thread;
     // chunk indices past the last are clamped (a re-read of valid memory whose
     // copy lands in the LDS half no step reads next)
-    constexpr int PPL = BN * kKC / 4;
-    constexpr int OPT = (PPL + kThreads - 1) / kThreads;
+    constexpr int PPL = BN * KC / 4;
+    constexpr int OPT = (PPL + TH - 1) / TH;
+    static_assert(!PK || PPL % TH == 0, "whole pieces per thread");
     auto om_load = [&](v4f* r, int c) {
         const int cc = c < nchunks ? c : nchunks - 1;
-        const float* src = t.fpack + ((t.strip * (kMfmaStrip / kKC) + cc) * t.kpad + n_base) * kKC;
+        const float* src = t.fpack + ((t.strip * (kMfmaStrip / KC) + cc) * t.kpad + n_base) * KC;
 #pragma unroll
-        for (int j = 0; j < OPT; ++j) {
-            const int p = min(tid + j * kThreads, PPL - 1);
-            r[j] = *reinterpret_cast<const v4f*>(src + 4 * p);
-        }
+        for (int j = 0; j < OPT; ++j) r[j] = *reinterpret_cast<const v4f*>(src + 4 * (tid + j * TH));
     };
     auto om_store = [&](const v4f* r, int c) {
         const int buf = c & 1;
 #pragma unroll
         for (int j = 0; j < OPT; ++j) {
-            const int p = min(tid + j * kThreads, PPL - 1);
-            const int n = p / (kKC / 4);
-            const int kl4 = (p - n * (kKC / 4)) * 4;
-            *reinterpret_cast<v4f*>(&om[buf][n][kl4]) = r[j];
+            const int p = tid + j * TH;
+            const int n = p / (KC / 4);
+            const float sc = stored ? __builtin_ldexpf(1.0f, kOmegaExp - L.ecol[n]) : 0x1p13f;
+            split_store4(om[buf][n], (p % (KC / 4)) * 4, r[j], sc);
         }
     };
 
@@ -489,105 +692,159 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, float (*om)[16 * NT][l
     for (int tm = 0; tm < kTM; ++tm)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) acc[tm][nt] = v4f{0.f, 0.f, 0.f, 0.f};
+    float s[kTM];                 // scale of row (tm, i16)
+    bool inf[kTM];                // the row holds an infinity
+#pragma unroll
+    for (int tm = 0; tm < kTM; ++tm) {
+        s[tm] = kRowStart;
+        inf[tm] = false;
+    }
 
-    v4f a0[kTM][kLV], a1[kTM][kLV];
+    // chunk's raw values -> MFMA operands, rescaling rows that outgrow FP16
+    h8 a0[kTM], a1[kTM], a0s[kTM];
+    auto split = [&](v4f (*a)[2]) {
+        float x[kTM][8], y[kTM][8];
+        float mx = 0.0f;
+#pragma unroll
+        for (int tm = 0; tm < kTM; ++tm) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                x[tm][e] = a[tm][e >> 2][e & 3];
+                y[tm][e] = x[tm][e] * s[tm];
+            }
+            mx = absmax8(y[tm], mx);
+        }
+        if (__builtin_expect(__any(mx > kRowLimit), 0)) {
+#pragma unroll
+            for (int tm = 0; tm < kTM; ++tm) {
+                const float f = rescale_row(x[tm], s[tm], inf[tm]);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) acc[tm][nt] *= f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) y[tm][e] = x[tm][e] * s[tm];
+            }
+        }
+#pragma unroll
+        for (int tm = 0; tm < kTM; ++tm) split_a(y[tm], a0[tm], a1[tm], a0s[tm]);
+    };
+
+    auto compute = [&](int c) {
+        const int buf = c & 1;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const _Float16* ob = &om[buf][nt * 16 + i16][8 * g];
+            const h8 b0 = *reinterpret_cast<const h8*>(ob);
+            const h8 b1 = *reinterpret_cast<const h8*>(ob + KC);
+            const h8 b2 = *reinterpret_cast<const h8*>(ob + 2 * KC);
+#pragma unroll
+            for (int tm = 0; tm < kTM; ++tm)
+                acc[tm][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(b0, a1[tm], acc[tm][nt], 0, 0, 0);
+#pragma unroll
+            for (int tm = 0; tm < kTM; ++tm)
+                acc[tm][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(b2, a0s[tm], acc[tm][nt], 0, 0, 0);
+#pragma unroll
+            for (int tm = 0; tm < kTM; ++tm)
+                acc[tm][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(b1, a0s[tm], acc[tm][nt], 0, 0, 0);
+#pragma unroll
+            for (int tm = 0; tm < kTM; ++tm)
+                acc[tm][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(b0, a0[tm], acc[tm][nt], 0, 0, 0);
+        }
+    };
+
+    v4f r0[kTM][2], r1[kTM][2];
     v4f orr[PK ? OPT : 1];
     if constexpr (PK) {
-        load_a(a0, 0);
         om_load(orr, 0);
+        A.load(r0, 0);
         om_store(orr, 0);
-        if constexpr (!single_a(NT)) {
-            om_load(orr, 1);
-            __builtin_amdgcn_sched_barrier(0);
-            load_a(a1, 1);
-        }
+        om_load(orr, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (!single_a(NT)) A.load(r1, 1);
     } else {
-        load_a(a0, 0);
-        if constexpr (!single_a(NT)) load_a(a1, 1);
+        A.load(r0, 0);
+        if constexpr (!single_a(NT)) A.load(r1, 1);
         make_chunk(0);
     }
     lds_barrier_m();
 
-    auto compute = [&](v4f (*a)[kLV], int c) {
-        const int buf = c & 1;
-#pragma unroll
-        for (int v = 0; v < kLV; ++v) {
-            v4f bop[NT];   // Omega operands of load v, read as they are used
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-                bop[nt] = *reinterpret_cast<const v4f*>(&om[buf][nt * 16 + i16][4 * kLV * g + 4 * v]);
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-#pragma unroll
-                for (int tm = 0; tm < kTM; ++tm)
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-                        acc[tm][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                            a[tm][v][s], bop[nt][s], acc[tm][nt], 0, 0, 0);
-        }
-    };
-
-    if constexpr (PK && single_a(NT)) {
-        // one A buffer (the accumulators leave no room for more): step c runs
-        // chunk c's MFMAs, then issues chunk c + 1's A and Omega loads and
-        // stores the Omega copy (its registers are never live across MFMAs);
-        // the next step needs those A loads at once either way
-        for (int c = 0; c < nchunks; ++c) {
-            compute(a0, c);
-            load_a(a0, c + 1);
-            om_load(orr, c + 1);
-            om_store(orr, c + 1);
-            lds_barrier_m();
-        }
-    } else if constexpr (PK) {
-        for (int c = 0; c < nchunks; c += 2) {
+    // step c: chunk c + 1's Omega to LDS, chunk c's A split, its registers refilled,
+    // chunk c's MFMAs
+    auto step = [&](v4f (*r)[2], int c) {
+        if constexpr (PK) {
             om_store(orr, c + 1);
             om_load(orr, c + 2);
             __builtin_amdgcn_sched_barrier(0);
-            compute(a0, c);
-            load_a(a0, c + 2);
-            if constexpr (FULL) __builtin_amdgcn_sched_barrier(0);
-            lds_barrier_m();
-            om_store(orr, c + 2);
-            om_load(orr, c + 3);
-            __builtin_amdgcn_sched_barrier(0);
-            if (c + 1 < nchunks) compute(a1, c + 1);
-            load_a(a1, c + 3);
-            if constexpr (FULL) __builtin_amdgcn_sched_barrier(0);
-            lds_barrier_m();
-        }
-    } else if constexpr (single_a(NT)) {
-        for (int c = 0; c < nchunks; ++c) {
+        } else {
             if (c + 1 < nchunks) make_chunk(c + 1);
-            compute(a0, c);
-            load_a(a0, c + 1);
-            lds_barrier_m();
         }
+        split(r);
+        A.load(r, c + (single_a(NT) ? 1 : 2));
+        if constexpr (FULL) __builtin_amdgcn_sched_barrier(0);
+        compute(c);
+        lds_barrier_m();
+    };
+    if constexpr (single_a(NT)) {
+        for (int c = 0; c < nchunks; ++c) step(r0, c);
     } else {
         for (int c = 0; c < nchunks; c += 2) {
-            if (c + 1 < nchunks) make_chunk(c + 1);
-            compute(a0, c);
-            load_a(a0, c + 2);
-            lds_barrier_m();
-            if (c + 1 < nchunks) {
-                if (c + 2 < nchunks) make_chunk(c + 2);
-                compute(a1, c + 1);
-                load_a(a1, c + 3);
-                lds_barrier_m();
-            }
+            step(r0, c);
+            if (c + 1 < nchunks) step(r1, c + 1);
         }
     }
 
-    store_tile<NT>(t, acc, row_base, kb, g, i16);
+    // ---- lane (g, i) holds sketch columns 4g .. 4g + 3 of row i of each tile ------
+    TileOut o;
+    o.scales = t.scales;
+    o.partials = t.single ? nullptr : t.partials + t.strip * t.m * t.k;
+    o.Y = t.Y;
+    o.k = t.k;
+    o.ldy = t.ldy;
+    o.y_trans = 0;
+    o.y_f64 = t.y_f64;
+    o.beta = t.beta;
+#pragma unroll
+    for (int tm = 0; tm < kTM; ++tm) {
+        const int64_t row = row_base + tm * 16 + i16;
+        if (row >= t.m) continue;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+            emit4(o, row, n_base + nt * 16 + 4 * g, n_base + kb, acc[tm][nt], s[tm],
+                  stored ? &L.ecol[nt * 16 + 4 * g] : nullptr);
+    }
+    // ---- non-finite entries, again with FP32 products ------------------------------
+    if (__any(inf[0] || inf[1] || inf[2] || inf[3])) {
+#pragma unroll
+        for (int tm = 0; tm < kTM; ++tm) {
+            for (uint64_t rows = __ballot(inf[tm]) & 0xFFFFu; rows != 0; rows &= rows - 1) {
+                const int64_t row = row_base + tm * 16 + __builtin_ctzll(rows);
+                if (row >= t.m) break;
+                fix_row<GEN, PK>(t, o, reinterpret_cast<const float*>(t.A) + row * t.lda + t.col_begin,
+                                 1, row, w, kb, [](int) { return true; });
+            }
+        }
+    }
+    if (stored) {
+        bool bad = false;
+        for (int n = lane; n < kb; n += 64) bad = bad || L.ecol[n] == kBadCol;
+        if (__any(bad)) {
+            for (int64_t row = row_base; row < min<int64_t>(row_base + kTM * 16, t.m); ++row)
+                fix_row<GEN, PK>(t, o, reinterpret_cast<const float*>(t.A) + row * t.lda + t.col_begin,
+                                 1, row, w, kb, [&](int c) { return L.ecol[c] == kBadCol; });
+        }
+    }
 }
 
-// One call: one workgroup per (strip of any block, 512-row tile, sketch-column
-// block), strip fastest.
-template <int NT, bool GEN, bool FULL>
-__global__ __launch_bounds__(kThreads) void k_gemm_mfma(const MArgs args) {
-    __shared__ float om[2][16 * NT][lds_row(NT)];
+template <int NT>
+using TileLds = std::conditional_t<NT == 1, F32Lds, SplitLds<NT>>;
+
+// One call: one workgroup per (strip of any block, 64W-row tile, sketch-column
+// block).
+template <int NT, int W, bool GEN, bool FULL>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 4 : 2)))
+void k_gemm_mfma(const MArgs args) {
+    __shared__ __attribute__((aligned(16))) TileLds<NT> lds;
     TileId id;
-    if (!mfma_tile_id<false>(args, id)) return;
+    if (!mfma_tile_id<(NT > 1)>(args, id)) return;
     const int strip = id.strip;
     int b = 0;
     int64_t sib = strip;
@@ -606,7 +863,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_mfma(const MArgs args) {
     t.m = args.m;
     t.k = args.k;
     t.col_begin = sib * kMfmaStrip;
-    t.block_row = id.rtile * kBM;
+    t.block_row = id.rtile * (64 * W);
     t.n_base = id.nb * 16 * NT;
     t.key0 = args.key0;
     t.key1 = args.key1;
@@ -625,15 +882,16 @@ __global__ __launch_bounds__(kThreads) void k_gemm_mfma(const MArgs args) {
     t.opack_lo = nullptr;
     t.kpad = args.kpad;
     t.fpack = args.fpack;
-    mfma_tile<NT, GEN, FULL, mfma_packed(NT)>(t, om);
+    if constexpr (NT == 1) mfma_tile_f32<W, GEN, FULL>(t, lds);
+    else mfma_tile<NT, W, GEN, FULL, mfma_packed(NT)>(t, lds);
 }
 
 // A batch of independent requests (serving): the tiles of each request are the
 // ones a call for that request alone would run, walked by a fixed grid in an
 // XCD-grouped order, so each result does not depend on the batch.
-template <int NT>
+template <int NT, bool FULL>
 __global__ __launch_bounds__(kThreads) void k_gemm_mfma_batch(const BatchArgs args) {
-    __shared__ float om[2][16 * NT][lds_row(NT)];
+    __shared__ __attribute__((aligned(16))) TileLds<NT> lds;
     const int64_t T8 = (args.total_tiles + 7) / 8;
     bool first = true;
     for (int64_t v = blockIdx.x; v < 8 * T8; v += gridDim.x) {   // gridDim.x is a multiple of 8
@@ -676,22 +934,23 @@ __global__ __launch_bounds__(kThreads) void k_gemm_mfma_batch(const BatchArgs ar
         t.fpack = nullptr;
         if (!first) lds_barrier_m();   // every wave is done with the previous tile's LDS
         first = false;
-        mfma_tile<NT, true>(t, om);
+        if constexpr (NT == 1) mfma_tile_f32<kWaves, true, FULL>(t, lds);
+        else mfma_tile<NT, kWaves, true, FULL>(t, lds);
     }
 }
 
 // ---------------------------------------------------------------------------
 // Column-major A (element (i, j) at A + j*lda + i, the paper's storage order) on
-// the same matrix cores, for k > 16.  The tile computes the transposed product
-// Y^T = Omega^T A^T: the Omega chunk in LDS (same layout and same reads as the
-// B operand above) is the A operand, and A enters as the B operand straight
-// from HBM.  Lane (g, j) loads 16 bytes, rows 4j .. 4j + 3 of one column (a
-// wave reads 256 contiguous bytes of each of four columns per load); component
-// q of the load feeds the MFMA of row set {4j + q}, so a wave holds four 16 x 16
-// accumulator tiles of Y^T per N-tile, covering 64 rows.  Step s of a chunk
-// reads column kc + g*KC/4 + s, the column that contraction index g of step s
-// stands for in the row-major kernel: both kernels form the same products in
-// the same order, and every A element is read once for all k sketch columns.
+// the same matrix cores, for k > 16: the same transposed product
+// Y^T = Omega^T A^T, the Omega chunk in LDS with the same layout and reads.
+// Lane (g, j) loads 16 bytes, rows 4j .. 4j + 3 of one column (a wave reads 256
+// contiguous bytes of each of four columns per load), for the eight columns
+// kc + 8 g .. kc + 8 g + 7 of a chunk; component q of the eight loads is the operand of
+// row set {4j + q}, so a wave holds four 16 x 16 accumulator tiles of Y^T per
+// N-tile, covering 64 rows.  A row's 32 entries of a chunk enter the MFMA at the
+// positions they have in the row-major kernel and carry the same scale: both
+// kernels form the same sums, and every A element is read once for all k
+// sketch columns.
 struct CmMArgs {
     const float* A;
     int64_t m, n, lda, row0;
@@ -711,23 +970,63 @@ struct CmMArgs {
 
 // KC = the row-major kernel's chunk for this k (chunk_cols(mfma_ntiles(k))),
 // whatever N-tile count the launch picked, so that the sums are the same.
-// FULL (m a multiple of 4, whole chunks): every lane of every wave issues the same
-// loads each chunk from a valid address (a lane or wave without rows reads row 0;
-// its sums are never stored; a load past the strip's end re-reads its last chunk),
-// so the compiler waits for the chunk in use alone (see mfma_tile).
+// FULL (at least four rows and one whole chunk of columns): every lane of every wave
+// issues the same loads each chunk from a valid address (a lane or wave without rows
+// reads row 0; its sums are never stored; a load past the strip's whole chunks re-reads
+// one), so the compiler waits for the chunk in use alone (see mfma_tile).  ROWS4: m is
+// a multiple of 4, so no lane's four rows are cut.
+constexpr bool cm_full(int64_t m, int64_t n) { return m >= 4 && n >= kSplitKC; }
+// four floats at any float's alignment
+typedef float v4f_a4 __attribute__((ext_vector_type(4), aligned(4)));
 // Packed Omega on the column-major tiles: four or more N-tiles, except eight
 // without whole chunks (that kernel's registers have no room for the copy).
 constexpr bool cm_packed(int nt, bool full) { return mfma_packed(nt) && (full || nt < 8); }
 
-template <int NT, int kKC, bool FULL>
+__device__ __forceinline__ TileOut cm_out(const CmMArgs& a, int strip) {
+    TileOut o;
+    o.scales = nullptr;
+    o.partials = a.S == 1 ? nullptr : a.partials + (int64_t)strip * a.m * a.k;
+    o.Y = a.Y;
+    o.k = a.k;
+    o.ldy = a.ldy;
+    o.y_trans = a.y_trans;
+    o.y_f64 = a.y_f64;
+    o.beta = a.beta;
+    return o;
+}
+
+// Rows of row set q (row 4j + q of lane j, from row r0 of the wave) that hold an infinity
+// (see fix_row).
+template <bool PK = true>
+__device__ __forceinline__ void cm_fix_rows(const CmMArgs& a, const TileOut& o, int strip,
+                                            int n_base, bool inf, int64_t first, int w, int kb) {
+    MTile t{};
+    t.row0 = a.row0;
+    t.col_begin = (int64_t)strip * kMfmaStrip;
+    t.n_base = n_base;
+    t.key0 = a.key0;
+    t.key1 = a.key1;
+    t.col0 = a.col0;
+    t.dist = a.dist;
+    t.strip = strip;
+    t.kpad = a.kpad;
+    t.fpack = a.fpack;
+    for (uint64_t rows = __ballot(inf) & 0xFFFFu; rows != 0; rows &= rows - 1) {
+        const int64_t row = first + 4 * __builtin_ctzll(rows);
+        if (row >= a.m) break;
+        fix_row<true, PK>(t, o, a.A + t.col_begin * a.lda + row, a.lda, row, w, kb,
+                          [](int) { return true; });
+    }
+}
+
+template <int NT, int kKC, bool FULL, bool ROWS4>
 __global__ __launch_bounds__(kThreads) void k_gemm_cm_mfma(const CmMArgs a) {
     constexpr int BN = 16 * NT;
-    constexpr int kNS = kKC / 4;     // MFMA steps (and 16-byte loads per lane) per chunk
-    constexpr int kLV = kKC / 16;    // 16-byte Omega reads per lane and N-tile per chunk
+    constexpr int kNS = kKC / 4;     // columns (and 16-byte loads) per lane and chunk
     // chunks generated per barrier: enough quads for every thread (1 when BN*KC/4 >= 512)
     constexpr int kG = kThreads / (kNS * BN) > 1 ? kThreads / (kNS * BN) : 1;
     static_assert(kG == 1 || kG % 2 == 0, "chunk pairs per generation group");
-    __shared__ float om[2 * kG][BN][kKC + 4];
+    __shared__ __attribute__((aligned(16))) _Float16 om[2 * kG][BN][kSplitRow];
 
     const int64_t id = blockIdx.x;
     const int64_t tt = (id % 8) * a.tiles8 + id / 8;       // XCD-grouped tile order
@@ -751,20 +1050,35 @@ __global__ __launch_bounds__(kThreads) void k_gemm_cm_mfma(const CmMArgs a) {
     const int j = lane & 15;
     const int w = (int)min<int64_t>(kMfmaStrip, a.n - t.col_begin);
     const int nchunks = (w + kKC - 1) / kKC;
+    const int nfull = w / kKC;                              // whole chunks
     const int kb = (int)min<int64_t>(BN, a.k - t.n_base);
     const int64_t r0 = (int64_t)rb * kBM + wave * 64;      // first row of the wave
     const int64_t rl = r0 + 4 * j;                          // first row of the lane
     const bool active = r0 < a.m;                           // the wave has rows
     const bool full_rows = rl + 3 < a.m;
+    // rows of the lane's group when m cuts it: the last four rows are loaded instead and
+    // moved down (FULL)
+    const int cut = FULL && rl < a.m && !full_rows ? (int)(a.m - rl) : 0;
 
     // ---- A loads: step s of chunk c is column col_begin + c*KC + g*KC/4 + s --------
-    const float* acol = a.A + (t.col_begin + g * kNS) * a.lda + (FULL && rl >= a.m ? 0 : rl);
+    const float* acol = a.A + (t.col_begin + g * kNS) * a.lda +
+                        (!FULL ? rl : cut ? a.m - 4 : rl >= a.m ? 0 : rl);
     auto load_a = [&](v4f* x, int c) {
         if constexpr (FULL) {
-            const int cc = c < nchunks ? c : nchunks - 1;
+            const int cc = c < nfull ? c : nfull - 1;
 #pragma unroll
             for (int s = 0; s < kNS; ++s)
-                x[s] = *reinterpret_cast<const v4f*>(acol + (int64_t)(cc * kKC + s) * a.lda);
+                x[s] = *reinterpret_cast<const v4f_a4*>(acol + (int64_t)(cc * kKC + s) * a.lda);
+            if (c != nfull || nfull == nchunks) return;
+#pragma unroll
+            for (int s = 0; s < kNS; ++s) {
+                v4f v = {0.f, 0.f, 0.f, 0.f};
+                if (c * kKC + g * kNS + s < w)
+                    v = *reinterpret_cast<const v4f_a4*>(acol + (int64_t)(c * kKC + s) * a.lda);
+                x[s] = v;
+            }
+#pragma unroll
+            for (int s = 0; s < kNS; ++s) asm volatile("" : "+v"(x[s]));
             return;
         }
         if (!active || c >= nchunks) return;
@@ -788,115 +1102,157 @@ __global__ __launch_bounds__(kThreads) void k_gemm_cm_mfma(const CmMArgs a) {
     constexpr bool PK = cm_packed(NT, FULL);
     constexpr int PPL = BN * kKC / 4;
     constexpr int OPT = (PPL + kThreads - 1) / kThreads;
+    static_assert(!PK || PPL % kThreads == 0, "whole pieces per thread");
     const int tid = threadIdx.x;
     auto om_load = [&](v4f* r, int c) {
         const int cc = c < nchunks ? c : nchunks - 1;
         const float* src = a.fpack + (((int64_t)strip * (kMfmaStrip / kKC) + cc) * a.kpad + t.n_base) * kKC;
 #pragma unroll
-        for (int i = 0; i < OPT; ++i) {
-            const int p = min(tid + i * kThreads, PPL - 1);
-            r[i] = *reinterpret_cast<const v4f*>(src + 4 * p);
-        }
+        for (int i = 0; i < OPT; ++i)
+            r[i] = *reinterpret_cast<const v4f*>(src + 4 * (tid + i * kThreads));
     };
     auto om_store = [&](const v4f* r, int slot) {
 #pragma unroll
         for (int i = 0; i < OPT; ++i) {
-            const int p = min(tid + i * kThreads, PPL - 1);
-            const int n = p / (kKC / 4);
-            const int kl4 = (p - n * (kKC / 4)) * 4;
-            *reinterpret_cast<v4f*>(&om[slot][n][kl4]) = r[i];
+            const int p = tid + i * kThreads;
+            split_store4(om[slot][p / (kKC / 4)], (p % (kKC / 4)) * 4, r[i], 0x1p13f);
         }
     };
 
-    if constexpr (!PK) omega_zero_pad<BN, kKC>(om, kb);
+    if constexpr (!PK) omega_zero_pad<BN, kThreads>(om, 2 * kG, kb);
     v4f acc[4][NT];
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) acc[q][nt] = v4f{0.f, 0.f, 0.f, 0.f};
+    float sc[4];                  // scale of row rl + q
+    bool inf[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        sc[q] = kRowStart;
+        inf[q] = false;
+    }
 
-    v4f a0[kNS], a1[kNS];
+    v4f x0[kNS], x1[kNS];
     v4f orr[PK ? OPT : 1];
     if constexpr (PK) {
         static_assert(!PK || kG == 1, "one chunk per barrier on the packed route");
-        load_a(a0, 0);
         om_load(orr, 0);
+        load_a(x0, 0);
         om_store(orr, 0);
-        if constexpr (!single_a(NT)) {
-            om_load(orr, 1);
-            __builtin_amdgcn_sched_barrier(0);
-            load_a(a1, 1);
-        }
+        om_load(orr, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (!single_a(NT)) load_a(x1, 1);
     } else {
-        load_a(a0, 0);
-        if constexpr (!single_a(NT)) load_a(a1, 1);
-        omega_group<BN, kKC, kG>(t, om, 0, 0, nchunks, w, kb);
+        load_a(x0, 0);
+        if constexpr (!single_a(NT)) load_a(x1, 1);
+        omega_group<BN, kThreads, kG, true>(t, om, 0, 0, nchunks, w, kb, nullptr);
     }
     lds_barrier_m();
 
-    auto compute = [&](const v4f* x, int buf) {
-        if (!active) return;
-        v4f wop[NT][kLV];
+    h8 a0[4], a1[4], a0s[4];
+    auto split = [&](v4f* x) {
+        if constexpr (FULL && !ROWS4) {
+            if (cut == 1) {
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
+                for (int e = 0; e < 8; ++e) x[e] = v4f{x[e][3], 0.f, 0.f, 0.f};
+            } else if (cut == 2) {
 #pragma unroll
-            for (int v = 0; v < kLV; ++v)
-                wop[nt][v] = *reinterpret_cast<const v4f*>(&om[buf][nt * 16 + j][4 * kLV * g + 4 * v]);
+                for (int e = 0; e < 8; ++e) x[e] = v4f{x[e][2], x[e][3], 0.f, 0.f};
+            } else if (cut == 3) {
 #pragma unroll
-        for (int v = 0; v < kLV; ++v)
+                for (int e = 0; e < 8; ++e) x[e] = v4f{x[e][1], x[e][2], x[e][3], 0.f};
+            }
+        }
+        float y[4][8];
+        float mx = 0.0f;
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
+        for (int q = 0; q < 4; ++q) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
+            for (int e = 0; e < 8; ++e) y[q][e] = x[e][q] * sc[q];
+            mx = absmax8(y[q], mx);
+        }
+        if (__builtin_expect(__any(mx > kRowLimit), 0)) {
 #pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-                        acc[q][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                            wop[nt][v][s], x[4 * v + s][q], acc[q][nt], 0, 0, 0);
+            for (int q = 0; q < 4; ++q) {
+                float xq[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) xq[e] = x[e][q];
+                const float f = rescale_row(xq, sc[q], inf[q]);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) acc[q][nt] *= f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) y[q][e] = x[e][q] * sc[q];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) split_a(y[q], a0[q], a1[q], a0s[q]);
+    };
+    auto compute = [&](int slot) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const _Float16* ob = &om[slot][nt * 16 + j][8 * g];
+            const h8 b0 = *reinterpret_cast<const h8*>(ob);
+            const h8 b1 = *reinterpret_cast<const h8*>(ob + kKC);
+            const h8 b2 = *reinterpret_cast<const h8*>(ob + 2 * kKC);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                acc[q][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(b0, a1[q], acc[q][nt], 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                acc[q][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(b2, a0s[q], acc[q][nt], 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                acc[q][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(b1, a0s[q], acc[q][nt], 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                acc[q][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(b0, a0[q], acc[q][nt], 0, 0, 0);
+        }
+    };
+    // chunk c: its A split, its registers refilled, its MFMAs
+    auto consume = [&](v4f* x, int c, int slot) {
+        if (FULL || active) {
+            split(x);
+            load_a(x, c + (single_a(NT) ? 1 : 2));
+            if constexpr (FULL) __builtin_amdgcn_sched_barrier(0);
+            compute(slot);
+        }
     };
 
-    if constexpr (PK && single_a(NT)) {
-        // the order of mfma_tile's packed loops (Omega copies never live across MFMAs here)
-        for (int c = 0; c < nchunks; ++c) {
-            compute(a0, c & 1);
-            load_a(a0, c + 1);
-            om_load(orr, c + 1);
+    if constexpr (PK) {
+        // the order of mfma_tile's packed loop
+        auto step = [&](v4f* x, int c) {
             om_store(orr, (c + 1) & 1);
-            lds_barrier_m();
-        }
-    } else if constexpr (PK) {
-        for (int c = 0; c < nchunks; c += 2) {
-            om_store(orr, 1);
             om_load(orr, c + 2);
             __builtin_amdgcn_sched_barrier(0);
-            compute(a0, 0);
-            load_a(a0, c + 2);
-            if constexpr (FULL) __builtin_amdgcn_sched_barrier(0);
+            consume(x, c, c & 1);
             lds_barrier_m();
-            om_store(orr, 0);
-            om_load(orr, c + 3);
-            __builtin_amdgcn_sched_barrier(0);
-            if (c + 1 < nchunks) compute(a1, 1);
-            load_a(a1, c + 3);
-            if constexpr (FULL) __builtin_amdgcn_sched_barrier(0);
-            lds_barrier_m();
+        };
+        if constexpr (single_a(NT)) {
+            for (int c = 0; c < nchunks; ++c) step(x0, c);
+        } else {
+            for (int c = 0; c < nchunks; c += 2) {
+                step(x0, c);
+                if (c + 1 < nchunks) step(x1, c + 1);
+            }
         }
     } else if constexpr (single_a(NT)) {
         for (int c = 0; c < nchunks; ++c) {
-            if (c + 1 < nchunks) omega_group<BN, kKC, 1>(t, om, (c + 1) & 1, c + 1, nchunks, w, kb);
-            compute(a0, c & 1);
-            load_a(a0, c + 1);
+            if (c + 1 < nchunks)
+                omega_group<BN, kThreads, 1, true>(t, om, (c + 1) & 1, c + 1, nchunks, w, kb, nullptr);
+            consume(x0, c, c & 1);
             lds_barrier_m();
         }
     } else if constexpr (kG == 1) {
         for (int c = 0; c < nchunks; c += 2) {
-            if (c + 1 < nchunks) omega_group<BN, kKC, 1>(t, om, 1, c + 1, nchunks, w, kb);
-            compute(a0, 0);
-            load_a(a0, c + 2);
+            if (c + 1 < nchunks)
+                omega_group<BN, kThreads, 1, true>(t, om, 1, c + 1, nchunks, w, kb, nullptr);
+            consume(x0, c, 0);
             lds_barrier_m();
             if (c + 1 < nchunks) {
-                if (c + 2 < nchunks) omega_group<BN, kKC, 1>(t, om, 0, c + 2, nchunks, w, kb);
-                compute(a1, 1);
-                load_a(a1, c + 3);
+                if (c + 2 < nchunks)
+                    omega_group<BN, kThreads, 1, true>(t, om, 0, c + 2, nchunks, w, kb, nullptr);
+                consume(x1, c + 1, 1);
                 lds_barrier_m();
             }
         }
@@ -905,17 +1261,13 @@ __global__ __launch_bounds__(kThreads) void k_gemm_cm_mfma(const CmMArgs a) {
         // into the other half while this one is consumed, one barrier per group
         for (int cb = 0; cb < nchunks; cb += kG) {
             const int half = (cb / kG) & 1;
-            if (cb + kG < nchunks) omega_group<BN, kKC, kG>(t, om, (half ^ 1) * kG, cb + kG, nchunks, w, kb);
+            if (cb + kG < nchunks)
+                omega_group<BN, kThreads, kG, true>(t, om, (half ^ 1) * kG, cb + kG, nchunks, w, kb,
+                                                    nullptr);
 #pragma unroll
             for (int i = 0; i < kG; i += 2) {
-                if (cb + i < nchunks) {
-                    compute(a0, half * kG + i);
-                    load_a(a0, cb + i + 2);
-                }
-                if (cb + i + 1 < nchunks) {
-                    compute(a1, half * kG + i + 1);
-                    load_a(a1, cb + i + 3);
-                }
+                if (cb + i < nchunks) consume(x0, cb + i, half * kG + i);
+                if (cb + i + 1 < nchunks) consume(x1, cb + i + 1, half * kG + i + 1);
             }
             lds_barrier_m();
         }
@@ -924,35 +1276,17 @@ __global__ __launch_bounds__(kThreads) void k_gemm_cm_mfma(const CmMArgs a) {
 
     // ---- lane l holds Y^T rows (sketch columns) 4g .. 4g + 3 of column j of each
     // accumulator tile: Y[rl + q][n_base + 16 nt + 4g + r] = acc[q][nt][r] ---------------
+    const TileOut o = cm_out(a, strip);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const int64_t row = rl + q;
-        if (row >= a.m) continue;
+        if (rl + q >= a.m) continue;
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
+        for (int nt = 0; nt < NT; ++nt)
+            emit4(o, rl + q, t.n_base + nt * 16 + 4 * g, t.n_base + kb, acc[q][nt], sc[q], nullptr);
+    }
+    if (__any(inf[0] || inf[1] || inf[2] || inf[3])) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int cn = nt * 16 + 4 * g + r;
-                if (cn >= kb) continue;
-                const int64_t col = t.n_base + cn;
-                const float v = acc[q][nt][r];
-                if (a.S == 1) {
-                    const int64_t off = a.y_trans ? col * a.ldy + row : row * a.ldy + col;
-                    double y = (double)v;
-                    if (a.y_f64) {
-                        double* Yp = static_cast<double*>(a.Y) + off;
-                        if (a.beta) y += *Yp;
-                        *Yp = y;
-                    } else {
-                        float* Yp = static_cast<float*>(a.Y) + off;
-                        if (a.beta) y += (double)*Yp;
-                        *Yp = (float)y;
-                    }
-                } else {
-                    a.partials[((int64_t)strip * a.m + row) * a.k + col] = v;
-                }
-            }
-        }
+        for (int q = 0; q < 4; ++q) cm_fix_rows<PK>(a, o, strip, t.n_base, inf[q], r0 + q, w, kb);
     }
 }
 
@@ -977,7 +1311,6 @@ template <int kKC, bool ALIGNED>
 __global__ __launch_bounds__(kSkThreads) void k_gemm_cm_mfma_skinny(const CmMArgs a) {
     constexpr int BN = 16;
     constexpr int kNS = kKC / 4;
-    constexpr int kLV = kKC / 16;
     constexpr int kGenThreads = kSkGenThreads;
     // a staged column of A: row 4j + q at [q][j], 2 floats of padding so that the
     // four lane groups of a chain's read (8 columns apart) fall on different banks
@@ -986,7 +1319,7 @@ __global__ __launch_bounds__(kSkThreads) void k_gemm_cm_mfma_skinny(const CmMArg
     constexpr int kOPieces = kSkG * BN * kKC / 4 / kGenThreads;   // and of Omega
     static_assert(kAPieces * kGenThreads == kSkG * kKC * 16 &&
                   kOPieces * kGenThreads == kSkG * BN * kKC / 4, "whole pieces per thread");
-    __shared__ __attribute__((aligned(16))) float om[2 * kSkG][BN][kKC + 4];
+    __shared__ __attribute__((aligned(16))) _Float16 om[2 * kSkG][BN][kSplitRow];
     __shared__ float as[2 * kSkG][kKC][kAP];
 
     const int64_t tt = blockIdx.x;
@@ -1008,13 +1341,7 @@ __global__ __launch_bounds__(kSkThreads) void k_gemm_cm_mfma_skinny(const CmMArg
     const int kb = (int)min<int64_t>(BN, a.k - n_base);
     const int64_t rl = 4 * j;                               // first row of the lane
 
-    // columns past k of every slot are zero (the packed plane holds zeros there too)
-    for (int it = threadIdx.x; it < 2 * kSkG * BN * (kKC + 4); it += kSkThreads) {
-        const int n = (it / (kKC + 4)) % BN;
-        if (n >= kb) (&om[0][0][0])[it] = 0.0f;
-    }
-
-    // staging (waves 4..7).  Every load is issued unconditionally from a valid
+    // staging (waves 4..11).  Every load is issued unconditionally from a valid
     // address (chunks past the strip's last re-read it, rows past m read rows 0..3,
     // columns past the strip's end read its last column), so the compiler waits for
     // the older group only; columns past the strip's end are stored as zeros, rows
@@ -1079,29 +1406,37 @@ __global__ __launch_bounds__(kSkThreads) void k_gemm_cm_mfma_skinny(const CmMArg
             const int pc = it - ci * PPC;
             const int n = pc / (kKC / 4);
             const int kl4 = (pc - n * (kKC / 4)) * 4;
-            *reinterpret_cast<v4f*>(&om[slot0 + ci][n][kl4]) = xo[t];
+            split_store4(om[slot0 + ci][n], kl4, xo[t], 0x1p13f);
         }
     };
 
     v4f acc = v4f{0.f, 0.f, 0.f, 0.f};
+    float sc = kRowStart;         // scale of row rl + q
+    bool inf = false;
     auto chain_group = [&](int gi) {
         const int slot0 = (gi & 1) * kSkG;
 #pragma unroll
         for (int cc = 0; cc < kSkG; ++cc) {
             if (gi * kSkG + cc < nchunks) {
-                const float* ob = &om[slot0 + cc][j][4 * kLV * g];
-                v4f wop[kLV];
-#pragma unroll
-                for (int v = 0; v < kLV; ++v) wop[v] = *reinterpret_cast<const v4f*>(ob + 4 * v);
+                const _Float16* ob = &om[slot0 + cc][j][8 * g];
+                const h8 b0 = *reinterpret_cast<const h8*>(ob);
+                const h8 b1 = *reinterpret_cast<const h8*>(ob + kKC);
+                const h8 b2 = *reinterpret_cast<const h8*>(ob + 2 * kKC);
                 const float* ab = &as[slot0 + cc][g * kNS][16 * q + j];
-                float x[kNS];
+                float x[kNS], y[kNS];
 #pragma unroll
-                for (int s = 0; s < kNS; ++s) x[s] = ab[s * kAP];
+                for (int s = 0; s < kNS; ++s) {
+                    x[s] = ab[s * kAP];
+                    y[s] = x[s] * sc;
+                }
+                if (__builtin_expect(__any(absmax8(y, 0.0f) > kRowLimit), 0)) {
+                    acc *= rescale_row(x, sc, inf);
 #pragma unroll
-                for (int v = 0; v < kLV; ++v)
-#pragma unroll
-                    for (int s = 0; s < 4; ++s)
-                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wop[v][s], x[4 * v + s], acc, 0, 0, 0);
+                    for (int s = 0; s < kNS; ++s) y[s] = x[s] * sc;
+                }
+                h8 a0, a1, a0s;
+                split_a(y, a0, a1, a0s);
+                acc = split_mfma(b0, b1, b2, a0, a1, a0s, acc);
             }
         }
     };
@@ -1132,39 +1467,21 @@ __global__ __launch_bounds__(kSkThreads) void k_gemm_cm_mfma_skinny(const CmMArg
 
     // lane (g, j) holds Y^T rows (sketch columns) 4g .. 4g + 3 of column j of the tile:
     // Y[rl + q][n_base + 4g + r] = acc[r]
+    const TileOut o = cm_out(a, strip);
     const int64_t row = rl + q;
-    if (row >= a.m) return;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int cn = 4 * g + r;
-        if (cn >= kb) continue;
-        const int64_t col = n_base + cn;
-        const float v = acc[r];
-        if (a.S == 1) {
-            const int64_t off = a.y_trans ? col * a.ldy + row : row * a.ldy + col;
-            double y = (double)v;
-            if (a.y_f64) {
-                double* Yp = static_cast<double*>(a.Y) + off;
-                if (a.beta) y += *Yp;
-                *Yp = y;
-            } else {
-                float* Yp = static_cast<float*>(a.Y) + off;
-                if (a.beta) y += (double)*Yp;
-                *Yp = (float)y;
-            }
-        } else {
-            a.partials[((int64_t)strip * a.m + row) * a.k + col] = v;
-        }
-    }
+    if (row < a.m) emit4(o, row, n_base + 4 * g, n_base + kb, acc, sc, nullptr);
+    cm_fix_rows(a, o, strip, n_base, inf, q, w, kb);
 }
 
 template <int NT, int KC>
 hipError_t launch_cm_mfma_nt(const CmMArgs& a, hipStream_t s) {
     const dim3 grid((unsigned)(8 * a.tiles8));
-    if (a.m % 4 == 0 && a.n % KC == 0)
-        hipLaunchKernelGGL((k_gemm_cm_mfma<NT, KC, true>), grid, dim3(kThreads), 0, s, a);
+    if (!cm_full(a.m, a.n))
+        hipLaunchKernelGGL((k_gemm_cm_mfma<NT, KC, false, false>), grid, dim3(kThreads), 0, s, a);
+    else if (a.m % 4 == 0)
+        hipLaunchKernelGGL((k_gemm_cm_mfma<NT, KC, true, true>), grid, dim3(kThreads), 0, s, a);
     else
-        hipLaunchKernelGGL((k_gemm_cm_mfma<NT, KC, false>), grid, dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL((k_gemm_cm_mfma<NT, KC, true, false>), grid, dim3(kThreads), 0, s, a);
     return hipGetLastError();
 }
 
@@ -1704,26 +2021,33 @@ hipError_t dispatch_lp(int nt, bool gen, int waves, const MArgs& a, hipStream_t 
     }
 }
 
-template <int NT, bool GEN>
-hipError_t launch_m(const MArgs& a, dim3 grid, hipStream_t s) {
+template <int NT, int W, bool GEN>
+hipError_t launch_m(const MArgs& args, hipStream_t s) {
     // packed tiles do not look at GEN (the packing kernel did): one instantiation
     constexpr bool G = mfma_packed(NT) || GEN;
+    MArgs a = args;
+    a.nrt = (a.m + 64 * W - 1) / (64 * W);
+    const dim3 grid = mfma_grid(a);
+    // one N-tile: whole chunks only (with a ragged end the unconditional loads measured
+    // 166 us against 158 for the per-lane path, 20011 x 9973 at k = 16)
     bool full = true;
-    for (int b = 0; b < a.P; ++b) full = full && a.blk[b].n % chunk_cols(NT) == 0;
+    for (int b = 0; b < a.P; ++b)
+        full = full && (NT == 1 ? a.blk[b].n % kSplitKC == 0
+                                : a.blk[b].n >= kSplitKC || a.blk[b].n == 0);
     if (full)
-        hipLaunchKernelGGL((k_gemm_mfma<NT, G, true>), grid, dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL((k_gemm_mfma<NT, W, G, true>), grid, dim3(64 * W), 0, s, a);
     else
-        hipLaunchKernelGGL((k_gemm_mfma<NT, G, false>), grid, dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL((k_gemm_mfma<NT, W, G, false>), grid, dim3(64 * W), 0, s, a);
     return hipGetLastError();
 }
 
 template <bool GEN>
-hipError_t dispatch_m(int nt, const MArgs& a, dim3 grid, hipStream_t s) {
+hipError_t dispatch_m(int nt, int waves, const MArgs& a, hipStream_t s) {
     switch (nt) {
-    case 1: return launch_m<1, GEN>(a, grid, s);
-    case 2: return launch_m<2, GEN>(a, grid, s);
-    case 4: return launch_m<4, GEN>(a, grid, s);
-    default: return launch_m<8, GEN>(a, grid, s);
+    case 1: return waves == 4 ? launch_m<1, 4, GEN>(a, s) : launch_m<1, 8, GEN>(a, s);
+    case 2: return waves == 4 ? launch_m<2, 4, GEN>(a, s) : launch_m<2, 8, GEN>(a, s);
+    case 4: return waves == 4 ? launch_m<4, 4, GEN>(a, s) : launch_m<4, 8, GEN>(a, s);
+    default: return launch_m<8, 8, GEN>(a, s);
     }
 }
 
@@ -1750,6 +2074,14 @@ size_t f32_plane_elems(int64_t strips, int64_t k) {
 }
 
 }  // namespace
+
+// Waves per workgroup of the FP32 kernel: 8 (512 rows share each Omega chunk), or 4 while
+// those tiles would fill half the compute units at most: the 256-row tiles then still run
+// in one round, with half the rows behind each chunk's latency (5000 x 5000 at k = 64:
+// 124 us against 187; with 200 512-row tiles, 20011 x 9973, it is 210 against 203).
+static int mfma_waves(int64_t m, int64_t strips, int64_t nblk) {
+    return 2 * strips * ((m + kBM - 1) / kBM) * nblk <= device_cus() ? 4 : 8;
+}
 
 hipError_t launch_gemm_mfma(const GemmLaunch& g) {
     const int nt = mfma_ntiles(g.k);
@@ -1790,9 +2122,8 @@ hipError_t launch_gemm_mfma(const GemmLaunch& g) {
     a.y_f64 = g.y_f64;
     a.beta = g.beta;
     for (int b = 0; b < g.P; ++b) a.blk[b] = g.blk[b];
-    a.nrt = (g.m + kBM - 1) / kBM;
     a.nblk = (int)nblk;
-    const dim3 grid = mfma_grid(a);
+    const int waves = mfma_waves(g.m, S, nblk);
     const TraceEvents& tr = g.trace;
     if (tr.begin) (void)hipEventRecord(tr.begin, g.stream);
     if (mfma_packed(nt)) {
@@ -1805,8 +2136,8 @@ hipError_t launch_gemm_mfma(const GemmLaunch& g) {
         const hipError_t pe = hipGetLastError();
         if (pe != hipSuccess) return pe;
     }
-    hipError_t e = (g.omega == nullptr) ? dispatch_m<true>(nt, a, grid, g.stream)
-                                        : dispatch_m<false>(nt, a, grid, g.stream);
+    hipError_t e = (g.omega == nullptr) ? dispatch_m<true>(nt, waves, a, g.stream)
+                                        : dispatch_m<false>(nt, waves, a, g.stream);
     if (e != hipSuccess) return e;
     if (tr.mid) (void)hipEventRecord(tr.mid, g.stream);
     if (S > 1) e = launch_reduce_partials(a.partials, (int)S, g.m, g.k, g.Y, g.y_f64, g.ldy,
@@ -1817,18 +2148,25 @@ hipError_t launch_gemm_mfma(const GemmLaunch& g) {
 
 namespace {
 
-template <int NT>
-hipError_t run_mfma_batch(const BatchArgs& a, int grid, hipStream_t s) {
+template <int NT, bool FULL>
+hipError_t run_mfma_batch_f(const BatchArgs& a, int grid, hipStream_t s) {
     static const int per_cu = [] {
         int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_gemm_mfma_batch<NT>, kThreads, 0) !=
-            hipSuccess)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_gemm_mfma_batch<NT, FULL>, kThreads,
+                                                         0) != hipSuccess)
             n = 1;
         return n;
     }();
     grid = batch_grid(per_cu, a.total_tiles, grid);
-    hipLaunchKernelGGL((k_gemm_mfma_batch<NT>), dim3((unsigned)grid), dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL((k_gemm_mfma_batch<NT, FULL>), dim3((unsigned)grid), dim3(kThreads), 0, s, a);
     return hipGetLastError();
+}
+
+template <int NT>
+hipError_t run_mfma_batch(const BatchArgs& a, int grid, hipStream_t s) {
+    bool full = true;             // as launch_m
+    for (int q = 0; q < a.count; ++q) full = full && a.req[q].n >= kSplitKC;
+    return full ? run_mfma_batch_f<NT, true>(a, grid, s) : run_mfma_batch_f<NT, false>(a, grid, s);
 }
 
 }  // namespace
@@ -1883,8 +2221,7 @@ hipError_t launch_gemm_cm_mfma(const CmLaunch& g) {
     a.tiles = (int64_t)a.S * a.num_rb * ((g.k + BN - 1) / BN);
     a.tiles8 = (a.tiles + 7) / 8;
     hipError_t e;
-    constexpr int KCc = chunk_cols(8);
-    if (skinny || cm_packed(nt, g.m % 4 == 0 && g.n % KCc == 0)) {
+    if (skinny || cm_packed(nt, cm_full(g.m, g.n))) {
         // the call's Omega, once (the same plane as the row-major call's); the
         // few-row kernel copies it instead of generating in its workgroups
         PackArgs pk{};
