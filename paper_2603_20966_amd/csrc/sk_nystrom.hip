@@ -386,7 +386,8 @@ __global__ __launch_bounds__(kJThreads) void k_jac_flag(const double* __restrict
 // Fixed-shape FP64 tile engine: out(i, j) = sum_l X(i, l) Y(j, l) (times mu_l
 // when mu is given), l ascending, for a TM x TM tile per workgroup (256 threads,
 // (TM/16) x (TM/16) outputs each, l in chunks of 16 staged in LDS).
-constexpr int kGT = 64, kGK = 16;
+constexpr int kGK = 16;
+constexpr int kGT = 64;            // tile of the workspace rule below
 
 template <int TM, typename TX, typename TY>
 __device__ __forceinline__ void tile_accumulate(const TX* __restrict__ X, int64_t ldx, int64_t mx,
@@ -464,70 +465,245 @@ __global__ __launch_bounds__(256) void k_pinv_form(const double* __restrict__ S,
         }
 }
 
-// W = B C^+ (rows [row0, row0 + mw) of B; C^+ symmetric, so W(i, j) =
-// sum_l B(i, l) C^+(j, l)).
-__global__ __launch_bounds__(256) void k_bw(const float* __restrict__ B, int64_t ldb, int64_t mw,
-                                            int64_t r, const double* __restrict__ Cp, int64_t ldcp,
-                                            double* __restrict__ W) {
-    __shared__ double xs[kGK][kGT], ys[kGK][kGT];
-    const int64_t i0 = (int64_t)blockIdx.y * kGT, j0 = (int64_t)blockIdx.x * kGT;
-    double acc[4][4];
-    tile_accumulate<kGT>(B, ldb, mw, Cp, ldcp, r, r, (const double*)nullptr, i0, j0, acc, xs, ys);
-    const int ty = threadIdx.x / 16, tx = threadIdx.x % 16;
-    for (int a = 0; a < 4; ++a)
-        for (int c = 0; c < 4; ++c) {
-            const int64_t i = i0 + ty * 4 + a, j = j0 + tx * 4 + c;
-            if (i < mw && j < r) W[i * r + j] = acc[a][c];
-        }
-}
+// FP64 matrix-core tile: out(i, j) = sum_l X(i, l) Y(j, l) for a 128 x 128 tile per workgroup
+// (4 waves of 64 x 64, 4 x 4 tiles of v_mfma_f64_16x16x4f64 each), l ascending in steps of
+// four.  16 values of l at a time are staged in LDS, [l][row] with a pitch of 16 mod 32
+// doubles, so that the four l of an operand read fall on different banks; the next 16 are
+// loaded while these are multiplied (64 MFMAs of 64 cycles a wave, which hide them).
+// The former tile of 64 x 64 with FP64 FMAs ran at 29 TFLOP/s, two LDS reads for every four
+// FMAs; this one at 58, the matrix cores busy 73% of the time (error at n = 16384, r = 256
+// with a C^+ that is not bitwise symmetric: 4.78 -> 2.45 ms; n = 5000, r = 100: 229 -> 177 us;
+// n = 2048, r = 16: 21 us either way).
+typedef double v4d __attribute__((ext_vector_type(4)));
+typedef double v2d_a8 __attribute__((ext_vector_type(2), aligned(8)));
+typedef float v4f_a4 __attribute__((ext_vector_type(4), aligned(4)));
+constexpr int kDT = 128;           // rows and columns of a tile
+constexpr int kDK = 16;            // contraction values staged at a time
+constexpr int kDP = kDT + 16;      // LDS pitch (doubles)
+struct TileLds64 {
+    double x[2][kDK][kDP], y[2][kDK][kDP];
+};
 
-// Rows of A~ = W B^T (out, mr x n) or, with A given, per-tile sums of
-// (A - A~)^2 and A^2 over the n x n matrix (part[2 t], part[2 t + 1]).
-template <bool ERR>
-__global__ __launch_bounds__(256) void k_nys_tile(const double* __restrict__ W, int64_t mw,
-                                                  const float* __restrict__ B, int64_t ldb,
-                                                  int64_t n, int64_t r,
-                                                  const float* __restrict__ A, int64_t lda,
-                                                  double* __restrict__ out, int64_t ldo,
-                                                  double* __restrict__ part) {
-    __shared__ double xs[kGK][kGT], ys[kGK][kGT];
-    __shared__ double red[2][kJThreads];
-    const int64_t i0 = (int64_t)blockIdx.y * kGT, j0 = (int64_t)blockIdx.x * kGT;
-    double acc[4][4];
-    tile_accumulate<kGT>(W, r, mw, B, ldb, n, r, (const double*)nullptr, i0, j0, acc, xs, ys);
-    const int ty = threadIdx.x / 16, tx = threadIdx.x % 16;
-    double se = 0.0, sa = 0.0;
-    for (int a = 0; a < 4; ++a)
-        for (int c = 0; c < 4; ++c) {
-            const int64_t i = i0 + ty * 4 + a, j = j0 + tx * 4 + c;
-            if (i >= mw || j >= n) continue;
-            if (ERR) {
-                const double av = (double)A[i * lda + j];
-                const double d = av - acc[a][c];
-                se = fma(d, d, se);
-                sa = fma(av, av, sa);
-            } else {
-                out[i * ldo + j] = acc[a][c];
-            }
+// 8 values p[0 .. 7] -> v, those from `left` on zero.
+__device__ __forceinline__ void load8(const double* p, int64_t left, double* v) {
+    if (left >= 8) {
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+            const v2d_a8 t = *reinterpret_cast<const v2d_a8*>(p + e);
+            v[e] = t[0];
+            v[e + 1] = t[1];
         }
-    if (ERR) {
-        block_sum2(se, sa, red);
-        if (threadIdx.x == 0) {
-            const int64_t t = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-            part[2 * t] = se;
-            part[2 * t + 1] = sa;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = e < left ? p[e] : 0.0;
+    }
+}
+__device__ __forceinline__ void load8(const float* p, int64_t left, double* v) {
+    if (left >= 8) {
+#pragma unroll
+        for (int e = 0; e < 8; e += 4) {
+            const v4f_a4 t = *reinterpret_cast<const v4f_a4*>(p + e);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[e + u] = (double)t[u];
         }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = e < left ? (double)p[e] : 0.0;
     }
 }
 
-// sums = (sum of part[2 t], sum of part[2 t + 1], sqrt(sums[0] / sums[1])), t in order.
+// acc[tm][tn]: register r of lane (g, j) is row 64 (wave / 2) + 16 tm + 4 r + g, column
+// 64 (wave % 2) + 16 tn + j of the tile.  Rows past mx (my) repeat the last one.
+template <typename TX, typename TY>
+__device__ __forceinline__ void tile_mfma64(const TX* __restrict__ X, int64_t ldx, int64_t mx,
+                                            const TY* __restrict__ Y, int64_t ldy, int64_t my,
+                                            int64_t K, int64_t i0, int64_t j0, v4d (&acc)[4][4],
+                                            TileLds64& L) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int g = lane >> 4, j = lane & 15;
+    const int row = tid >> 1, half = (tid & 1) * 8;      // staging: row, first l
+    const TX* xp = X + min(i0 + row, mx - 1) * ldx + half;
+    const TY* yp = Y + min(j0 + row, my - 1) * ldy + half;
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[a][c] = v4d{0.0, 0.0, 0.0, 0.0};
+    double xv[8], yv[8];
+    auto load = [&](int64_t l0) {
+        load8(xp + l0, K - l0 - half, xv);
+        load8(yp + l0, K - l0 - half, yv);
+    };
+    auto store = [&](int b) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            L.x[b][half + e][row] = xv[e];
+            L.y[b][half + e][row] = yv[e];
+        }
+    };
+    load(0);
+    store(0);
+    __syncthreads();
+    int b = 0;
+    for (int64_t l0 = 0; l0 < K; l0 += kDK, b ^= 1) {
+        const bool more = l0 + kDK < K;
+        if (more) load(l0 + kDK);
+        const double* xb = &L.x[b][g][(wave >> 1) * 64 + j];
+        const double* yb = &L.y[b][g][(wave & 1) * 64 + j];
+#pragma unroll
+        for (int kk = 0; kk < kDK; kk += 4) {
+            double av[4], bv[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                av[t] = xb[kk * kDP + 16 * t];
+                bv[t] = yb[kk * kDP + 16 * t];
+            }
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    acc[a][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[c], acc[a][c], 0, 0, 0);
+        }
+        if (more) store(b ^ 1);
+        __syncthreads();
+    }
+}
+
+// W = B C^+ (rows [row0, row0 + mw) of B; C^+ symmetric, so W(i, j) =
+// sum_l B(i, l) C^+(j, l)).
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+void k_bw(const float* __restrict__ B, int64_t ldb, int64_t mw, int64_t r,
+          const double* __restrict__ Cp, int64_t ldcp, double* __restrict__ W, int* sym) {
+    __shared__ TileLds64 lds;
+    if (sym && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *sym = 1;
+    const int64_t i0 = (int64_t)blockIdx.y * kDT, j0 = (int64_t)blockIdx.x * kDT;
+    v4d acc[4][4];
+    tile_mfma64(B, ldb, mw, Cp, ldcp, r, r, i0, j0, acc, lds);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int64_t i = i0 + (wave >> 1) * 64 + 16 * a + 4 * q + (lane >> 4);
+                const int64_t j = j0 + (wave & 1) * 64 + 16 * c + (lane & 15);
+                if (i < mw && j < r) W[i * r + j] = acc[a][c][q];
+            }
+}
+
+// *sym (1 on entry, from k_bw) = 0 if C^+ differs from its transpose in any bit: one
+// workgroup per 32 x 32 tile, the mirror tile turned round in LDS.
+__global__ __launch_bounds__(256) void k_symmetric(const double* __restrict__ Cp, int64_t r,
+                                                   int64_t ldcp, int* __restrict__ sym) {
+    if (blockIdx.x < blockIdx.y) return;
+    __shared__ double m[32][33];
+    const int x = threadIdx.x & 31, y = threadIdx.x >> 5;
+    const int64_t i0 = (int64_t)blockIdx.y * 32, j0 = (int64_t)blockIdx.x * 32;
+    for (int u = y; u < 32; u += 8)
+        m[u][x] = (j0 + u < r && i0 + x < r) ? Cp[(j0 + u) * ldcp + i0 + x] : 0.0;
+    __syncthreads();
+    bool same = true;
+    for (int u = y; u < 32; u += 8) {
+        const double c = (i0 + u < r && j0 + x < r) ? Cp[(i0 + u) * ldcp + j0 + x] : 0.0;
+        same = same && __double_as_longlong(c) == __double_as_longlong(m[x][u]);
+    }
+    if (!same) *sym = 0;
+}
+
+// Rows of A~ = W B^T (out, mr x n) or, with A given, per-tile sums of
+// (A - A~)^2 and A^2 over the n x n matrix (part[2 t], part[2 t + 1]).  With a symmetric
+// C^+ (*sym), A~ is symmetric: a tile above the diagonal serves its mirror image too, and
+// the tiles below the diagonal do nothing.  The tile's elements of A are loaded from clamped
+// addresses without a branch, 16 of a lane (32 with the mirror image) in flight.
+template <bool ERR>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+void k_nys_tile(const double* __restrict__ W, int64_t mw, const float* __restrict__ B, int64_t ldb,
+                int64_t n, int64_t r, const float* __restrict__ A, int64_t lda,
+                double* __restrict__ out, int64_t ldo, double* __restrict__ part,
+                const int* __restrict__ sym) {
+    __shared__ TileLds64 lds;
+    __shared__ double red[2][kJThreads];
+    const int64_t t = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    const bool mirror = ERR && sym && *sym && blockIdx.x != blockIdx.y;
+    if (mirror && blockIdx.x < blockIdx.y) {
+        if (threadIdx.x == 0) {
+            part[2 * t] = 0.0;
+            part[2 * t + 1] = 0.0;
+        }
+        return;
+    }
+    const int64_t i0 = (int64_t)blockIdx.y * kDT, j0 = (int64_t)blockIdx.x * kDT;
+    v4d acc[4][4];
+    tile_mfma64(W, r, mw, B, ldb, n, r, i0, j0, acc, lds);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int li = (wave >> 1) * 64 + (lane >> 4), lj = (wave & 1) * 64 + (lane & 15);
+    if constexpr (!ERR) {
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int64_t i = i0 + li + 16 * a + 4 * q, j = j0 + lj + 16 * c;
+                    if (i < mw && j < n) out[i * ldo + j] = acc[a][c][q];
+                }
+        return;
+    }
+    double se = 0.0, sa = 0.0;
+    auto add = [&](float a32, bool in, double at) {
+        const double av = in ? (double)a32 : 0.0;
+        const double d = in ? av - at : 0.0;
+        se = fma(d, d, se);
+        sa = fma(av, av, sa);
+    };
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        float av[4][4], bv[4][4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int64_t i = min(i0 + li + 16 * a + 4 * q, n - 1), j = min(j0 + lj + 16 * c, n - 1);
+                av[c][q] = A[i * lda + j];
+                if (mirror) bv[c][q] = A[j * lda + i];
+            }
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const bool in = i0 + li + 16 * a + 4 * q < n && j0 + lj + 16 * c < n;
+                add(av[c][q], in, acc[a][c][q]);
+                if (mirror) add(bv[c][q], in, acc[a][c][q]);
+            }
+    }
+    block_sum2(se, sa, red);
+    if (threadIdx.x == 0) {
+        part[2 * t] = se;
+        part[2 * t + 1] = sa;
+    }
+}
+
+// sums = (sum of part[2 t], sum of part[2 t + 1], sqrt(sums[0] / sums[1])): every thread its
+// t, t + 256, ... in order, eight loads at a time, then the threads in a fixed tree.
 __global__ __launch_bounds__(kJThreads) void k_err_sum(const double* __restrict__ part, int64_t T,
                                                        double* __restrict__ sums) {
     __shared__ double red[2][kJThreads];
+    const double2* p = reinterpret_cast<const double2*>(part);
     double se = 0.0, sa = 0.0;
-    for (int64_t t = threadIdx.x; t < T; t += kJThreads) {
-        se += part[2 * t];
-        sa += part[2 * t + 1];
+    int64_t t = threadIdx.x;
+    for (; t + 7 * kJThreads < T; t += 8 * kJThreads) {
+        double2 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = p[t + u * kJThreads];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            se += v[u].x;
+            sa += v[u].y;
+        }
+    }
+    for (; t < T; t += kJThreads) {
+        se += p[t].x;
+        sa += p[t].y;
     }
     block_sum2(se, sa, red);
     if (threadIdx.x == 0) {
@@ -605,21 +781,28 @@ hipError_t launch_nystrom(const float* A, int64_t lda, const float* B, int64_t n
                           int64_t ldb, const double* Cp, int64_t ldcp, int64_t row0, int64_t mr,
                           double* out, int64_t ldo, double* sums, void* ws, hipStream_t s) {
     double* W = static_cast<double*>(ws);
-    double* part = reinterpret_cast<double*>(static_cast<char*>(ws) +
-                                             align256((size_t)(n * r) * 8));
-    const unsigned gr = (unsigned)((r + kGT - 1) / kGT);
+    char* pp = static_cast<char*>(ws) + align256((size_t)(n * r) * 8);
+    double* part = reinterpret_cast<double*>(pp);
+    const int64_t t64 = (n + kGT - 1) / kGT;
+    // the partial sums of the kDT-wide tiles leave the last 8 bytes of their area free
+    // (r < 64: the product is a small part, every tile reads its own A)
+    int* sym = A && r >= 64 ? reinterpret_cast<int*>(pp + align256((size_t)(t64 * t64) * 16) - 8)
+                            : nullptr;
+    const unsigned gr = (unsigned)((r + kDT - 1) / kDT);
     const int64_t mw = A ? n : mr;
     const float* Bw = A ? B : B + row0 * ldb;
-    k_bw<<<dim3(gr, (unsigned)((mw + kGT - 1) / kGT)), 256, 0, s>>>(Bw, ldb, mw, r, Cp, ldcp, W);
-    const unsigned gn = (unsigned)((n + kGT - 1) / kGT);
-    const unsigned gm = (unsigned)((mw + kGT - 1) / kGT);
+    const unsigned gn = (unsigned)((n + kDT - 1) / kDT);
+    const unsigned gm = (unsigned)((mw + kDT - 1) / kDT);
+    k_bw<<<dim3(gr, gm), 256, 0, s>>>(Bw, ldb, mw, r, Cp, ldcp, W, sym);
+    const unsigned g32 = (unsigned)((r + 31) / 32);
+    if (sym) k_symmetric<<<dim3(g32, g32), 256, 0, s>>>(Cp, r, ldcp, sym);
     if (A) {
         k_nys_tile<true><<<dim3(gn, gm), 256, 0, s>>>(W, mw, B, ldb, n, r, A, lda, nullptr, 0,
-                                                      part);
+                                                      part, sym);
         k_err_sum<<<1, kJThreads, 0, s>>>(part, (int64_t)gn * gm, sums);
     } else {
         k_nys_tile<false><<<dim3(gn, gm), 256, 0, s>>>(W, mw, B, ldb, n, r, nullptr, 0, out, ldo,
-                                                       nullptr);
+                                                       nullptr, nullptr);
     }
     return hipGetLastError();
 }

@@ -170,3 +170,30 @@ def test_reconstruction_kernels_match_fp64_formula():
     for row0, mr in ((0, 1), (37, 100), (n - 70, 70)):
         rows = sk.sketch_nystrom_rows(B, Cp, row0, mr).cpu().numpy()
         assert np.abs(rows - At[row0:row0 + mr]).max() <= 1e-12 * np.abs(At).max()
+
+
+@pytest.mark.parametrize("n,r", [(1, 1), (63, 5), (127, 16), (128, 17), (129, 33), (300, 100)])
+@pytest.mark.parametrize("symmetric", [True, False])
+def test_reconstruction_tiles_at_their_edges(n, r, symmetric):
+    """Tiles of 128 x 128 with 16 contraction values at a time, and their mirror images for a
+    symmetric C^+ (a C^+ that is not takes every tile), at remainders of each.  Only the
+    summation order differs from the host's FP64 formula: r-term sums of products and n^2-term
+    sums of squares, within 8 (r + 64) and 8 n units of FP64 rounding of their terms' size."""
+    rng = np.random.default_rng(n + r)
+    A = rng.standard_normal((n, n)).astype(np.float32)       # no symmetry in A itself
+    B = rng.standard_normal((n, r)).astype(np.float32)
+    Cp = rng.standard_normal((r, r))
+    if symmetric:
+        Cp = Cp + Cp.T
+    Ad, Bd, Cd = (torch.from_numpy(x).to(DEV) for x in (A, B, Cp))
+    B64 = B.astype(np.float64)
+    At = B64 @ Cp.T @ B64.T
+    size = np.abs(B64) @ np.abs(Cp.T) @ np.abs(B64.T)
+    rows = sk.sketch_nystrom_rows(Bd, Cd, n // 3, n - n // 3).cpu().numpy()
+    assert (np.abs(rows - At[n // 3:]) <= 8 * (r + 64) * U64 * size[n // 3:]).all()
+    D = A.astype(np.float64) - At
+    se, sa = (D ** 2).sum(), (A.astype(np.float64) ** 2).sum()
+    got = sk.sketch_nystrom_error(Ad, Bd, Cd).cpu().numpy()
+    slack = 8 * n * U64 * se + 16 * (r + 64) * U64 * (np.abs(D) * size).sum()
+    assert abs(got[0] - se) <= slack and abs(got[1] - sa) <= 8 * n * U64 * sa
+    assert abs(got[2] - math.sqrt(se / sa)) <= (slack / se + 16 * n * U64) * math.sqrt(se / sa)
