@@ -335,7 +335,9 @@ int sketch_quantize(const float* A, int64_t m, int64_t n, int64_t lda, int dst_d
  *   8 Rp 2^-53 ||S||_F, Rp = r rounded up to a multiple of 32, or after
  *   max_sweeps sweeps), then
  *   Cp = V diag(mu) V^T, mu_i = 1 / lambda_i if |lambda_i| > tol max_j |lambda_j|,
- *   else 0.
+ *   else 0.  When the eigenvalues are not asked for and an a posteriori bound shows
+ *   that none of them is cut, Cp is formed directly as the inverse of S, which it then
+ *   is (no sweep runs).
  *   C     device, r x r row-major, leading dim ldc >= r, storage c_dtype
  *         (SK_Y_F32 or SK_Y_F64); only read.
  *   r     0 <= r <= 1024 (r = 0: nothing is done).
@@ -344,7 +346,8 @@ int sketch_quantize(const float* A, int64_t m, int64_t n, int64_t lda, int dst_d
  *   Cp    device, r x r FP64 row-major, leading dim ldcp >= r; exactly
  *         symmetric.
  *   eigvals  device FP64 array of r (the lambda_i, unsorted) or NULL.
- *   info  device int32[2] or NULL: (sweeps run, 1 if converged else 0).
+ *   info  device int32[2] or NULL: (sweeps run, 1 if converged else 0); (0, 1) for a
+ *         core that was inverted directly.
  *   workspace  device, at least sketch_core_pinv_workspace(r) bytes
  *         (16-byte aligned); its contents on entry do not matter.
  *   Errors: SK_EDTYPE, SK_EINVAL (sizes, tol, max_sweeps, NULL buffers),

@@ -2,7 +2,8 @@
 // the core C = Omega^T B (both from the product kernels), the approximation is
 // A~ = B C^+ B^T.  This file holds the rest of it on the device, in FP64:
 //
-//   * the pseudo-inverse of the symmetric r x r core by a parallel block Jacobi
+//   * the pseudo-inverse of the symmetric r x r core: its inverse where no eigenvalue
+//     is cut, else by a parallel block Jacobi
 //     eigensolver (two-sided, cyclic round-robin over 16-row blocks), with the
 //     eigenvalue cut of Sec. 6.2: eigenvalues of modulus at most tol times the
 //     largest are treated as zero;
@@ -36,7 +37,6 @@ constexpr int kJB = 16;            // rows of a Jacobi block
 constexpr int kJT = 2 * kJB;       // rows of a pair tile
 constexpr int kJP = kJT + 1;       // LDS row pitch of a tile (doubles)
 constexpr int kJThreads = 256;
-constexpr int kPerThread = kJT * kJT / kJThreads;   // tile elements per thread (4)
 
 // Circle-method pairing of nb (even) players at round s in [0, nb - 1): player 0
 // meets 1 + s; for i >= 1 the players 1 + (s + i) mod (nb - 1) and
@@ -60,7 +60,12 @@ __device__ __forceinline__ int64_t tile_row(int I, int J, int t) {
 struct JacState {
     int converged;      // set once the off-diagonal norm is small enough
     int sweeps;         // sweeps run before convergence
+    int inverse;        // C^+ is the inverse of S (no eigenvalue is cut), left in S
+    // of k_jac_sweep, zero between sweeps
+    unsigned ticket;    // workgroups started
+    alignas(128) unsigned solved;    // pair solves done, over all steps so far
 };
+static_assert(sizeof(JacState) <= 256, "the state's area of the workspace");
 
 // S = (C + C^T)/2 padded to Rp x Rp, V = I, state cleared.
 template <typename TC>
@@ -71,6 +76,9 @@ __global__ __launch_bounds__(256) void k_jac_init(const TC* __restrict__ C, int6
     if (e == 0) {
         st->converged = 0;
         st->sweeps = 0;
+        st->inverse = 0;
+        st->ticket = 0;
+        st->solved = 0;
     }
     if (e >= Rp * Rp) return;
     const int64_t i = e / Rp, j = e % Rp;
@@ -88,6 +96,12 @@ __device__ __forceinline__ double rsqrt_nr(double x) {
         const double e = fma(-(x * y), y, 1.0);
         y = fma(0.5 * y, e, y);
     }
+    return y;
+}
+
+__device__ __forceinline__ double rcp_nr(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    for (int i = 0; i < 2; ++i) y = fma(fma(-x, y, 1.0), y, y);
     return y;
 }
 
@@ -171,24 +185,47 @@ constexpr int rounds() { return MODE == kFull ? kJT - 1 : kJB; }
 // every block, and moves the entries to their next positions through LDS.
 constexpr int kSolveThreads = 2 * kJThreads;
 
-template <int MODE>
-__global__ __launch_bounds__(kSolveThreads) void k_jac_solve(const double* __restrict__ S,
-                                                             int64_t Rp, double* __restrict__ Q,
-                                                             int nb, int step, const JacState* st) {
-    if (st->converged) return;
-    __shared__ double al[kJT][kJP];
-    __shared__ double ql[kJT][kJP];
-    __shared__ double rc[kJT / 2], rs[kJT / 2];
+// Accesses to S, V, Q and the norms.  SH: they pass between workgroups inside a launch
+// (k_jac_sweep) and go to the device's point of coherence, so that neither side has to
+// write back or invalidate a whole L2 around them (with plain accesses under device-scope
+// fences r = 256 took 7.7 ms instead of 4.7).
+template <bool SH>
+__device__ __forceinline__ double mem_load(const double* p) {
+    if constexpr (SH) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else return *p;
+}
+template <bool SH>
+__device__ __forceinline__ void mem_store(double* p, double v) {
+    if constexpr (SH) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *p = v;
+}
+
+struct SolveLds {
+    // rc and rs far apart: combined into one two-address access, their latency sits in the
+    // chain of every round (14.2 us a solve against 13.7)
+    double rc[kJT / 2];
+    double al[kJT][kJP];
+    double ql[kJT][kJP];
+    double rs[kJT / 2];
+};
+
+template <int MODE, bool SH>
+__device__ __forceinline__ void jac_solve(const double* S, int64_t Rp, double* Q, int nb, int step,
+                                          int pair, SolveLds& L) {
+    double (*al)[kJP] = L.al;
+    double (*ql)[kJP] = L.ql;
+    double* rc = L.rc;
+    double* rs = L.rs;
     const bool qrole = threadIdx.x >= kJThreads;
     const int tid = threadIdx.x & (kJThreads - 1), X = tid / 16, Y = tid % 16;
     int I, J;
-    pair_blocks<MODE>(nb, step, blockIdx.x, I, J);
+    pair_blocks<MODE>(nb, step, pair, I, J);
     double a[2][2];
     for (int u = 0; u < 2; ++u)
         for (int v = 0; v < 2; ++v)
             a[u][v] = qrole ? ((2 * X + u == 2 * Y + v) ? 1.0 : 0.0)
-                            : S[tile_row(I, J, tile_index<MODE>(2 * X + u)) * Rp +
-                                tile_row(I, J, tile_index<MODE>(2 * Y + v))];
+                            : mem_load<SH>(S + tile_row(I, J, tile_index<MODE>(2 * X + u)) * Rp +
+                                          tile_row(I, J, tile_index<MODE>(2 * Y + v)));
     int sx[2], sy[2];
     for (int u = 0; u < 2; ++u) {
         sx[u] = qrole ? 2 * X + u : sigma<MODE>(2 * X + u);    // Q's rows do not move
@@ -233,20 +270,21 @@ __global__ __launch_bounds__(kSolveThreads) void k_jac_solve(const double* __res
             for (int v = 0; v < 2; ++v) a[u][v] = buf[2 * X + u][2 * Y + v];
     }
     if (qrole) {        // back at the starting positions: Q in tile-index order
-        double* Qp = Q + (int64_t)blockIdx.x * kJT * kJT;
+        double* Qp = Q + (int64_t)pair * kJT * kJT;
         for (int u = 0; u < 2; ++u)
             for (int v = 0; v < 2; ++v)
-                Qp[tile_index<MODE>(2 * X + u) * kJT + tile_index<MODE>(2 * Y + v)] = a[u][v];
+                mem_store<SH>(Qp + tile_index<MODE>(2 * X + u) * kJT + tile_index<MODE>(2 * Y + v), a[u][v]);
     }
 }
 
-// Fixed-order workgroup sum of two doubles per thread (256 threads).
-__device__ __forceinline__ void block_sum2(double& x, double& y, double (*red)[kJThreads]) {
+// Fixed-order workgroup sum of two doubles per thread.
+template <int TH>
+__device__ __forceinline__ void block_sum2(double& x, double& y, double (*red)[TH]) {
     const int tid = threadIdx.x;
     red[0][tid] = x;
     red[1][tid] = y;
     __syncthreads();
-    for (int w = kJThreads / 2; w > 0; w >>= 1) {
+    for (int w = TH / 2; w > 0; w >>= 1) {
         if (tid < w) {
             red[0][tid] += red[0][tid + w];
             red[1][tid] += red[1][tid + w];
@@ -257,9 +295,275 @@ __device__ __forceinline__ void block_sum2(double& x, double& y, double (*red)[k
     y = red[1][0];
 }
 
-// S <- Q^T S Q over the upper pair-tiles (blocks [0, nT)) and V <- V Q over
-// 32-row blocks of V (blocks [nT, nT + nV)).  Each S tile also writes its
+// S <- Q^T S Q over the upper pair-tiles (b in [0, nT)) and V <- V Q over
+// 32-row blocks of V (b in [nT, nT + nV)).  Each S tile also writes its
 // squared off-diagonal and total norms (mirror counted) to part[2 b], part[2 b + 1].
+// TH threads: thread (ti, tj) forms rows ti, ti + TH/16, ... and columns tj, tj + 16.
+template <int TH>
+struct ApplyLds {
+    double x[kJT][kJP], qa[kJT][kJP], qb[kJT][kJP], u[kJT][kJP];
+    double red[2][TH];
+};
+
+// Blocks of rows (Ia, Ja) and columns (Ib, Jb) of piece b: of S, or of V (rows 32 rb ..).
+struct Piece {
+    bool s;
+    int pa, pb, rb;
+    int Ia, Ja, Ib, Jb;
+};
+template <int MODE>
+__device__ __forceinline__ Piece jac_piece(int nb, int step, int b) {
+    const int np = nb / 2, nT = np * (np + 1) / 2;
+    Piece p{};
+    p.s = b < nT;
+    if (p.s) {
+        while (b >= np - p.pa) {
+            b -= np - p.pa;
+            ++p.pa;
+        }
+        p.pb = p.pa + b;
+        pair_blocks<MODE>(nb, step, p.pa, p.Ia, p.Ja);
+        pair_blocks<MODE>(nb, step, p.pb, p.Ib, p.Jb);
+    } else {
+        p.rb = (b - nT) / np;
+        p.pa = (b - nT) % np;
+        pair_blocks<MODE>(nb, step, p.pa, p.Ib, p.Jb);
+    }
+    return p;
+}
+
+// Element (i, j) of the piece's tile of S or V.
+template <bool SH>
+__device__ __forceinline__ double piece_s(const double* S, int64_t Rp, const Piece& p, int i, int j) {
+    return mem_load<SH>(S + tile_row(p.Ia, p.Ja, i) * Rp + tile_row(p.Ib, p.Jb, j));
+}
+template <bool SH>
+__device__ __forceinline__ double piece_v(const double* V, int64_t Rp, const Piece& p, int i, int j) {
+    return mem_load<SH>(V + ((int64_t)p.rb * kJT + i) * Rp + tile_row(p.Ib, p.Jb, j));
+}
+
+// The piece's tile -> L.x, ahead of jac_apply<..., PRE = true>.
+template <bool SH, int TH>
+__device__ __forceinline__ void jac_apply_load(const double* S, const double* V, int64_t Rp,
+                                               const Piece& p, ApplyLds<TH>& L) {
+    if (p.s) {
+#pragma unroll
+        for (int v = 0; v < kJT * kJT / TH; ++v) {
+            const int e = threadIdx.x + TH * v, i = e / kJT, j = e % kJT;
+            L.x[i][j] = piece_s<SH>(S, Rp, p, i, j);
+        }
+    } else {
+#pragma unroll
+        for (int v = 0; v < kJT * kJT / TH; ++v) {
+            const int e = threadIdx.x + TH * v, i = e / kJT, j = e % kJT;
+            L.x[i][j] = piece_v<SH>(V, Rp, p, i, j);
+        }
+    }
+}
+
+template <bool SH, bool PRE, int TH>
+__device__ __forceinline__ void jac_apply(double* S, double* V, int64_t Rp, const double* Q,
+                                          const Piece& p, int b, double* part, ApplyLds<TH>& L) {
+    constexpr int RS = TH / 16, RN = kJT / RS;            // row step, rows per thread
+    const int tid = threadIdx.x;
+    const int ti = tid / 16, tj = tid % 16;
+    const double* Qa = Q + (int64_t)p.pa * kJT * kJT;
+    const double* Qb = Q + (int64_t)p.pb * kJT * kJT;
+    if (p.s) {
+#pragma unroll
+        for (int v = 0; v < kJT * kJT / TH; ++v) {
+            const int e = tid + TH * v, i = e / kJT, j = e % kJT;
+            if constexpr (!PRE) L.x[i][j] = piece_s<SH>(S, Rp, p, i, j);
+            L.qa[i][j] = mem_load<SH>(Qa + e);
+            L.qb[i][j] = mem_load<SH>(Qb + e);
+        }
+    } else {
+#pragma unroll
+        for (int v = 0; v < kJT * kJT / TH; ++v) {
+            const int e = tid + TH * v, i = e / kJT, j = e % kJT;
+            if constexpr (!PRE) L.x[i][j] = piece_v<SH>(V, Rp, p, i, j);
+            L.qb[i][j] = mem_load<SH>(Qa + e);
+        }
+    }
+    __syncthreads();
+    double acc[RN][2];
+#pragma unroll
+    for (int a = 0; a < RN; ++a) acc[a][0] = acc[a][1] = 0.0;
+    for (int z = 0; z < kJT; ++z) {                       // U = X Q_b (V Q)
+        const double q0 = L.qb[z][tj], q1 = L.qb[z][tj + 16];
+#pragma unroll
+        for (int a = 0; a < RN; ++a) {
+            const double xv = L.x[ti + RS * a][z];
+            acc[a][0] = fma(xv, q0, acc[a][0]);
+            acc[a][1] = fma(xv, q1, acc[a][1]);
+        }
+    }
+    if (!p.s) {
+#pragma unroll
+        for (int a = 0; a < RN; ++a)
+            for (int c = 0; c < 2; ++c)
+                mem_store<SH>(V + ((int64_t)p.rb * kJT + ti + RS * a) * Rp + tile_row(p.Ib, p.Jb, tj + 16 * c),
+                              acc[a][c]);
+        return;
+    }
+#pragma unroll
+    for (int a = 0; a < RN; ++a) {
+        L.u[ti + RS * a][tj] = acc[a][0];
+        L.u[ti + RS * a][tj + 16] = acc[a][1];
+        acc[a][0] = acc[a][1] = 0.0;
+    }
+    __syncthreads();
+    for (int z = 0; z < kJT; ++z) {                       // T = Q_a^T U
+        const double u0 = L.u[z][tj], u1 = L.u[z][tj + 16];
+#pragma unroll
+        for (int a = 0; a < RN; ++a) {
+            const double q = L.qa[z][ti + RS * a];
+            acc[a][0] = fma(q, u0, acc[a][0]);
+            acc[a][1] = fma(q, u1, acc[a][1]);
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < RN; ++a) {                        // every reader of X is past the barrier
+        L.x[ti + RS * a][tj] = acc[a][0];
+        L.x[ti + RS * a][tj + 16] = acc[a][1];
+    }
+    __syncthreads();
+    double off = 0.0, tot = 0.0;
+#pragma unroll
+    for (int v = 0; v < kJT * kJT / TH; ++v) {
+        const int e = tid + TH * v, i = e / kJT, j = e % kJT;
+        const int64_t gi = tile_row(p.Ia, p.Ja, i), gj = tile_row(p.Ib, p.Jb, j);
+        if (p.pa == p.pb) {
+            const double t = i <= j ? L.x[i][j] : L.x[j][i];
+            mem_store<SH>(S + gi * Rp + gj, t);
+            tot += t * t;
+            if (i != j) off += t * t;
+        } else {
+            const double t = L.x[i][j];
+            mem_store<SH>(S + gi * Rp + gj, t);
+            mem_store<SH>(S + gj * Rp + gi, t);
+            tot += 2.0 * t * t;
+            off += 2.0 * t * t;
+        }
+    }
+    block_sum2(off, tot, L.red);
+    if (tid == 0) {
+        mem_store<SH>(part + 2 * b, off);
+        mem_store<SH>(part + 2 * b + 1, tot);
+    }
+}
+
+// One sweep in one launch (r <= kSweepMaxR): the kFull step, then nb - 1 kCross steps (none
+// if nb == 2), each np solves and nT + nV applied tiles, and at last the convergence test.
+// A workgroup takes the next piece of work in that order when it starts (a ticket), and
+// waits only for pieces before its own: a solve for every tile of the step before, an applied
+// tile for the solves of its step.  Whoever holds a smaller ticket has started already and
+// itself waits only for still smaller ones, so the first unfinished piece always runs and
+// every wait ends, whatever the order or the number of workgroups that the device keeps
+// resident.  Solves count up one counter; applied tiles, of which there are many, each set
+// their own flag (done[b] = steps finished since the first sweep began), as additions to one
+// address come one at a time.
+// After convergence, or when the inverse was taken, a sweep then costs one short launch
+// (2.9 us) instead of 2 nb + 1 of 2.7 us each (r = 256, 16 sweeps: 1.4 ms of the inverse's
+// 1.6).  While sweeps run it takes as long as separate launches (a singular core, the
+// inverse's attempt included: r = 64 943 us against 961, r = 160 2824 against 2817, r = 256
+// 4692 against 4461); with many tiles the tickets take longer than the tiles, and larger
+// cores keep the launches.
+constexpr int64_t kSweepMaxR = 256;
+
+__device__ __forceinline__ void wait_solved(unsigned* solved, unsigned target, unsigned near) {
+    if (threadIdx.x == 0) {
+        for (;;) {
+            const unsigned v = __hip_atomic_load(solved, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (v >= target) break;
+            // a step or more away: look seldom, the counter's own traffic goes first
+            if (target - v > near) __builtin_amdgcn_s_sleep(127);
+            else __builtin_amdgcn_s_sleep(2);
+        }
+    }
+    __syncthreads();
+}
+
+__device__ __forceinline__ void wait_applied(const unsigned* done, unsigned nA, unsigned target) {
+    for (;;) {
+        bool ok = true;
+        unsigned least = target;
+        for (unsigned b = threadIdx.x; b < nA; b += kSolveThreads) {
+            const unsigned v = __hip_atomic_load(done + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            ok = ok && v >= target;
+            least = min(least, v);
+        }
+        if (__syncthreads_and(ok)) break;
+        if (__syncthreads_or(least + 1 < target)) __builtin_amdgcn_s_sleep(127);
+        else __builtin_amdgcn_s_sleep(2);
+    }
+}
+
+__global__ __launch_bounds__(kSolveThreads) void k_jac_sweep(double* S, double* V, int64_t Rp, double* Q,
+                                                             int nb, double* part, double tolc,
+                                                             unsigned* done, JacState* st) {
+    if (st->converged) return;
+    __shared__ union {
+        SolveLds solve;
+        ApplyLds<kSolveThreads> apply;
+    } lds;
+    __shared__ unsigned word;
+    const unsigned np = (unsigned)nb / 2, nT = np * (np + 1) / 2, nA = nT + np * np;
+    const unsigned steps = nb > 2 ? (unsigned)nb : 1u;
+    const unsigned base = (unsigned)st->sweeps * steps;      // steps before this sweep
+    if (threadIdx.x == 0)
+        word = __hip_atomic_fetch_add(&st->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const unsigned step = word / (np + nA), piece = word % (np + nA);
+    if (step == steps) {         // the last ticket: end of the sweep
+        wait_applied(done, nA, base + steps);
+        double off = 0.0, tot = 0.0;
+        for (unsigned i = threadIdx.x; i < nT; i += kSolveThreads) {
+            off += mem_load<true>(part + 2 * i);
+            tot += mem_load<true>(part + 2 * i + 1);
+        }
+        block_sum2(off, tot, lds.apply.red);
+        if (threadIdx.x == 0) {
+            st->sweeps += 1;
+            st->ticket = 0;
+            st->solved = 0;
+            if (off <= tolc * tolc * tot) st->converged = 1;
+        }
+    } else if (piece < np) {
+        wait_applied(done, nA, base + step);
+        if (step == 0) jac_solve<kFull, true>(S, Rp, Q, nb, 0, (int)piece, lds.solve);
+        else jac_solve<kCross, true>(S, Rp, Q, nb, (int)step - 1, (int)piece, lds.solve);
+        // every wave's stores have reached the point of coherence before the count moves
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (threadIdx.x == 0)
+            __hip_atomic_fetch_add(&st->solved, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+        // the tile is loaded while the step's solves run
+        const int b = (int)(piece - np);
+        const Piece p = step == 0 ? jac_piece<kFull>(nb, 0, b) : jac_piece<kCross>(nb, (int)step - 1, b);
+        wait_applied(done, nA, base + step);
+        jac_apply_load<true>(S, V, Rp, p, lds.apply);
+        wait_solved(&st->solved, (step + 1) * np, np);
+        jac_apply<true, true>(S, V, Rp, Q, p, b, part, lds.apply);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (threadIdx.x == 0)
+            __hip_atomic_store(done + (piece - np), base + step + 1, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// The same steps as launches of their own.
+template <int MODE>
+__global__ __launch_bounds__(kSolveThreads) void k_jac_solve(const double* __restrict__ S,
+                                                             int64_t Rp, double* __restrict__ Q,
+                                                             int nb, int step, const JacState* st) {
+    if (st->converged) return;
+    __shared__ SolveLds lds;
+    jac_solve<MODE, false>(S, Rp, Q, nb, step, blockIdx.x, lds);
+}
+
 template <int MODE>
 __global__ __launch_bounds__(kJThreads) void k_jac_apply(double* __restrict__ S,
                                                          double* __restrict__ V, int64_t Rp,
@@ -267,102 +571,9 @@ __global__ __launch_bounds__(kJThreads) void k_jac_apply(double* __restrict__ S,
                                                          int step, double* __restrict__ part,
                                                          const JacState* st) {
     if (st->converged) return;
-    __shared__ double x[kJT][kJP];
-    __shared__ double qa[kJT][kJP];
-    __shared__ double qb[kJT][kJP];
-    __shared__ double u[kJT][kJP];
-    __shared__ double red[2][kJThreads];
-    const int tid = threadIdx.x;
-    const int np = nb / 2;
-    const int nT = np * (np + 1) / 2;
-    int b = blockIdx.x;
-    if (b < nT) {
-        int pa = 0;
-        while (b >= np - pa) {
-            b -= np - pa;
-            ++pa;
-        }
-        const int pb = pa + b;
-        int Ia, Ja, Ib, Jb;
-        pair_blocks<MODE>(nb, step, pa, Ia, Ja);
-        pair_blocks<MODE>(nb, step, pb, Ib, Jb);
-        for (int v = 0; v < kPerThread; ++v) {
-            const int e = tid + kJThreads * v, i = e / kJT, j = e % kJT;
-            x[i][j] = S[tile_row(Ia, Ja, i) * Rp + tile_row(Ib, Jb, j)];
-            qa[i][j] = Q[(int64_t)pa * kJT * kJT + e];
-            qb[i][j] = Q[(int64_t)pb * kJT * kJT + e];
-        }
-        __syncthreads();
-        const int ti = tid / 16, tj = tid % 16;           // rows ti, ti+16; columns tj, tj+16
-        double acc[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
-        for (int z = 0; z < kJT; ++z) {                  // U = X Q_b
-            const double x0 = x[ti][z], x1 = x[ti + 16][z], q0 = qb[z][tj], q1 = qb[z][tj + 16];
-            acc[0][0] = fma(x0, q0, acc[0][0]);
-            acc[0][1] = fma(x0, q1, acc[0][1]);
-            acc[1][0] = fma(x1, q0, acc[1][0]);
-            acc[1][1] = fma(x1, q1, acc[1][1]);
-        }
-        for (int a2 = 0; a2 < 2; ++a2)
-            for (int b2 = 0; b2 < 2; ++b2) u[ti + 16 * a2][tj + 16 * b2] = acc[a2][b2];
-        __syncthreads();
-        double tacc[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
-        for (int z = 0; z < kJT; ++z) {                  // T = Q_a^T U
-            const double q0 = qa[z][ti], q1 = qa[z][ti + 16], u0 = u[z][tj], u1 = u[z][tj + 16];
-            tacc[0][0] = fma(q0, u0, tacc[0][0]);
-            tacc[0][1] = fma(q0, u1, tacc[0][1]);
-            tacc[1][0] = fma(q1, u0, tacc[1][0]);
-            tacc[1][1] = fma(q1, u1, tacc[1][1]);
-        }
-        __syncthreads();
-        for (int a2 = 0; a2 < 2; ++a2)
-            for (int b2 = 0; b2 < 2; ++b2) x[ti + 16 * a2][tj + 16 * b2] = tacc[a2][b2];
-        __syncthreads();
-        double off = 0.0, tot = 0.0;
-        for (int v = 0; v < kPerThread; ++v) {
-            const int e = tid + kJThreads * v, i = e / kJT, j = e % kJT;
-            const int64_t gi = tile_row(Ia, Ja, i), gj = tile_row(Ib, Jb, j);
-            if (pa == pb) {
-                const double t = i <= j ? x[i][j] : x[j][i];
-                S[gi * Rp + gj] = t;
-                tot += t * t;
-                if (i != j) off += t * t;
-            } else {
-                const double t = x[i][j];
-                S[gi * Rp + gj] = t;
-                S[gj * Rp + gi] = t;
-                tot += 2.0 * t * t;
-                off += 2.0 * t * t;
-            }
-        }
-        block_sum2(off, tot, red);
-        if (tid == 0) {
-            part[2 * blockIdx.x] = off;
-            part[2 * blockIdx.x + 1] = tot;
-        }
-        return;
-    }
-    b -= nT;                                              // V role
-    const int rb = b / np, pc = b % np;
-    int Ic, Jc;
-    pair_blocks<MODE>(nb, step, pc, Ic, Jc);
-    for (int v = 0; v < kPerThread; ++v) {
-        const int e = tid + kJThreads * v, i = e / kJT, j = e % kJT;
-        x[i][j] = V[((int64_t)rb * kJT + i) * Rp + tile_row(Ic, Jc, j)];
-        qa[i][j] = Q[(int64_t)pc * kJT * kJT + e];
-    }
-    __syncthreads();
-    const int ti = tid / 16, tj = tid % 16;
-    double acc[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
-    for (int z = 0; z < kJT; ++z) {
-        const double x0 = x[ti][z], x1 = x[ti + 16][z], q0 = qa[z][tj], q1 = qa[z][tj + 16];
-        acc[0][0] = fma(x0, q0, acc[0][0]);
-        acc[0][1] = fma(x0, q1, acc[0][1]);
-        acc[1][0] = fma(x1, q0, acc[1][0]);
-        acc[1][1] = fma(x1, q1, acc[1][1]);
-    }
-    for (int a2 = 0; a2 < 2; ++a2)
-        for (int b2 = 0; b2 < 2; ++b2)
-            V[((int64_t)rb * kJT + ti + 16 * a2) * Rp + tile_row(Ic, Jc, tj + 16 * b2)] = acc[a2][b2];
+    __shared__ ApplyLds<kJThreads> lds;
+    const Piece p = jac_piece<MODE>(nb, step, blockIdx.x);
+    jac_apply<false, false>(S, V, Rp, Q, p, blockIdx.x, part, lds);
 }
 
 // End of a sweep: sum the tiles' norms in tile order; converged when
@@ -426,6 +637,222 @@ __device__ __forceinline__ void tile_accumulate(const TX* __restrict__ X, int64_
     }
 }
 
+// ---- The inverse, where no eigenvalue is cut ----------------------------------------
+// If every |lambda| exceeds tol max|lambda|, V diag(mu) V^T is the inverse of S, which
+// takes Rp/32 short launches instead of a dozen Jacobi sweeps of 2 Rp/16 each.  A call at
+// r = 24 takes 80 us against 259, r = 64 85 against 814, r = 256 214 against 3618 and
+// r = 500 (whose idle sweeps stay separate launches) 1.8 ms against 8.3; a core that needs
+// the sweeps pays for the attempt, 15 us at r = 24 to 300 us at r = 500 (3 to 6%).  X = S^-1 by a block Gauss-Jordan
+// elimination without pivoting, R = I - S X, and the certificate
+//     ||R||_F <= 2^-24   and   tol ||S||_F ||X||_F < 1 / 1.01
+// (then min|lambda| >= (1 - ||R||) / ||X||_F > tol ||S||_F >= tol max|lambda|), after which
+// X + X R is the inverse to FP64 rounding.  A singular, badly scaled or unluckily
+// indefinite S fails it (NaN included), and the sweeps run as they do when the caller asks
+// for the eigenvalues.
+
+// Element (i, j) of a matrix of r x r, continued by the identity.
+struct Padded {
+    double* p;
+    int64_t ld;
+    int64_t r;
+    __device__ __forceinline__ double get(int64_t i, int64_t j) const {
+        return i < r && j < r ? p[i * ld + j] : i == j ? 1.0 : 0.0;
+    }
+    __device__ __forceinline__ void put(int64_t i, int64_t j, double v) const {
+        if (i < r && j < r) p[i * ld + j] = v;
+    }
+};
+
+// (acc[u]) += sum_k a[ti][k] b[k][4 tj + u] over a 32 x 32 x 32 product.
+__device__ __forceinline__ void mul32(const double (*a)[kJP], const double (*b)[kJP], int ti, int tj,
+                                      double sign, double (&acc)[4]) {
+#pragma unroll 8
+    for (int k = 0; k < kJT; ++k) {
+        const double x = sign * a[ti][k];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc[u] = fma(x, b[k][4 * tj + u], acc[u]);
+    }
+}
+
+__device__ __forceinline__ void load32(double (*t)[kJP], const Padded& m, int bi, int bj, int ti, int tj) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t[ti][4 * tj + u] = m.get((int64_t)bi * kJT + ti, (int64_t)bj * kJT + 4 * tj + u);
+}
+
+// Step k of the elimination, src -> dst: every workgroup forms one 32 x 32 block and
+// inverts the pivot block for itself (32 pivots, one barrier each).
+__global__ __launch_bounds__(kJThreads) void k_inv_step(const Padded src, const Padded dst, int k) {
+    __shared__ double d[kJT][kJP], a[kJT][kJP], b[kJT][kJP];
+    __shared__ double prow[2][kJT], pcol[2][kJT];
+    const int bi = blockIdx.y, bj = blockIdx.x;
+    const int tid = threadIdx.x, ti = tid / 8, tj = tid % 8;
+    double e[4], own[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int u = 0; u < 4; ++u) e[u] = src.get((int64_t)k * kJT + ti, (int64_t)k * kJT + 4 * tj + u);
+    if (bj != k) load32(b, src, k, bj, ti, tj);
+    if (bi != k) load32(a, src, bi, k, ti, tj);
+    if (bi != k && bj != k) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            own[u] = src.get((int64_t)bi * kJT + ti, (int64_t)bj * kJT + 4 * tj + u);
+    }
+#pragma unroll
+    for (int p = 0; p < kJT; ++p) {
+        double* pr = prow[p & 1];
+        double* pc = pcol[p & 1];
+        if (ti == p) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) pr[4 * tj + u] = e[u];
+        }
+        if (tj == p / 4) pc[ti] = e[p % 4];
+        __syncthreads();
+        const double inv = rcp_nr(pr[p]);
+        const double f = pc[ti] * inv;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int j = 4 * tj + u;
+            const double v = ti == p ? (j == p ? inv : pr[j] * inv)
+                                     : (j == p ? -f : fma(-f, pr[j], e[u]));
+            e[u] = v;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) d[ti][4 * tj + u] = e[u];
+    __syncthreads();
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    if (bi == k && bj == k) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = e[u];
+    } else if (bj == k) {
+        mul32(a, d, ti, tj, -1.0, v);
+    } else {
+        mul32(d, b, ti, tj, 1.0, v);
+        if (bi != k) {
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                b[ti][4 * tj + u] = v[u];
+                v[u] = own[u];
+            }
+            __syncthreads();
+            mul32(a, b, ti, tj, -1.0, v);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) dst.put((int64_t)bi * kJT + ti, (int64_t)bj * kJT + 4 * tj + u, v[u]);
+}
+
+// One 32 x 32 block of L M (np blocks of 32 along the contraction): acc of thread (ti, tj);
+// the next blocks are loaded while these are multiplied.
+__device__ __forceinline__ void block_product(const Padded& L, const Padded& M, int bi, int bj, int np,
+                                              int ti, int tj, double (*a)[kJP], double (*b)[kJP],
+                                              double sign, double (&acc)[4]) {
+    double na[4], nb[4];
+    auto fetch = [&](int k) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            na[u] = L.get((int64_t)bi * kJT + ti, (int64_t)k * kJT + 4 * tj + u);
+            nb[u] = M.get((int64_t)k * kJT + ti, (int64_t)bj * kJT + 4 * tj + u);
+        }
+    };
+    fetch(0);
+    for (int k = 0; k < np; ++k) {
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            a[ti][4 * tj + u] = na[u];
+            b[ti][4 * tj + u] = nb[u];
+        }
+        __syncthreads();
+        if (k + 1 < np) fetch(k + 1);
+        mul32(a, b, ti, tj, sign, acc);
+    }
+}
+
+// Fixed-order workgroup sum (256 threads).
+__device__ __forceinline__ double block_sum1(double x, double* red) {
+    red[threadIdx.x] = x;
+    __syncthreads();
+    for (int w = kJThreads / 2; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+        __syncthreads();
+    }
+    const double t = red[0];
+    __syncthreads();
+    return t;
+}
+
+// R = I - S X by blocks; norm[3 t ..] = the block's squares of R, S and X.
+__global__ __launch_bounds__(kJThreads) void k_inv_residual(const Padded S, const Padded X,
+                                                            const Padded R, double* __restrict__ norm) {
+    __shared__ double a[kJT][kJP], b[kJT][kJP];
+    __shared__ double red[kJThreads];
+    const int bi = blockIdx.y, bj = blockIdx.x, np = gridDim.x;
+    const int tid = threadIdx.x, ti = tid / 8, tj = tid % 8;
+    const int64_t i = (int64_t)bi * kJT + ti, j0 = (int64_t)bj * kJT + 4 * tj;
+    double acc[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[u] = i == j0 + u ? 1.0 : 0.0;
+    block_product(S, X, bi, bj, np, ti, tj, a, b, -1.0, acc);
+    double r2 = 0.0, s2 = 0.0, x2 = 0.0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        if (i >= S.r || j0 + u >= S.r) continue;
+        const double sv = S.get(i, j0 + u), xv = X.get(i, j0 + u);
+        r2 = fma(acc[u], acc[u], r2);
+        s2 = fma(sv, sv, s2);
+        x2 = fma(xv, xv, x2);
+        R.put(i, j0 + u, acc[u]);
+    }
+    r2 = block_sum1(r2, red);
+    s2 = block_sum1(s2, red);
+    x2 = block_sum1(x2, red);
+    if (tid == 0) {
+        double* n = norm + 3 * (bi * np + bj);
+        n[0] = r2;
+        n[1] = s2;
+        n[2] = x2;
+    }
+}
+
+// With the certificate: S <- X + X R, state "converged".  Without it: V <- I for the
+// sweeps, and their flags (in the output, which X or R held) cleared.  (X or R may lie in V:
+// every block decides alike.)
+__global__ __launch_bounds__(kJThreads) void k_inv_finish(const Padded X, const Padded R,
+                                                          const double* __restrict__ norm, double tol,
+                                                          double* __restrict__ S, double* __restrict__ V,
+                                                          int64_t Rp, unsigned* done, int nA,
+                                                          JacState* st) {
+    __shared__ double a[kJT][kJP], b[kJT][kJP];
+    __shared__ double red[kJThreads];
+    const int bi = blockIdx.y, bj = blockIdx.x, np = gridDim.x;
+    const int tid = threadIdx.x, ti = tid / 8, tj = tid % 8;
+    double q[3] = {0.0, 0.0, 0.0};
+    for (int t = tid; t < np * np; t += kJThreads)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) q[c] += norm[3 * t + c];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) q[c] = block_sum1(q[c], red);
+    const int64_t i = (int64_t)bi * kJT + ti, j0 = (int64_t)bj * kJT + 4 * tj;
+    if (!(q[0] <= 0x1p-48 && tol * sqrt(q[1]) * sqrt(q[2]) * 1.01 < 1.0)) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) V[i * Rp + j0 + u] = i == j0 + u ? 1.0 : 0.0;
+        if (bi == 0 && bj == 0)
+            for (int t = tid; t < nA; t += kJThreads) done[t] = 0u;
+        return;
+    }
+    double acc[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[u] = X.get(i, j0 + u);
+    block_product(X, R, bi, bj, np, ti, tj, a, b, 1.0, acc);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) S[i * Rp + j0 + u] = acc[u];
+    if (bi == 0 && bj == 0 && tid == 0) {
+        st->converged = 1;
+        st->inverse = 1;
+    }
+}
+
 // C^+ = V diag(mu) V^T on the first r rows / columns, mu_l = 1 / lambda_l for
 // |lambda_l| > tol max|lambda|, else 0 (lambda_l = S(l, l) after convergence).
 // (V_il V_jl) mu_l is the same product for (i, j) and (j, i): C^+ is exactly
@@ -433,8 +860,16 @@ __device__ __forceinline__ void tile_accumulate(const TX* __restrict__ X, int64_
 __global__ __launch_bounds__(256) void k_pinv_form(const double* __restrict__ S,
                                                    const double* __restrict__ V, int64_t Rp,
                                                    int64_t r, double tol, double* __restrict__ Cp,
-                                                   int64_t ldcp, double* __restrict__ eig) {
+                                                   int64_t ldcp, double* __restrict__ eig,
+                                                   const JacState* st) {
     constexpr int TM = 32;
+    if (st->inverse) {           // the symmetric part of the inverse
+        for (int e = threadIdx.x; e < TM * TM; e += 256) {
+            const int64_t i = (int64_t)blockIdx.y * TM + e / TM, j = (int64_t)blockIdx.x * TM + e % TM;
+            if (i < r && j < r) Cp[i * ldcp + j] = 0.5 * (S[i * Rp + j] + S[j * Rp + i]);
+        }
+        return;
+    }
     __shared__ double xs[kGK][TM], ys[kGK][TM];
     __shared__ double mu[1024];
     __shared__ double red[256];
@@ -753,10 +1188,31 @@ hipError_t launch_core_pinv(const void* C, int c_f64, int64_t r, int64_t ldc, do
         k_jac_init<double><<<gi, 256, 0, s>>>(static_cast<const double*>(C), r, ldc, S, V, Rp, st);
     else
         k_jac_init<float><<<gi, 256, 0, s>>>(static_cast<const float*>(C), r, ldc, S, V, Rp, st);
+    // flags of k_jac_sweep: nT + nV <= 2 r words, in the output's first row
+    unsigned* done = reinterpret_cast<unsigned*>(Cp);
+    if (eig == nullptr) {
+        // blocks of V and of the output in turn; Q's area (Rp/32 KiB x 8) holds the norms
+        const Padded ms{S, Rp, r}, mv{V, Rp, r}, mc{Cp, ldcp, r};
+        const dim3 gb((unsigned)np, (unsigned)np);
+        for (int k = 0; k < (int)np; ++k)
+            k_inv_step<<<gb, kJThreads, 0, s>>>(k == 0 ? ms : k % 2 ? mv : mc, k % 2 ? mc : mv, k);
+        const Padded& X = np % 2 ? mv : mc;
+        const Padded& R = np % 2 ? mc : mv;
+        k_inv_residual<<<gb, kJThreads, 0, s>>>(ms, X, R, Q);
+        k_inv_finish<<<gb, kJThreads, 0, s>>>(X, R, Q, tol, S, V, Rp, done, (int)(nT + nV), st);
+    }
     // off-diagonal Frobenius norm at most 8 Rp units of FP64 rounding of ||S||
     const double tolc = 8.0 * (double)Rp * 0x1p-53;
     const unsigned ga = (unsigned)(nT + nV);
+    const unsigned steps = nb > 2 ? (unsigned)nb : 1u;
+    // sweeps that may have nothing to do go out as one launch each, the others step by step
+    const bool sweep_launch = eig == nullptr && r <= kSweepMaxR;
     for (int sw = 0; sw < max_sweeps; ++sw) {
+        if (sweep_launch) {
+            k_jac_sweep<<<steps * (unsigned)(np + nT + nV) + 1, kSolveThreads, 0, s>>>(
+                S, V, Rp, Q, (int)nb, part, tolc, done, st);
+            continue;
+        }
         k_jac_solve<kFull><<<(unsigned)np, kSolveThreads, 0, s>>>(S, Rp, Q, (int)nb, 0, st);
         k_jac_apply<kFull><<<ga, kJThreads, 0, s>>>(S, V, Rp, Q, (int)nb, 0, part, st);
         for (int step = 0; nb > 2 && step < nb - 1; ++step) {
@@ -766,7 +1222,7 @@ hipError_t launch_core_pinv(const void* C, int c_f64, int64_t r, int64_t ldc, do
         k_jac_flag<<<1, kJThreads, 0, s>>>(part, (int)nT, tolc, st);
     }
     const unsigned gt = (unsigned)((r + 31) / 32);
-    k_pinv_form<<<dim3(gt, gt), 256, 0, s>>>(S, V, Rp, r, tol, Cp, ldcp, eig);
+    k_pinv_form<<<dim3(gt, gt), 256, 0, s>>>(S, V, Rp, r, tol, Cp, ldcp, eig, st);
     if (info) k_jac_info<<<1, 64, 0, s>>>(st, info);
     return hipGetLastError();
 }

@@ -197,3 +197,54 @@ def test_reconstruction_tiles_at_their_edges(n, r, symmetric):
     slack = 8 * n * U64 * se + 16 * (r + 64) * U64 * (np.abs(D) * size).sum()
     assert abs(got[0] - se) <= slack and abs(got[1] - sa) <= 8 * n * U64 * sa
     assert abs(got[2] - math.sqrt(se / sa)) <= (slack / se + 16 * n * U64) * math.sqrt(se / sa)
+
+
+@pytest.mark.parametrize("r", [1, 5, 31, 32, 33, 64, 65, 100, 256, 500])
+@pytest.mark.parametrize("kind", ["positive", "indefinite", "singular", "below_cut"])
+def test_core_pinv_inverse_or_sweeps(r, kind):
+    """Without the eigenvalues asked for, a core none of whose eigenvalues is cut is inverted
+    directly (0 sweeps); any other takes the Jacobi sweeps.  Both within the bound of the
+    known-spectrum test, exactly symmetric, and the first equal to the spectral formula that a
+    call with eigenvalues uses to within twice that bound."""
+    lam = np.logspace(0, -4, r) * (1.0 + 0.1 * np.arange(r) / r)
+    if kind == "indefinite":
+        lam[::3] *= -1.0
+    if kind == "singular":
+        lam[-1] = 0.0
+    if kind == "below_cut":
+        lam[-1] = 0.4 * TOL * np.abs(lam).max() if r > 1 else lam[-1]
+    C, want = known_spectrum(r, 300 + r, lam)
+    Cd = torch.from_numpy(C).to(DEV)
+    out = torch.full((r, r + 3), 7.0, dtype=torch.float64, device=DEV)
+    Cp, info = sk.sketch_core_pinv(Cd, TOL, max_sweeps=30, Cp=out[:, :r])
+    sweeps, conv = info.cpu().tolist()
+    assert conv == 1
+    if kind == "positive":
+        assert sweeps == 0
+    if kind in ("singular", "below_cut") and r > 1:
+        assert sweeps >= 1
+    got = Cp.cpu().numpy()
+    assert (out[:, r:] == 7.0).all()
+    Rp = (r + 31) // 32 * 32
+    kept = np.abs(lam) > TOL * np.abs(lam).max()
+    kappa = np.abs(lam).max() / np.abs(lam[kept]).min() if kept.any() else 1.0
+    bound = 64 * Rp * U64 * kappa * np.linalg.norm(want)
+    assert np.linalg.norm(got - want) <= bound
+    assert np.array_equal(got, got.T)
+    Ce, _, _ = sk.sketch_core_pinv(Cd, TOL, max_sweeps=30, eigvals=True)
+    assert np.linalg.norm(got - Ce.cpu().numpy()) <= 2 * bound
+
+
+def test_core_pinv_inverse_special_cores():
+    """A diagonal core inverts to diag(1 / lambda) bitwise; tol = 1 cuts every eigenvalue but
+    none is kept by the inverse path; a core with a zero pivot and a NaN take the sweeps."""
+    lam = np.linspace(3.0, -2.9, 40)
+    Cp, info = sk.sketch_core_pinv(torch.from_numpy(np.diag(lam)).to(DEV), TOL)
+    assert info.cpu().tolist() == [0, 1]
+    assert np.array_equal(Cp.cpu().numpy(), np.diag(1.0 / lam))
+    C1, _ = sk.sketch_core_pinv(torch.from_numpy(np.diag(lam)).to(DEV), 1.0)
+    assert not C1.cpu().numpy().any()
+    P = np.array([[0.0, 1.0], [1.0, 0.0]])
+    Cp, info = sk.sketch_core_pinv(torch.from_numpy(P).to(DEV), TOL)
+    assert info.cpu().tolist()[0] >= 1
+    assert np.abs(Cp.cpu().numpy() - P).max() <= 64 * 32 * U64
