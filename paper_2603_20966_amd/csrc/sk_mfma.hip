@@ -49,7 +49,14 @@ static_assert(kBM == kMfmaRows, "tile rows");
 // registers): they are split before a chunk's 128 MFMAs, which cover the next
 // chunk's load.
 constexpr int chunk_cols(int) { return kSplitKC; }
-constexpr bool single_a(int nt) { return nt >= 8; }
+constexpr bool single_a(int nt, int tm = kTM) { return nt >= 8 && tm >= kTM; }
+// Chunks of Omega generated per barrier by a tile of W waves x 16 TM rows (one or two
+// N-tiles): one in the 512-row tile, where the other waves' MFMAs cover a chunk's few
+// Philox quads; as many as give every thread a quad in the smaller tiles, which run a
+// workgroup or less per compute unit and wait for each chunk.
+constexpr int tile_group(int nt, int w, int tm) {
+    return tm >= kTM || nt > 2 || 64 * w < 256 * nt ? 1 : 64 * w / (128 * nt);
+}
 
 struct MArgs {
     int64_t m;
@@ -170,11 +177,11 @@ struct PackArgs {
 // Write a wave's accumulators: lane (g, j) holds rows 4g..4g+3 and column j of
 // each 16 x 16 tile.  The per-128-row scale (FP8 storage) is applied to each
 // strip partial; a single-strip call writes Y directly (old Y added in FP64).
-template <int NT>
-__device__ __forceinline__ void store_tile(const MTile& t, const v4f (&acc)[kTM][NT],
+template <int NT, int TM = kTM>
+__device__ __forceinline__ void store_tile(const MTile& t, const v4f (&acc)[TM][NT],
                                            int64_t row_base, int kb, int g, int i16) {
 #pragma unroll
-    for (int tm = 0; tm < kTM; ++tm) {
+    for (int tm = 0; tm < TM; ++tm) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
             const int cn = nt * 16 + i16;
@@ -468,7 +475,7 @@ __device__ __forceinline__ void omega_exponents(const MTile& t, int* ecol, int w
     __syncthreads();
 }
 
-// A operand loads of a wave: chunk c of rows row_base .. row_base + 63, lane (g, i) the 8
+// A operand loads of a wave: chunk c of rows row_base .. row_base + 16 TM - 1, lane (g, i) the 8
 // floats at columns 8 g .. of row (tm, i).
 // FULL: every block of the launch has at least one whole chunk of columns.  Then every
 // lane issues the same loads every chunk, unconditionally (a load past the strip's
@@ -477,14 +484,14 @@ __device__ __forceinline__ void omega_exponents(const MTile& t, int* ecol, int w
 // the loop it waits for every load in flight, including the next chunk's, which
 // undoes the double buffering.  A ragged last chunk is loaded behind a wave-uniform
 // branch that waits for its own loads.  Narrower blocks take the per-lane path.
-template <bool FULL>
+template <int TM, bool FULL>
 struct ALoads {
-    const unsigned char* arow[kTM];
+    const unsigned char* arow[TM];
     int g, w;
     __device__ __forceinline__ ALoads(const MTile& t, int64_t row_base, int g_, int i16, int w_)
         : g(g_), w(w_) {
 #pragma unroll
-        for (int tm = 0; tm < kTM; ++tm) {
+        for (int tm = 0; tm < TM; ++tm) {
             const int64_t r = min<int64_t>(row_base + tm * 16 + i16, t.m - 1);
             arow[tm] = t.A + r * (t.lda * 4) + (t.col_begin + 8 * g) * 4;
         }
@@ -495,7 +502,7 @@ struct ALoads {
         if constexpr (FULL) {
             const int cc = c < nfull ? c : nfull - 1;
 #pragma unroll
-            for (int tm = 0; tm < kTM; ++tm) {
+            for (int tm = 0; tm < TM; ++tm) {
                 const unsigned char* p = arow[tm] + (int64_t)cc * KC * 4;
 #pragma unroll
                 for (int v = 0; v < 2; ++v) a[tm][v] = *reinterpret_cast<const v4f*>(p + 16 * v);
@@ -505,7 +512,7 @@ struct ALoads {
         const int kl = c * KC + 8 * g;                      // strip column of component 0
         if (c * KC >= w) return;
 #pragma unroll
-        for (int tm = 0; tm < kTM; ++tm) {
+        for (int tm = 0; tm < TM; ++tm) {
             const unsigned char* p = arow[tm] + (int64_t)c * KC * 4;
             if (kl + 7 < w) {
 #pragma unroll
@@ -523,7 +530,7 @@ struct ALoads {
         }
         if constexpr (FULL) {
 #pragma unroll
-            for (int tm = 0; tm < kTM; ++tm) asm volatile("" : "+v"(a[tm][0]), "+v"(a[tm][1]));
+            for (int tm = 0; tm < TM; ++tm) asm volatile("" : "+v"(a[tm][0]), "+v"(a[tm][1]));
         }
     }
 };
@@ -534,20 +541,24 @@ struct ALoads {
 // mfma_tile; A is the A operand, 8 MFMAs per chunk and row tile: component s of 16-byte load
 // v is contraction index g of MFMA 4v + s.  FULL as for mfma_tile.
 constexpr int kF32Row = kSplitKC + 4;   // floats per LDS column of a chunk
+template <int G>
 struct F32Lds {
-    float om[2][16][kF32Row];
+    float om[2 * G][16][kF32Row];
 };
 
 template <int TH, bool GEN>
 __device__ __forceinline__ void omega_chunk_f32(const MTile& t, float (*om)[kF32Row], int c, int w,
-                                                int kb) {
+                                                int kb, int first) {
+    // thread `first` takes the first item
+    const int start = (int)threadIdx.x >= first ? (int)threadIdx.x - first
+                                                : (int)threadIdx.x - first + TH;
     constexpr int KC = kSplitKC;
     const int kvalid = min(KC, w - c * KC);
     if constexpr (GEN) {
         const int64_t g0 = t.row0 + t.col_begin + (int64_t)c * KC;   // global Omega row of local 0
         const int64_t q_lo = g0 >> 2;
         const int nq = (int)(((g0 + KC - 1) >> 2) - q_lo + 1);        // KC/4, or one more if unaligned
-        for (int it = threadIdx.x; it < nq * kb; it += TH) {
+        for (int it = start; it < nq * kb; it += TH) {
             const int qi = it / kb;
             const int n = it - qi * kb;
             const float4 z = omega4_dist((uint64_t)(q_lo + qi), t.col0 + (uint32_t)(t.n_base + n),
@@ -565,7 +576,7 @@ __device__ __forceinline__ void omega_chunk_f32(const MTile& t, float (*om)[kF32
             }
         }
     } else {
-        for (int it = threadIdx.x; it < KC * kb; it += TH) {
+        for (int it = start; it < KC * kb; it += TH) {
             const int kl = it / kb;
             const int n = it - kl * kb;
             om[n][kl] = (kl < kvalid)
@@ -575,9 +586,10 @@ __device__ __forceinline__ void omega_chunk_f32(const MTile& t, float (*om)[kF32
     }
 }
 
-template <int W, bool GEN, bool FULL>
-__device__ __forceinline__ void mfma_tile_f32(const MTile& t, F32Lds& L) {
+template <int W, int TM, bool GEN, bool FULL>
+__device__ __forceinline__ void mfma_tile_f32(const MTile& t, F32Lds<tile_group(1, W, TM)>& L) {
     constexpr int TH = 64 * W;
+    constexpr int G = tile_group(1, W, TM);
     constexpr int KC = kSplitKC;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -586,59 +598,65 @@ __device__ __forceinline__ void mfma_tile_f32(const MTile& t, F32Lds& L) {
 
     const int w = (int)min<int64_t>(kMfmaStrip, t.n - t.col_begin);
     const int nchunks = (w + KC - 1) / KC;
-    const int nfull = w / KC;
-    const int64_t row_base = t.block_row + wave * (kTM * 16);
+    const int64_t row_base = t.block_row + wave * (TM * 16);
     const int kb = (int)min<int64_t>(16, t.k - t.n_base);
-    const ALoads<FULL> A(t, row_base, g, i16, w);
+    const ALoads<TM, FULL> A(t, row_base, g, i16, w);
 
-    // columns past k of both halves are zeroed once: generation never writes them
-    for (int it = threadIdx.x; it < 2 * 16 * kF32Row; it += TH)
+    // columns past k of every slot are zeroed once: generation never writes them
+    for (int it = threadIdx.x; it < 2 * G * 16 * kF32Row; it += TH)
         if ((it / kF32Row) % 16 >= kb) (&L.om[0][0][0])[it] = 0.0f;
-    auto make_chunk = [&](int c) { omega_chunk_f32<TH, GEN>(t, L.om[c & 1], c, w, kb); };
-
-    v4f acc[kTM][1];
+    // chunks c .. c + G - 1, one call each: their quads go to different threads
+    auto make_group = [&](int c) {
 #pragma unroll
-    for (int tm = 0; tm < kTM; ++tm) acc[tm][0] = v4f{0.f, 0.f, 0.f, 0.f};
-    v4f a0[kTM][2], a1[kTM][2];
+        for (int u = 0; u < G; ++u)
+            if (c + u < nchunks)
+                omega_chunk_f32<TH, GEN>(t, L.om[(c + u) & (2 * G - 1)], c + u, w, kb, u * (TH / G));
+    };
+
+    v4f acc[TM][1];
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm) acc[tm][0] = v4f{0.f, 0.f, 0.f, 0.f};
+    v4f a0[TM][2], a1[TM][2];
     A.load(a0, 0);
     A.load(a1, 1);
-    make_chunk(0);
+    make_group(0);
     lds_barrier_m();
     auto step = [&](v4f (*a)[2], int c) {
-        if (c + 1 < nchunks) make_chunk(c + 1);
+        if (c % G == 0) make_group(c + G);
 #pragma unroll
         for (int v = 0; v < 2; ++v) {
-            const v4f bop = *reinterpret_cast<const v4f*>(&L.om[c & 1][i16][8 * g + 4 * v]);
+            const v4f bop = *reinterpret_cast<const v4f*>(&L.om[c & (2 * G - 1)][i16][8 * g + 4 * v]);
 #pragma unroll
             for (int s = 0; s < 4; ++s)
 #pragma unroll
-                for (int tm = 0; tm < kTM; ++tm)
+                for (int tm = 0; tm < TM; ++tm)
                     acc[tm][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[tm][v][s], bop[s], acc[tm][0],
                                                                       0, 0, 0);
         }
         A.load(a, c + 2);
         if constexpr (FULL) __builtin_amdgcn_sched_barrier(0);
-        lds_barrier_m();
+        if (c % G == G - 1) lds_barrier_m();
     };
     for (int c = 0; c < nchunks; c += 2) {
         step(a0, c);
         if (c + 1 < nchunks) step(a1, c + 1);
     }
-    store_tile<1>(t, acc, row_base, kb, g, i16);
+    store_tile<1, TM>(t, acc, row_base, kb, g, i16);
 }
 
 // Split operands (two or more N-tiles).
 // PK: Omega chunks copied from the call's packed Omega (k_f32_pack) and split on the
 // way to LDS; the copy of chunk c + 2 is issued ahead of the A loads issued after it,
 // so waiting for it leaves those in flight.
-template <int NT>
+template <int NT, int G>
 struct SplitLds {
-    _Float16 om[2][16 * NT][kSplitRow];
+    _Float16 om[2 * G][16 * NT][kSplitRow];
     int ecol[16 * NT];
 };
 
-template <int NT, int W, bool GEN, bool FULL = false, bool PK = false>
-__device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT>& L) {
+template <int NT, int W, int TM, bool GEN, bool FULL = false, bool PK = false>
+__device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT, tile_group(NT, W, TM)>& L) {
+    constexpr int G = PK ? 1 : tile_group(NT, W, TM);   // chunks generated per barrier
     constexpr int BN = 16 * NT;
     constexpr int TH = 64 * W;
     constexpr int KC = kSplitKC;
@@ -651,18 +669,18 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT>& L) {
 
     const int w = (int)min<int64_t>(kMfmaStrip, t.n - t.col_begin);
     const int nchunks = (w + KC - 1) / KC;
-    const int64_t row_base = t.block_row + wave * (kTM * 16);
+    const int64_t row_base = t.block_row + wave * (TM * 16);
     const int n_base = t.n_base;
     const int kb = (int)min<int64_t>(BN, t.k - n_base);
     const bool stored = (PK || !GEN) && t.omega != nullptr;   // uniform across the launch
 
-    const ALoads<FULL> A(t, row_base, g, i16, w);
+    const ALoads<TM, FULL> A(t, row_base, g, i16, w);
 
     // ---- Omega chunk -> LDS ----------------------------------------------------------
-    if constexpr (!PK) omega_zero_pad<BN, TH>(om, 2, kb);
+    if constexpr (!PK) omega_zero_pad<BN, TH>(om, 2 * G, kb);
     if (stored) omega_exponents<BN, TH, PK>(t, L.ecol, w, kb);
-    auto make_chunk = [&](int c) {
-        omega_group<BN, TH, 1, GEN>(t, om, c & 1, c, nchunks, w, kb, L.ecol);
+    auto make_group = [&](int c) {
+        omega_group<BN, TH, G, GEN>(t, om, c & (2 * G - 1), c, nchunks, w, kb, L.ecol);
     };
     // packed route: 16-byte pieces of the tile's run of a chunk, OPT per thread;
     // chunk indices past the last are clamped (a re-read of valid memory whose
@@ -687,26 +705,26 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT>& L) {
         }
     };
 
-    v4f acc[kTM][NT];
+    v4f acc[TM][NT];
 #pragma unroll
-    for (int tm = 0; tm < kTM; ++tm)
+    for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) acc[tm][nt] = v4f{0.f, 0.f, 0.f, 0.f};
-    float s[kTM];                 // scale of row (tm, i16)
-    bool inf[kTM];                // the row holds an infinity
+    float s[TM];                 // scale of row (tm, i16)
+    bool inf[TM];                // the row holds an infinity
 #pragma unroll
-    for (int tm = 0; tm < kTM; ++tm) {
+    for (int tm = 0; tm < TM; ++tm) {
         s[tm] = kRowStart;
         inf[tm] = false;
     }
 
     // chunk's raw values -> MFMA operands, rescaling rows that outgrow FP16
-    h8 a0[kTM], a1[kTM], a0s[kTM];
+    h8 a0[TM], a1[TM], a0s[TM];
     auto split = [&](v4f (*a)[2]) {
-        float x[kTM][8], y[kTM][8];
+        float x[TM][8], y[TM][8];
         float mx = 0.0f;
 #pragma unroll
-        for (int tm = 0; tm < kTM; ++tm) {
+        for (int tm = 0; tm < TM; ++tm) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 x[tm][e] = a[tm][e >> 2][e & 3];
@@ -716,7 +734,7 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT>& L) {
         }
         if (__builtin_expect(__any(mx > kRowLimit), 0)) {
 #pragma unroll
-            for (int tm = 0; tm < kTM; ++tm) {
+            for (int tm = 0; tm < TM; ++tm) {
                 const float f = rescale_row(x[tm], s[tm], inf[tm]);
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) acc[tm][nt] *= f;
@@ -725,11 +743,11 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT>& L) {
             }
         }
 #pragma unroll
-        for (int tm = 0; tm < kTM; ++tm) split_a(y[tm], a0[tm], a1[tm], a0s[tm]);
+        for (int tm = 0; tm < TM; ++tm) split_a(y[tm], a0[tm], a1[tm], a0s[tm]);
     };
 
     auto compute = [&](int c) {
-        const int buf = c & 1;
+        const int buf = c & (2 * G - 1);
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
             const _Float16* ob = &om[buf][nt * 16 + i16][8 * g];
@@ -737,21 +755,21 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT>& L) {
             const h8 b1 = *reinterpret_cast<const h8*>(ob + KC);
             const h8 b2 = *reinterpret_cast<const h8*>(ob + 2 * KC);
 #pragma unroll
-            for (int tm = 0; tm < kTM; ++tm)
+            for (int tm = 0; tm < TM; ++tm)
                 acc[tm][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(b0, a1[tm], acc[tm][nt], 0, 0, 0);
 #pragma unroll
-            for (int tm = 0; tm < kTM; ++tm)
+            for (int tm = 0; tm < TM; ++tm)
                 acc[tm][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(b2, a0s[tm], acc[tm][nt], 0, 0, 0);
 #pragma unroll
-            for (int tm = 0; tm < kTM; ++tm)
+            for (int tm = 0; tm < TM; ++tm)
                 acc[tm][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(b1, a0s[tm], acc[tm][nt], 0, 0, 0);
 #pragma unroll
-            for (int tm = 0; tm < kTM; ++tm)
+            for (int tm = 0; tm < TM; ++tm)
                 acc[tm][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(b0, a0[tm], acc[tm][nt], 0, 0, 0);
         }
     };
 
-    v4f r0[kTM][2], r1[kTM][2];
+    v4f r0[TM][2], r1[TM][2];
     v4f orr[PK ? OPT : 1];
     if constexpr (PK) {
         om_load(orr, 0);
@@ -759,11 +777,11 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT>& L) {
         om_store(orr, 0);
         om_load(orr, 1);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (!single_a(NT)) A.load(r1, 1);
+        if constexpr (!single_a(NT, TM)) A.load(r1, 1);
     } else {
         A.load(r0, 0);
-        if constexpr (!single_a(NT)) A.load(r1, 1);
-        make_chunk(0);
+        if constexpr (!single_a(NT, TM)) A.load(r1, 1);
+        make_group(0);
     }
     lds_barrier_m();
 
@@ -775,15 +793,15 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT>& L) {
             om_load(orr, c + 2);
             __builtin_amdgcn_sched_barrier(0);
         } else {
-            if (c + 1 < nchunks) make_chunk(c + 1);
+            if (c % G == 0 && c + G < nchunks) make_group(c + G);
         }
         split(r);
-        A.load(r, c + (single_a(NT) ? 1 : 2));
+        A.load(r, c + (single_a(NT, TM) ? 1 : 2));
         if constexpr (FULL) __builtin_amdgcn_sched_barrier(0);
         compute(c);
-        lds_barrier_m();
+        if (c % G == G - 1) lds_barrier_m();
     };
-    if constexpr (single_a(NT)) {
+    if constexpr (single_a(NT, TM)) {
         for (int c = 0; c < nchunks; ++c) step(r0, c);
     } else {
         for (int c = 0; c < nchunks; c += 2) {
@@ -803,7 +821,7 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT>& L) {
     o.y_f64 = t.y_f64;
     o.beta = t.beta;
 #pragma unroll
-    for (int tm = 0; tm < kTM; ++tm) {
+    for (int tm = 0; tm < TM; ++tm) {
         const int64_t row = row_base + tm * 16 + i16;
         if (row >= t.m) continue;
 #pragma unroll
@@ -812,9 +830,12 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT>& L) {
                   stored ? &L.ecol[nt * 16 + 4 * g] : nullptr);
     }
     // ---- non-finite entries, again with FP32 products ------------------------------
-    if (__any(inf[0] || inf[1] || inf[2] || inf[3])) {
+    bool any_inf = false;
 #pragma unroll
-        for (int tm = 0; tm < kTM; ++tm) {
+    for (int tm = 0; tm < TM; ++tm) any_inf = any_inf || inf[tm];
+    if (__any(any_inf)) {
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) {
             for (uint64_t rows = __ballot(inf[tm]) & 0xFFFFu; rows != 0; rows &= rows - 1) {
                 const int64_t row = row_base + tm * 16 + __builtin_ctzll(rows);
                 if (row >= t.m) break;
@@ -827,22 +848,23 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT>& L) {
         bool bad = false;
         for (int n = lane; n < kb; n += 64) bad = bad || L.ecol[n] == kBadCol;
         if (__any(bad)) {
-            for (int64_t row = row_base; row < min<int64_t>(row_base + kTM * 16, t.m); ++row)
+            for (int64_t row = row_base; row < min<int64_t>(row_base + TM * 16, t.m); ++row)
                 fix_row<GEN, PK>(t, o, reinterpret_cast<const float*>(t.A) + row * t.lda + t.col_begin,
                                  1, row, w, kb, [&](int c) { return L.ecol[c] == kBadCol; });
         }
     }
 }
 
-template <int NT>
-using TileLds = std::conditional_t<NT == 1, F32Lds, SplitLds<NT>>;
+template <int NT, int W, int TM>
+using TileLds = std::conditional_t<NT == 1, F32Lds<tile_group(1, W, TM)>,
+                                   SplitLds<NT, tile_group(NT, W, TM)>>;
 
 // One call: one workgroup per (strip of any block, 64W-row tile, sketch-column
 // block).
-template <int NT, int W, bool GEN, bool FULL>
+template <int NT, int W, int TM, bool GEN, bool FULL>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 4 : 2)))
 void k_gemm_mfma(const MArgs args) {
-    __shared__ __attribute__((aligned(16))) TileLds<NT> lds;
+    __shared__ __attribute__((aligned(16))) TileLds<NT, W, TM> lds;
     TileId id;
     if (!mfma_tile_id<(NT > 1)>(args, id)) return;
     const int strip = id.strip;
@@ -863,7 +885,7 @@ void k_gemm_mfma(const MArgs args) {
     t.m = args.m;
     t.k = args.k;
     t.col_begin = sib * kMfmaStrip;
-    t.block_row = id.rtile * (64 * W);
+    t.block_row = id.rtile * (16 * TM * W);
     t.n_base = id.nb * 16 * NT;
     t.key0 = args.key0;
     t.key1 = args.key1;
@@ -882,8 +904,8 @@ void k_gemm_mfma(const MArgs args) {
     t.opack_lo = nullptr;
     t.kpad = args.kpad;
     t.fpack = args.fpack;
-    if constexpr (NT == 1) mfma_tile_f32<W, GEN, FULL>(t, lds);
-    else mfma_tile<NT, W, GEN, FULL, mfma_packed(NT)>(t, lds);
+    if constexpr (NT == 1) mfma_tile_f32<W, TM, GEN, FULL>(t, lds);
+    else mfma_tile<NT, W, TM, GEN, FULL, mfma_packed(NT)>(t, lds);
 }
 
 // A batch of independent requests (serving): the tiles of each request are the
@@ -891,7 +913,7 @@ void k_gemm_mfma(const MArgs args) {
 // XCD-grouped order, so each result does not depend on the batch.
 template <int NT, bool FULL>
 __global__ __launch_bounds__(kThreads) void k_gemm_mfma_batch(const BatchArgs args) {
-    __shared__ __attribute__((aligned(16))) TileLds<NT> lds;
+    __shared__ __attribute__((aligned(16))) TileLds<NT, kWaves, kTM> lds;
     const int64_t T8 = (args.total_tiles + 7) / 8;
     bool first = true;
     for (int64_t v = blockIdx.x; v < 8 * T8; v += gridDim.x) {   // gridDim.x is a multiple of 8
@@ -934,8 +956,8 @@ __global__ __launch_bounds__(kThreads) void k_gemm_mfma_batch(const BatchArgs ar
         t.fpack = nullptr;
         if (!first) lds_barrier_m();   // every wave is done with the previous tile's LDS
         first = false;
-        if constexpr (NT == 1) mfma_tile_f32<kWaves, true, FULL>(t, lds);
-        else mfma_tile<NT, kWaves, true, FULL>(t, lds);
+        if constexpr (NT == 1) mfma_tile_f32<kWaves, kTM, true, FULL>(t, lds);
+        else mfma_tile<NT, kWaves, kTM, true, FULL>(t, lds);
     }
 }
 
@@ -2021,33 +2043,39 @@ hipError_t dispatch_lp(int nt, bool gen, int waves, const MArgs& a, hipStream_t 
     }
 }
 
-template <int NT, int W, bool GEN>
-hipError_t launch_m(const MArgs& args, hipStream_t s) {
+template <int NT, int W, int TM, bool GEN, bool FULL>
+hipError_t launch_m_tile(const MArgs& args, hipStream_t s) {
     // packed tiles do not look at GEN (the packing kernel did): one instantiation
     constexpr bool G = mfma_packed(NT) || GEN;
     MArgs a = args;
-    a.nrt = (a.m + 64 * W - 1) / (64 * W);
-    const dim3 grid = mfma_grid(a);
-    // one N-tile: whole chunks only (with a ragged end the unconditional loads measured
-    // 166 us against 158 for the per-lane path, 20011 x 9973 at k = 16)
-    bool full = true;
-    for (int b = 0; b < a.P; ++b)
-        full = full && (NT == 1 ? a.blk[b].n % kSplitKC == 0
-                                : a.blk[b].n >= kSplitKC || a.blk[b].n == 0);
-    if (full)
-        hipLaunchKernelGGL((k_gemm_mfma<NT, W, G, true>), grid, dim3(64 * W), 0, s, a);
-    else
-        hipLaunchKernelGGL((k_gemm_mfma<NT, W, G, false>), grid, dim3(64 * W), 0, s, a);
+    a.nrt = (a.m + 16 * TM * W - 1) / (16 * TM * W);
+    hipLaunchKernelGGL((k_gemm_mfma<NT, W, TM, G, FULL>), mfma_grid(a), dim3(64 * W), 0, s, a);
     return hipGetLastError();
 }
 
+template <int NT, bool GEN>
+hipError_t launch_m(int rows, const MArgs& a, hipStream_t s) {
+    bool full = true, whole = true;
+    for (int b = 0; b < a.P; ++b) {
+        full = full && (a.blk[b].n >= kSplitKC || a.blk[b].n == 0);
+        whole = whole && a.blk[b].n % kSplitKC == 0;
+    }
+    if (full && rows == 64) return launch_m_tile<NT, 4, 1, GEN, true>(a, s);
+    if (full && rows == 128) return launch_m_tile<NT, 8, 1, GEN, true>(a, s);
+    if (full && rows == 256) return launch_m_tile<NT, 8, 2, GEN, true>(a, s);
+    // one N-tile: whole chunks only (with a ragged end the unconditional loads measured
+    // 166 us against 158 for the per-lane path, 20011 x 9973 at k = 16)
+    return (NT == 1 ? whole : full) ? launch_m_tile<NT, 8, 4, GEN, true>(a, s)
+                                    : launch_m_tile<NT, 8, 4, GEN, false>(a, s);
+}
+
 template <bool GEN>
-hipError_t dispatch_m(int nt, int waves, const MArgs& a, hipStream_t s) {
+hipError_t dispatch_m(int nt, int rows, const MArgs& a, hipStream_t s) {
     switch (nt) {
-    case 1: return waves == 4 ? launch_m<1, 4, GEN>(a, s) : launch_m<1, 8, GEN>(a, s);
-    case 2: return waves == 4 ? launch_m<2, 4, GEN>(a, s) : launch_m<2, 8, GEN>(a, s);
-    case 4: return waves == 4 ? launch_m<4, 4, GEN>(a, s) : launch_m<4, 8, GEN>(a, s);
-    default: return launch_m<8, 8, GEN>(a, s);
+    case 1: return launch_m<1, GEN>(rows, a, s);
+    case 2: return launch_m<2, GEN>(rows, a, s);
+    case 4: return launch_m<4, GEN>(rows, a, s);
+    default: return launch_m<8, GEN>(rows, a, s);
     }
 }
 
@@ -2075,12 +2103,16 @@ size_t f32_plane_elems(int64_t strips, int64_t k) {
 
 }  // namespace
 
-// Waves per workgroup of the FP32 kernel: 8 (512 rows share each Omega chunk), or 4 while
-// those tiles would fill half the compute units at most: the 256-row tiles then still run
-// in one round, with half the rows behind each chunk's latency (5000 x 5000 at k = 64:
-// 124 us against 187; with 200 512-row tiles, 20011 x 9973, it is 210 against 203).
-static int mfma_waves(int64_t m, int64_t strips, int64_t nblk) {
-    return 2 * strips * ((m + kBM - 1) / kBM) * nblk <= device_cus() ? 4 : 8;
+// Rows per tile of the FP32 kernel: 512 (8 waves of 64 rows, which share each Omega chunk),
+// halved down to 64 while those tiles would fill half the compute units at most.  A strip's
+// 64 chunks follow one another, so a call with few tiles takes as long as one tile, and a
+// smaller tile does less per chunk.  With 512- or 256-row tiles of 64 rows a wave (before)
+// and with this rule: 5000 x 5000 at k = 64 124 and 59 us, 2000 x 3000 at k = 16 86 and 43,
+// at k = 24 about 95 and 80, 10000 x 2000 at k = 130 558 (FP32 instruction) and 86.
+static int mfma_rows(int64_t m, int64_t strips, int64_t nblk) {
+    int rows = kBM;
+    while (rows > 64 && 2 * strips * ((m + rows - 1) / rows) * nblk <= device_cus()) rows /= 2;
+    return rows;
 }
 
 hipError_t launch_gemm_mfma(const GemmLaunch& g) {
@@ -2123,7 +2155,7 @@ hipError_t launch_gemm_mfma(const GemmLaunch& g) {
     a.beta = g.beta;
     for (int b = 0; b < g.P; ++b) a.blk[b] = g.blk[b];
     a.nblk = (int)nblk;
-    const int waves = mfma_waves(g.m, S, nblk);
+    const int rows = mfma_rows(g.m, S, nblk);
     const TraceEvents& tr = g.trace;
     if (tr.begin) (void)hipEventRecord(tr.begin, g.stream);
     if (mfma_packed(nt)) {
@@ -2136,8 +2168,8 @@ hipError_t launch_gemm_mfma(const GemmLaunch& g) {
         const hipError_t pe = hipGetLastError();
         if (pe != hipSuccess) return pe;
     }
-    hipError_t e = (g.omega == nullptr) ? dispatch_m<true>(nt, waves, a, g.stream)
-                                        : dispatch_m<false>(nt, waves, a, g.stream);
+    hipError_t e = (g.omega == nullptr) ? dispatch_m<true>(nt, rows, a, g.stream)
+                                        : dispatch_m<false>(nt, rows, a, g.stream);
     if (e != hipSuccess) return e;
     if (tr.mid) (void)hipEventRecord(tr.mid, g.stream);
     if (S > 1) e = launch_reduce_partials(a.partials, (int)S, g.m, g.k, g.Y, g.y_f64, g.ldy,

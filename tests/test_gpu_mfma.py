@@ -103,3 +103,23 @@ def test_mfma_beta_and_f64():
     assert oracle.rel_fro((Y - Y0).cpu().numpy(), ref) <= 1e-5
     Y64 = sk.sketch_gen_matmul(Ad, 2, 48, y_dtype=torch.float64)
     assert torch.equal(sk.sketch_gen_matmul(Ad, 2, 48), Y64.float())
+
+
+@pytest.mark.parametrize("n", [2100, 2112])
+@pytest.mark.parametrize("k", [16, 24, 64, 130])
+def test_tile_heights_give_the_same_bits(n, k):
+    """Row tiles are 512 rows high, or 256, 128 or 64 when the call has few of them; a row's
+    sums do not depend on the tile.  Heights on 256 compute units, two strips, one column
+    block (two at k = 130): 33000 rows 512; 20000 rows 256 (512); 10000 rows 128 (256);
+    3000 rows 64."""
+    m = 33000
+    A = torch.empty((m, (n + 3) // 4 * 4), device=DEV)
+    A.normal_(generator=torch.Generator(device=DEV).manual_seed(n + k))
+    A = A[:, :n]
+    Y = sk.sketch_gen_matmul(A, 3, k, omega_row0=1)
+    Om = sk.sketch_gen_omega(3, 1, n, 0, k, device=DEV)
+    for rows in (20000, 10000, 3000, 70, 5):
+        assert torch.equal(sk.sketch_gen_matmul(A[:rows], 3, k, omega_row0=1), Y[:rows]), rows
+        assert torch.equal(sk.sketch_matmul_omega(A[:rows], Om), Y[:rows]), rows
+    Ah = A[:64].cpu().numpy()
+    check(Y[:64], np.ascontiguousarray(Ah), 3, 1, 0, k)
