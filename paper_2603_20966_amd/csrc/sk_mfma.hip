@@ -5,9 +5,9 @@
 // (sk_split.hpp: four v_mfma_f32_16x16x32_f16 per 32 contraction columns, FP32
 // sums), whose error against FP64 is below that of an FP32 chain.
 //
-// Tile of one workgroup (64 W threads = W waves): 64 W rows of A x a strip of
+// Tile of one workgroup (64 W threads = W waves): 16 TM W rows of A x a strip of
 // kMfmaStrip contraction columns x BN = 16*NT sketch columns.  Each wave owns
-// 64 rows (4 row tiles of 16) x NT N-tiles, i.e. 4*NT accumulator tiles of
+// TM row tiles of 16 rows x NT N-tiles, i.e. TM*NT accumulator tiles of
 // Y^T (Omega is the A operand, A the B operand, so a lane's accumulators belong
 // to one row of each row tile and the row's scale is the lane's own).
 //
@@ -859,7 +859,7 @@ template <int NT, int W, int TM>
 using TileLds = std::conditional_t<NT == 1, F32Lds<tile_group(1, W, TM)>,
                                    SplitLds<NT, tile_group(NT, W, TM)>>;
 
-// One call: one workgroup per (strip of any block, 64W-row tile, sketch-column
+// One call: one workgroup per (strip of any block, 16 TM W-row tile, sketch-column
 // block).
 template <int NT, int W, int TM, bool GEN, bool FULL>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 4 : 2)))
@@ -1643,7 +1643,7 @@ __global__ __launch_bounds__(256) void k_lp_pack(const PackArgs a) {
 // PK: Omega chunks copied from the call's packed Omega (k_lp_pack) instead of
 // generated or split here; the copy of chunk c + 2 is issued ahead of the A
 // loads of chunk c + 2, so waiting for it leaves those in flight.
-template <int NT, int ADT, int W, bool GEN, bool FULL = false, bool PK = false>
+template <int NT, int ADT, int W, int TM, bool GEN, bool FULL = false, bool PK = false>
 __device__ __forceinline__ void lp_tile(const MTile& t, uint16_t (*oh)[16 * NT][lp_row(ADT)],
                                         uint16_t (*ol)[16 * NT][lp_row(ADT)]) {
     constexpr int BN = 16 * NT;
@@ -1662,14 +1662,14 @@ __device__ __forceinline__ void lp_tile(const MTile& t, uint16_t (*oh)[16 * NT][
 
     const int w = (int)min<int64_t>(kLpStrip, t.n - t.col_begin);
     const int nchunks = (w + KC - 1) / KC;
-    const int64_t row_base = t.block_row + wave * (kTM * 16);
+    const int64_t row_base = t.block_row + wave * (TM * 16);
     const int kb = (int)min<int64_t>(BN, t.k - t.n_base);
 
     // ---- A: lane (g, i) holds columns kc + KG g .. kc + KG g + KG - 1 of row i ------
     const int64_t ldab = t.lda * es;
-    const unsigned char* arow[kTM];
+    const unsigned char* arow[TM];
 #pragma unroll
-    for (int tm = 0; tm < kTM; ++tm) {
+    for (int tm = 0; tm < TM; ++tm) {
         const int64_t r = min<int64_t>(row_base + tm * 16 + i16, t.m - 1);
         arow[tm] = t.A + r * ldab + (t.col_begin + KG * g) * es;
     }
@@ -1680,7 +1680,7 @@ __device__ __forceinline__ void lp_tile(const MTile& t, uint16_t (*oh)[16 * NT][
         if constexpr (FULL) {
             const int cc = c < nchunks ? c : nchunks - 1;
 #pragma unroll
-            for (int tm = 0; tm < kTM; ++tm) {
+            for (int tm = 0; tm < TM; ++tm) {
                 const unsigned char* p = arow[tm] + (int64_t)cc * KC * es;
 #pragma unroll
                 for (int v = 0; v < RW; ++v) a[tm][v] = *reinterpret_cast<const v4u*>(p + 16 * v);
@@ -1690,7 +1690,7 @@ __device__ __forceinline__ void lp_tile(const MTile& t, uint16_t (*oh)[16 * NT][
         if (c >= nchunks) return;
         const int kl = c * KC + KG * g;
 #pragma unroll
-        for (int tm = 0; tm < kTM; ++tm) {
+        for (int tm = 0; tm < TM; ++tm) {
             const unsigned char* p = arow[tm] + (int64_t)c * KC * es;
             if (kl + KG - 1 < w) {
 #pragma unroll
@@ -1805,13 +1805,13 @@ __device__ __forceinline__ void lp_tile(const MTile& t, uint16_t (*oh)[16 * NT][
         }
     };
 
-    v4f acc[kTM][NT];
+    v4f acc[TM][NT];
 #pragma unroll
-    for (int tm = 0; tm < kTM; ++tm)
+    for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) acc[tm][nt] = v4f{0.f, 0.f, 0.f, 0.f};
 
-    v4u a0[kTM][RW], a1[kTM][RW];
+    v4u a0[TM][RW], a1[TM][RW];
     v4u orr[PK ? OPT : 1];
     if constexpr (PK) {
         load_a(a0, 0);
@@ -1831,15 +1831,15 @@ __device__ __forceinline__ void lp_tile(const MTile& t, uint16_t (*oh)[16 * NT][
         const int buf = c & 1;
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-            v4u op[kTM];
+            v4u op[TM];
 #pragma unroll
-            for (int tm = 0; tm < kTM; ++tm) op[tm] = operand(a[tm], v);
+            for (int tm = 0; tm < TM; ++tm) op[tm] = operand(a[tm], v);
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
                 const v4u bh = *reinterpret_cast<const v4u*>(&oh[buf][nt * 16 + i16][KG * g + 8 * v]);
                 const v4u bl = *reinterpret_cast<const v4u*>(&ol[buf][nt * 16 + i16][KG * g + 8 * v]);
 #pragma unroll
-                for (int tm = 0; tm < kTM; ++tm) {
+                for (int tm = 0; tm < TM; ++tm) {
                     const v8bf av = __builtin_bit_cast(v8bf, op[tm]);
                     acc[tm][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                         av, __builtin_bit_cast(v8bf, bh), acc[tm][nt], 0, 0, 0);
@@ -1897,23 +1897,23 @@ __device__ __forceinline__ void lp_tile(const MTile& t, uint16_t (*oh)[16 * NT][
             }
         }
     }
-    store_tile<NT>(t, acc, row_base, kb, g, i16);
+    store_tile<NT, TM>(t, acc, row_base, kb, g, i16);
 }
 
-// One call: one workgroup per (strip of any block, 64W-row tile, sketch-column
+// One call: one workgroup per (strip of any block, 16 TM W-row tile, sketch-column
 // block), in the XCD-grouped order of mfma_tile_id.
 // One-N-tile, 4-wave workgroups are kept within 128 registers so that four of
 // them share a compute unit (a 32768-row FP8 launch is exactly four per unit;
 // with three, a quarter of the tiles run as a tail on an underfilled chip).
-constexpr int lp_min_waves(int nt, int w) { return nt == 1 && w == 4 ? 4 : 1; }
+constexpr int lp_min_waves(int nt, int w, int tm) { return nt == 1 && w == 4 && tm == kTM ? 4 : 1; }
 
 // Omega from the call's packed copy with more than one N-tile; one N-tile
 // generates (or splits) its chunks in the tile, as the 128 registers of its
 // 4-wave workgroups hold no staging registers besides.
 constexpr bool lp_packed(int nt) { return nt > 1; }
 
-template <int NT, int ADT, int W, bool GEN, bool FULL>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(lp_min_waves(NT, W))))
+template <int NT, int ADT, int W, int TM, bool GEN, bool FULL>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(lp_min_waves(NT, W, TM))))
 void k_gemm_mfma_lp(const MArgs args) {
     __shared__ __attribute__((aligned(16))) uint16_t oh[2][16 * NT][lp_row(ADT)];
     __shared__ __attribute__((aligned(16))) uint16_t ol[2][16 * NT][lp_row(ADT)];
@@ -1937,7 +1937,7 @@ void k_gemm_mfma_lp(const MArgs args) {
     t.m = args.m;
     t.k = args.k;
     t.col_begin = sib * kLpStrip;
-    t.block_row = id.rtile * (64 * W);
+    t.block_row = id.rtile * (16 * TM * W);
     t.n_base = id.nb * 16 * NT;
     t.key0 = args.key0;
     t.key1 = args.key1;
@@ -1956,7 +1956,7 @@ void k_gemm_mfma_lp(const MArgs args) {
     t.opack_lo = args.opack_lo;
     t.kpad = args.kpad;
     t.fpack = nullptr;
-    lp_tile<NT, ADT, W, GEN, FULL, lp_packed(NT)>(t, oh, ol);
+    lp_tile<NT, ADT, W, TM, GEN, FULL, lp_packed(NT)>(t, oh, ol);
 }
 
 // Batch of requests of one class (serving); rows per tile = kLpBatchRows.
@@ -2006,40 +2006,45 @@ __global__ __launch_bounds__(64 * kLpBatchWaves) void k_gemm_mfma_lp_batch(const
         t.fpack = nullptr;
         if (!first) lds_barrier_m();
         first = false;
-        lp_tile<NT, ADT, kLpBatchWaves, true>(t, oh, ol);
+        lp_tile<NT, ADT, kLpBatchWaves, kTM, true>(t, oh, ol);
     }
 }
 
-template <int NT, int ADT, int W, bool GEN>
+template <int NT, int ADT, int W, int TM, bool GEN>
 hipError_t launch_lp(const MArgs& args, hipStream_t s) {
     MArgs a = args;
-    a.nrt = (a.m + 64 * W - 1) / (64 * W);
+    a.nrt = (a.m + 16 * TM * W - 1) / (16 * TM * W);
     const dim3 grid = mfma_grid(a);
     // whole chunks: unconditional loads (one N-tile measured 5-8% slower with them: its
     // 4-wave, 128-register tiles already keep enough loads in flight)
     bool full = NT > 1;
     for (int b = 0; b < a.P; ++b) full = full && a.blk[b].n % lp_kc(ADT) == 0;
     if (full)
-        hipLaunchKernelGGL((k_gemm_mfma_lp<NT, ADT, W, GEN, true>), grid, dim3(64 * W), 0, s, a);
+        hipLaunchKernelGGL((k_gemm_mfma_lp<NT, ADT, W, TM, GEN, true>), grid, dim3(64 * W), 0, s, a);
     else
-        hipLaunchKernelGGL((k_gemm_mfma_lp<NT, ADT, W, GEN, false>), grid, dim3(64 * W), 0, s, a);
+        hipLaunchKernelGGL((k_gemm_mfma_lp<NT, ADT, W, TM, GEN, false>), grid, dim3(64 * W), 0, s, a);
     return hipGetLastError();
 }
 
 template <int NT, int ADT, bool GEN>
-hipError_t dispatch_lp_w(int waves, const MArgs& a, hipStream_t s) {
-    return waves == 4 ? launch_lp<NT, ADT, 4, GEN>(a, s) : launch_lp<NT, ADT, 8, GEN>(a, s);
+hipError_t dispatch_lp_w(int rows, const MArgs& a, hipStream_t s) {
+    switch (rows) {
+    case 64: return launch_lp<NT, ADT, 4, 1, GEN>(a, s);
+    case 128: return launch_lp<NT, ADT, 8, 1, GEN>(a, s);
+    case 256: return launch_lp<NT, ADT, 4, 4, GEN>(a, s);
+    default: return launch_lp<NT, ADT, 8, 4, GEN>(a, s);
+    }
 }
 
 // packed tiles do not look at GEN (the packing kernel did): one instantiation
 template <int ADT>
-hipError_t dispatch_lp(int nt, bool gen, int waves, const MArgs& a, hipStream_t s) {
+hipError_t dispatch_lp(int nt, bool gen, int rows, const MArgs& a, hipStream_t s) {
     static_assert(!lp_packed(1) && lp_packed(2) && lp_packed(4), "routes below");
     switch (nt) {
-    case 1: return gen ? dispatch_lp_w<1, ADT, true>(waves, a, s)
-                       : dispatch_lp_w<1, ADT, false>(waves, a, s);
-    case 2: return dispatch_lp_w<2, ADT, true>(waves, a, s);
-    default: return dispatch_lp_w<4, ADT, true>(waves, a, s);
+    case 1: return gen ? dispatch_lp_w<1, ADT, true>(rows, a, s)
+                       : dispatch_lp_w<1, ADT, false>(rows, a, s);
+    case 2: return dispatch_lp_w<2, ADT, true>(rows, a, s);
+    default: return dispatch_lp_w<4, ADT, true>(rows, a, s);
     }
 }
 
@@ -2298,15 +2303,18 @@ hipError_t launch_gemm_cm_mfma(const CmLaunch& g) {
 
 int lp_ntiles(int64_t k) { return k <= 16 ? 1 : k <= 32 ? 2 : 4; }
 
-// Waves per workgroup of the low-precision kernel: 8 (512 rows share each
-// Omega chunk), unless that leaves compute units without a tile.  Measured on
+// Rows per tile of the low-precision kernel: 512 (8 waves of 64 rows share each
+// Omega chunk), unless that leaves compute units without a tile, then 256.  Measured on
 // 32768^2 with the XCD-grouped tile order: FP8 k = 5 199-201 us against 207-210
-// with 4-wave workgroups, k = 64 299 against 375.  (Before that order, 4-wave
-// workgroups had won at k = 5: 3.2 vs 2.6 TB/s.)
-int lp_waves(int64_t m, int64_t strips, int64_t nblk, int nt) {
-    (void)nt;
-    const int64_t tiles8 = strips * ((m + 511) / 512) * nblk;
-    return tiles8 >= device_cus() ? 8 : 4;
+// with 256-row tiles, k = 64 299 against 375.  128 and 64 rows (waves of 16) while the
+// tiles would fill half the compute units at most, as for the FP32 kernel.
+// With 256-row tiles and with these: 5000 x 5000 BF16 k = 64 97 and 52 us, FP8 k = 5 65
+// and 47; 2000 x 3000 FP8 k = 64 74 and 36, BF16 k = 16 75 and 54.
+static int lp_rows(int64_t m, int64_t strips, int64_t nblk) {
+    const auto tiles = [&](int rows) { return strips * ((m + rows - 1) / rows) * nblk; };
+    if (tiles(512) >= device_cus()) return 512;
+    if (2 * tiles(256) > device_cus()) return 256;
+    return 2 * tiles(128) > device_cus() ? 128 : 64;
 }
 
 namespace {
@@ -2396,7 +2404,7 @@ hipError_t launch_gemm_mfma_lp(const GemmLaunch& g) {
     a.y_f64 = g.y_f64;
     a.beta = g.beta;
     for (int b = 0; b < g.P; ++b) a.blk[b] = g.blk[b];
-    const int waves = lp_waves(g.m, S, nblk, nt);
+    const int rows = lp_rows(g.m, S, nblk);
     a.nblk = (int)nblk;
     const TraceEvents& tr = g.trace;
     if (tr.begin) (void)hipEventRecord(tr.begin, g.stream);
@@ -2406,8 +2414,8 @@ hipError_t launch_gemm_mfma_lp(const GemmLaunch& g) {
         if (e != hipSuccess) return e;
     }
     const bool gen = (g.omega == nullptr);
-    e = g.adtype == 1 ? dispatch_lp<1>(nt, gen, waves, a, g.stream)
-                      : dispatch_lp<2>(nt, gen, waves, a, g.stream);
+    e = g.adtype == 1 ? dispatch_lp<1>(nt, gen, rows, a, g.stream)
+                      : dispatch_lp<2>(nt, gen, rows, a, g.stream);
     if (e != hipSuccess) return e;
     if (tr.mid) (void)hipEventRecord(tr.mid, g.stream);
     if (S > 1) e = launch_reduce_partials(a.partials, (int)S, g.m, g.k, g.Y, g.y_f64, g.ldy,

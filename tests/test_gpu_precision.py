@@ -191,3 +191,20 @@ def test_matrix_core_layouts_and_stored_omega_bitwise(kind, k):
     assert torch.equal(torch.cat(parts), Yrow)
     Om = sk.sketch_gen_omega(6, 0, n, 0, k, device=DEV)
     assert torch.equal(sk.sketch_matmul_omega(Aq, Om, a_scales=sc), Yrow)
+
+
+@pytest.mark.parametrize("kind,k,n", [("fp8", 5, 2112), ("fp8", 40, 2048), ("bf16", 12, 2104),
+                                      ("bf16", 100, 2112)])
+def test_low_precision_tile_heights_give_the_same_bits(kind, k, n):
+    """Row tiles of 512, 256, 128 or 64 rows by the number of tiles (one strip of columns):
+    rows of a tall call equal shorter calls bit for bit."""
+    m = 140000
+    A = torch.empty((m, n), device=DEV)
+    A.normal_(generator=torch.Generator(device=DEV).manual_seed(k))
+    parts = [sk.sketch_quantize(a, kind) for a in A.split(511 * 128)]   # at most 65535 rows each
+    Aq = torch.cat([q for q, _ in parts])
+    sc = None if kind == "bf16" else torch.cat([s for _, s in parts])
+    Y = sk.sketch_gen_matmul(Aq, 3, k, a_scales=sc, omega_row0=1)
+    for rows in (60000, 20000, 9000, 1000, 130, 3):
+        s = None if sc is None else sc[:(rows + 127) // 128]
+        assert torch.equal(sk.sketch_gen_matmul(Aq[:rows], 3, k, a_scales=s, omega_row0=1), Y[:rows]), rows
