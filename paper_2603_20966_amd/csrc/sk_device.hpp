@@ -19,6 +19,11 @@ struct Words4 {
     uint32_t x, y, z, w;
 };
 
+// a ^ b ^ c in one instruction
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96);
+}
+
 // Philox4x32-10: ten rounds of two 32x32->64 multiplies and xors; the key is
 // advanced by the Weyl constants before rounds 2..10.
 __device__ __forceinline__ Words4 philox4x32_10(Words4 c, uint32_t k0, uint32_t k1) {
@@ -31,9 +36,9 @@ __device__ __forceinline__ Words4 philox4x32_10(Words4 c, uint32_t k0, uint32_t 
         const uint64_t p0 = (uint64_t)0xD2511F53u * (uint64_t)c.x;
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c.z;
         Words4 d;
-        d.x = (uint32_t)(p1 >> 32) ^ c.y ^ k0;
+        d.x = xor3((uint32_t)(p1 >> 32), c.y, k0);
         d.y = (uint32_t)p1;
-        d.z = (uint32_t)(p0 >> 32) ^ c.w ^ k1;
+        d.z = xor3((uint32_t)(p0 >> 32), c.w, k1);
         d.w = (uint32_t)p0;
         c = d;
     }
@@ -44,18 +49,28 @@ __device__ __forceinline__ Words4 philox4x32_10(Words4 c, uint32_t k0, uint32_t 
 // variate is u = (2x+1) 2^-24, in (0, 1) and never 0 or 1.
 __device__ __forceinline__ uint32_t odd24(uint32_t r) { return ((r >> 9) << 1) | 1u; }
 
+// s / d rounded correctly for the operands of log_u24 (d in [1.7, 2.42], |s| in
+// [2^-24, 0.42] or 0: no scaling, no special values): one Newton step on the hardware
+// reciprocal, then one correction of the quotient by its exact remainder.  Equal to the
+// rounded quotient for each of the 2^23 words that odd24 can give.
+__device__ __forceinline__ float div_log(float s, float d) {
+    float y = __builtin_amdgcn_rcpf(d);
+    y = __builtin_fmaf(__builtin_fmaf(-d, y, 1.0f), y, y);
+    const float q = s * y;
+    return __builtin_fmaf(__builtin_fmaf(-d, q, s), y, q);
+}
+
 // ln(mo 2^-24), mo odd in [1, 2^24): u = 2^e f with f in [sqrt(1/2), sqrt 2)
-// found in integers; ln f = 2 atanh(w), w = (f-1)/(f+1), by the atanh series
+// found in the bits of the FP32 value of u, which is exact (0x3f3504f4 is the first
+// FP32 number above sqrt(1/2)); ln f = 2 atanh(w), w = (f-1)/(f+1), by the atanh series
 // through w^10 (coefficients 1/(2i+1) rounded to FP32).
 __device__ __forceinline__ float log_u24(uint32_t mo) {
-    int b = 31 - __clz(mo);
-    const uint64_t sq = (uint64_t)mo * (uint64_t)mo;
-    if (sq >= (1ull << (2 * b + 1))) b += 1;
-    const int e = b - 24;
-    const float f = __builtin_ldexpf((float)mo, -b);
+    const uint32_t ub = __float_as_uint((float)mo) - (24u << 23);   // bits of mo 2^-24
+    const int e = (int)(ub - 0x3f3504f4u) >> 23;
+    const float f = __uint_as_float(ub - ((uint32_t)e << 23));
     const float s = f - 1.0f;
     const float d = f + 1.0f;
-    const float w = __fdiv_rn(s, d);
+    const float w = div_log(s, d);
     const float w2 = w * w;
     float p = 0x1.745d18p-4f;                  // 1/11
     p = __builtin_fmaf(p, w2, 0x1.c71c72p-4f);  // 1/9
@@ -74,7 +89,7 @@ __device__ __forceinline__ float log_u24(uint32_t mo) {
 __device__ __forceinline__ void cos_sin_2pi_u24(uint32_t mo, float& c_out, float& s_out) {
     const uint32_t nq = (mo + (1u << 21)) >> 22;
     const int32_t fi = (int32_t)mo - (int32_t)(nq << 22);
-    const float f = __builtin_ldexpf((float)fi, -22);
+    const float f = (float)fi * 0x1p-22f;
     const float f2 = f * f;
     float ps = 0x1.507834p-13f;
     ps = __builtin_fmaf(ps, f2, -0x1.32d2ccp-8f);
@@ -88,11 +103,11 @@ __device__ __forceinline__ void cos_sin_2pi_u24(uint32_t mo, float& c_out, float
     pc = __builtin_fmaf(pc, f2, 0x1.03c1f0p-2f);
     pc = __builtin_fmaf(pc, f2, -0x1.3bd3ccp+0f);
     const float cs = __builtin_fmaf(pc, f2, 1.0f);
-    const uint32_t quad = nq & 3u;
-    const float a = (quad & 1u) ? sn : cs;   // |cos| of the rotated angle
-    const float bb = (quad & 1u) ? cs : sn;  // |sin| of the rotated angle
-    c_out = (quad == 1u || quad == 2u) ? -a : a;
-    s_out = (quad >= 2u) ? -bb : bb;
+    // nq odd: cosine and sine change places; the signs are bit 1 of nq + 1 and of nq
+    const uint32_t a = __float_as_uint((nq & 1u) ? sn : cs);
+    const uint32_t bb = __float_as_uint((nq & 1u) ? cs : sn);
+    c_out = __uint_as_float(a ^ (((nq + 1u) << 30) & 0x80000000u));
+    s_out = __uint_as_float(bb ^ ((nq << 30) & 0x80000000u));
 }
 
 // Correctly rounded square root of a positive normal x.  The hardware
@@ -128,6 +143,9 @@ __device__ __forceinline__ void box_muller(uint32_t r_even, uint32_t r_odd, floa
 }
 
 // Omega rows 4q .. 4q+3 of global column c, from one Philox call.
+// Bound by instruction issue (some 200 a quad); 52.4 M quads took 280 us with the
+// library's division, the logarithm's range found by a 64-bit square and two-operand
+// xors, and take 200 us with the forms above, bit for bit the same for every word.
 __device__ __forceinline__ float4 omega4(uint64_t q, uint32_t c, uint32_t k0, uint32_t k1) {
     Words4 ctr{(uint32_t)q, (uint32_t)(q >> 32), c, 0u};
     const Words4 r = philox4x32_10(ctr, k0, k1);
