@@ -454,10 +454,45 @@ template <int BN, int TH, bool PK>
 __device__ __forceinline__ void omega_exponents(const MTile& t, int* ecol, int w, int kb) {
     for (int n = threadIdx.x; n < BN; n += TH) ecol[n] = 0;
     __syncthreads();
-    for (int64_t it = threadIdx.x; it < (int64_t)w * kb; it += TH) {
-        const int j = (int)(it / kb);
-        const int n = (int)(it - (int64_t)j * kb);
-        atomicMax(&ecol[n], __float_as_int(omega_at<false, PK>(t, j, n)) & 0x7FFFFFFF);
+    if constexpr (PK) {
+        // a chunk's BN columns are one run of the packed plane (zeros past w and k): thread
+        // tid's V pieces of four values lie in the same columns in every chunk
+        constexpr int kPieces = kSplitKC / 4;
+        constexpr int V = BN * kPieces / TH;
+        static_assert(V * TH == BN * kPieces, "whole pieces per thread");
+        constexpr int CPS = kMfmaStrip / kSplitKC;
+        int amax[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v) amax[v] = 0;
+        const int nch = (w + kSplitKC - 1) / kSplitKC;
+#pragma unroll 8
+        for (int c = 0; c < nch; ++c) {
+            const float* p = t.fpack + ((t.strip * CPS + c) * t.kpad + t.n_base) * kSplitKC;
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                const v4f x = *reinterpret_cast<const v4f*>(p + 4 * (threadIdx.x + v * TH));
+#pragma unroll
+                for (int u = 0; u < 4; ++u) amax[v] = max(amax[v], __float_as_int(x[u]) & 0x7FFFFFFF);
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < V; ++v) atomicMax(&ecol[(threadIdx.x + v * TH) / kPieces], amax[v]);
+    } else {
+        // eight loads in flight per thread; a position past the end repeats the last one
+        const int total = w * kb;
+        for (int it0 = threadIdx.x; it0 < total; it0 += 8 * TH) {
+            float x[8];
+            int n[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int it = min(it0 + u * TH, total - 1);
+                const int j = it / kb;
+                n[u] = it - j * kb;
+                x[u] = omega_at<false, PK>(t, j, n[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) atomicMax(&ecol[n[u]], __float_as_int(x[u]) & 0x7FFFFFFF);
+        }
     }
     __syncthreads();
     for (int n = threadIdx.x; n < BN; n += TH) {
