@@ -270,9 +270,11 @@ def run_ksweep(args):
                           args.steps)
         bytes_a = m * n * 4
         flops = 2 * m * n * k
-        kern = "matrix cores (v_mfma_f32_16x16x4f32)" if k > 8 else "VALU FMA"
-        bound = "hbm" if k <= 16 else "mfma_fp32"
-        peak = HBM_PEAK_GBPS if bound == "hbm" else 157.3
+        kern = ("matrix cores (v_mfma_f32_16x16x32_f16, split operands)" if k > 16 else
+                "matrix cores (v_mfma_f32_16x16x4f32)" if k > 8 else "VALU FMA")
+        # k > 16: four FP16 products each, of the dense FP16 peak 2500 TFLOP/s
+        bound = "hbm" if k <= 64 else "mfma_f16"
+        peak = HBM_PEAK_GBPS if bound == "hbm" else 2500.0 / 4
         achieved = bytes_a / (t_gen * 1e-3) / 1e9 if bound == "hbm" else flops / (t_gen * 1e-3) / 1e12
         rows.append({"k": k, "kernel": kern, "gen_ms": round(t_gen, 4), "gen_min_ms": round(t_gen_min, 4),
                      "gen_GBps": round(bytes_a / (t_gen * 1e-3) / 1e9, 1),
