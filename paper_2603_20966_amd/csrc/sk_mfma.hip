@@ -395,20 +395,28 @@ __device__ __forceinline__ void emit(const TileOut& o, int64_t row, int64_t col,
     }
 }
 
+// Exponent of a stored Omega's column that holds an infinity or NaN (see omega_exponents).
+constexpr int kBadCol = 0x7FFF;
+
 // Sketch columns col .. col + 3 of a row, those below `end` (the lane's accumulator of
-// one 16 x 16 tile of Y^T).
+// one 16 x 16 tile of Y^T).  Columns that fix_row evaluates are left to it: with one strip
+// and beta = 1 a second store would add to the first.
 __device__ __forceinline__ void emit4(const TileOut& o, int64_t row, int64_t col, int64_t end,
                                       const v4f v, float s, const int* ecol) {
     v4f u;
 #pragma unroll
     for (int r = 0; r < 4; ++r) u[r] = unscale(v[r], s, ecol ? ecol[r] : 0);
-    if (o.partials && !o.scales && (o.k & 3) == 0 && col + 3 < end) {
+    bool bad[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) bad[r] = ecol && ecol[r] == kBadCol;
+    if (o.partials && !o.scales && (o.k & 3) == 0 && col + 3 < end &&
+        !(bad[0] || bad[1] || bad[2] || bad[3])) {
         *reinterpret_cast<v4f*>(o.partials + row * o.k + col) = u;   // k, col multiples of 4
         return;
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-        if (col + r < end) emit(o, row, col + r, u[r]);
+        if (col + r < end && !bad[r]) emit(o, row, col + r, u[r]);
 }
 
 // Omega(j, c) of the tile's strip (j its column, c below 16 NT), wherever the tile
@@ -431,8 +439,8 @@ __device__ __forceinline__ float omega_at(const MTile& t, int j, int c) {
 }
 
 // Strip sums whose row of A holds an infinity, or whose column of a stored Omega holds
-// an infinity or NaN, once more with FP32 products (the FP16 terms of an infinity
-// would meet zeros and the other sign): row `row` (its first strip element at `a`, the
+// infinity or NaN, with FP32 products (the FP16 terms of an infinity would meet zeros
+// and the other sign): row `row` (its first strip element at `a`, the
 // next `stride` further), sketch columns lane, lane + 64, ... below kb that `want` picks.
 template <bool GEN, bool PK, typename Want>
 __device__ __forceinline__ void fix_row(const MTile& t, const TileOut& o, const float* a,
@@ -449,7 +457,6 @@ __device__ __forceinline__ void fix_row(const MTile& t, const TileOut& o, const 
 // into FP16's range (0 for |omega| <= 6 down to 2^-25, which every generated strip has,
 // so that a stored copy of it multiplies with the same bits); kBadCol marks an
 // infinity or NaN.
-constexpr int kBadCol = 0x7FFF;
 template <int BN, int TH, bool PK>
 __device__ __forceinline__ void omega_exponents(const MTile& t, int* ecol, int w, int kb) {
     for (int n = threadIdx.x; n < BN; n += TH) ecol[n] = 0;
@@ -858,19 +865,21 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT, tile_grou
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
         const int64_t row = row_base + tm * 16 + i16;
-        if (row >= t.m) continue;
+        if (row >= t.m || inf[tm]) continue;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
             emit4(o, row, n_base + nt * 16 + 4 * g, n_base + kb, acc[tm][nt], s[tm],
                   stored ? &L.ecol[nt * 16 + 4 * g] : nullptr);
     }
-    // ---- non-finite entries, again with FP32 products ------------------------------
+    // ---- non-finite entries, with FP32 products ---------------------------------------
     bool any_inf = false;
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) any_inf = any_inf || inf[tm];
+    uint64_t done = 0;            // rows (of the wave's 16 TM) evaluated whole
     if (__any(any_inf)) {
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
+            done |= (__ballot(inf[tm]) & 0xFFFFu) << (16 * tm);
             for (uint64_t rows = __ballot(inf[tm]) & 0xFFFFu; rows != 0; rows &= rows - 1) {
                 const int64_t row = row_base + tm * 16 + __builtin_ctzll(rows);
                 if (row >= t.m) break;
@@ -884,8 +893,10 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT, tile_grou
         for (int n = lane; n < kb; n += 64) bad = bad || L.ecol[n] == kBadCol;
         if (__any(bad)) {
             for (int64_t row = row_base; row < min<int64_t>(row_base + TM * 16, t.m); ++row)
-                fix_row<GEN, PK>(t, o, reinterpret_cast<const float*>(t.A) + row * t.lda + t.col_begin,
-                                 1, row, w, kb, [&](int c) { return L.ecol[c] == kBadCol; });
+                if (!((done >> (row - row_base)) & 1))
+                    fix_row<GEN, PK>(t, o,
+                                     reinterpret_cast<const float*>(t.A) + row * t.lda + t.col_begin,
+                                     1, row, w, kb, [&](int c) { return L.ecol[c] == kBadCol; });
         }
     }
 }
@@ -1336,7 +1347,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_cm_mfma(const CmMArgs a) {
     const TileOut o = cm_out(a, strip);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        if (rl + q >= a.m) continue;
+        if (rl + q >= a.m || inf[q]) continue;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
             emit4(o, rl + q, t.n_base + nt * 16 + 4 * g, t.n_base + kb, acc[q][nt], sc[q], nullptr);
@@ -1526,7 +1537,7 @@ __global__ __launch_bounds__(kSkThreads) void k_gemm_cm_mfma_skinny(const CmMArg
     // Y[rl + q][n_base + 4g + r] = acc[r]
     const TileOut o = cm_out(a, strip);
     const int64_t row = rl + q;
-    if (row < a.m) emit4(o, row, n_base + 4 * g, n_base + kb, acc, sc, nullptr);
+    if (row < a.m && !inf) emit4(o, row, n_base + 4 * g, n_base + kb, acc, sc, nullptr);
     cm_fix_rows(a, o, strip, n_base, inf, q, w, kb);
 }
 

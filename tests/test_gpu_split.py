@@ -164,3 +164,60 @@ def test_stored_columns_of_any_size(k):
     assert np.array_equal(Y2[:, 6], np.copysign(np.inf, A[:, 10]))
     assert np.array_equal(Y2[:, 7], -np.copysign(np.inf, A[:, 4000]))
     assert np.isnan(Y2[:, 8]).all()
+
+
+@pytest.mark.parametrize("y_dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("n,k", [(300, 24), (2048, 40), (2047, 130)])
+def test_non_finite_entries_add_to_y_once(n, k, y_dtype):
+    """One strip and beta = 1: the old Y plus the IEEE product, on every route."""
+    m = 80
+    A = normal_matrix(m, n, seed=n)
+    bad = {0: [(5, np.inf)], 17: [(n - 1, -np.inf)], 33: [(7, np.nan)], 40: [(2, np.inf), (9, -np.inf)]}
+    B = A.copy()
+    for r, es in bad.items():
+        for j, v in es:
+            B[r, j] = v
+    Om = oracle.omega_block(7, 0, n, 0, k)
+    Y0 = torch.from_numpy(normal_matrix(m, k, seed=11)).to(DEV, y_dtype)
+    with np.errstate(invalid="ignore"):
+        want = {r: sum((np.float64(v) * Om[j].astype(np.float64) for j, v in es), np.zeros(k))
+                for r, es in bad.items()}
+    fine = [r for r in range(m) if r not in bad]
+
+    def run(f, rows=m):
+        Y = Y0[:rows].clone()
+        f(Y)
+        return Y
+
+    def serve(Y):
+        torch.cuda.synchronize()
+        Bd = to_dev(B)
+        with sk.SketchServer(1 << 28, max_slots=2, max_batch=2) as srv:
+            t = srv.submit(sv.make_request(A=Bd, k=k, seed=7, Y=Y, beta=1), Bd, Y)
+            assert srv.wait(t, 60.0)["state"] == sv.SK_REQ_DONE
+
+    clean = run(lambda Y: sk.sketch_gen_matmul(to_dev(A), 7, k, Y=Y, beta=1))
+    Omd = torch.from_numpy(Om).to(DEV)
+    outs = [run(lambda Y: sk.sketch_gen_matmul(to_dev(B), 7, k, Y=Y, beta=1)), run(serve),
+            run(lambda Y: sk.sketch_gen_matmul_cm(cm_dev(B), 7, k, Y=Y, beta=1)),
+            run(lambda Y: sk.sketch_gen_matmul_cm(cm_dev(B)[:44], 7, k, Y=Y, beta=1), 44),
+            run(lambda Y: sk.sketch_matmul_omega(to_dev(B), Omd, Y=Y, beta=1))]
+    for Y in outs:
+        rows = [r for r in fine if r < Y.shape[0]]
+        assert torch.equal(Y[rows], clean[rows])
+        for r in bad:
+            assert np.array_equal(Y[r].double().cpu().numpy(), want[r], equal_nan=True), r
+    # non-finite columns of a stored Omega, met by finite and by infinite rows
+    Om2 = Om.copy()
+    Om2[10, 6], Om2[n - 1, 7], Om2[3, 8] = np.inf, -np.inf, np.nan
+    Y = run(lambda Y: sk.sketch_matmul_omega(to_dev(B), torch.from_numpy(Om2).to(DEV), Y=Y, beta=1))
+    keep = [c for c in range(k) if c not in (6, 7, 8)]
+    assert torch.equal(Y[fine][:, keep], clean[fine][:, keep])
+    Yh = Y.double().cpu().numpy()
+    with np.errstate(invalid="ignore"):
+        ref = B.astype(np.float64) @ Om2.astype(np.float64)
+    for r in range(m):
+        assert np.array_equal(Yh[r, 6:9], np.where(np.isnan(ref[r, 6:9]), np.nan, np.sign(ref[r, 6:9]) * np.inf),
+                              equal_nan=True), r
+        if r in bad:
+            assert np.array_equal(Yh[r, keep], want[r][keep], equal_nan=True), r
