@@ -399,7 +399,7 @@ __device__ __forceinline__ void emit(const TileOut& o, int64_t row, int64_t col,
 constexpr int kBadCol = 0x7FFF;
 
 // Sketch columns col .. col + 3 of a row, those below `end` (the lane's accumulator of
-// one 16 x 16 tile of Y^T).  Columns that fix_row evaluates are left to it: with one strip
+// one 16 x 16 tile of Y^T).  Columns that f32_sums evaluates are left to it: with one strip
 // and beta = 1 a second store would add to the first.
 __device__ __forceinline__ void emit4(const TileOut& o, int64_t row, int64_t col, int64_t end,
                                       const v4f v, float s, const int* ecol) {
@@ -419,37 +419,107 @@ __device__ __forceinline__ void emit4(const TileOut& o, int64_t row, int64_t col
         if (col + r < end && !bad[r]) emit(o, row, col + r, u[r]);
 }
 
-// Omega(j, c) of the tile's strip (j its column, c below 16 NT), wherever the tile
-// takes it from.
+// Omega rows 32 c + 8 g .. + 7 of the tile's strip, sketch column n_base + n, wherever the
+// tile takes them from; zeros past the strip's end and past kb columns.
 template <bool GEN, bool PK>
-__device__ __forceinline__ float omega_at(const MTile& t, int j, int c) {
-    if constexpr (PK) {
-        constexpr int CPS = kMfmaStrip / kSplitKC;
-        return t.fpack[((t.strip * CPS + j / kSplitKC) * t.kpad + t.n_base + c) * kSplitKC +
-                       j % kSplitKC];
+__device__ __forceinline__ void omega8(const MTile& t, int c, int g, int n, int w, int kb,
+                                       float (&z)[8]) {
+    constexpr int KC = kSplitKC;
+    const int kl0 = c * KC + 8 * g;
+    if constexpr (PK) {                       // the plane holds those zeros
+        const float* p = t.fpack + ((t.strip * (kMfmaStrip / KC) + c) * t.kpad + t.n_base + n) * KC + 8 * g;
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+            const v4f x = *reinterpret_cast<const v4f*>(p + 4 * v);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) z[4 * v + u] = x[u];
+        }
     } else if constexpr (GEN) {
-        const int64_t g = t.row0 + t.col_begin + j;
-        const float4 z = omega4_dist((uint64_t)(g >> 2), t.col0 + (uint32_t)(t.n_base + c), t.key0,
-                                     t.key1, t.dist);
-        const int u = (int)(g & 3);
-        return u == 0 ? z.x : u == 1 ? z.y : u == 2 ? z.z : z.w;
+        const int off = (int)((t.row0 + t.col_begin) & 3);   // the same in every lane
+        const uint64_t q = (uint64_t)((t.row0 + t.col_begin + kl0) >> 2);
+        const uint32_t col = t.col0 + (uint32_t)(t.n_base + n);
+        v4f quad[3] = {};
+#pragma unroll
+        for (int v = 0; v < 3; ++v) {
+            if (v == 2 && off == 0) break;             // not needed
+            const float4 x = omega4_dist(q + v, col, t.key0, t.key1, t.dist);
+            quad[v] = v4f{x.x, x.y, x.z, x.w};
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float r0 = quad[e / 4][e % 4], r1 = quad[(e + 1) / 4][(e + 1) % 4];
+            const float r2 = quad[(e + 2) / 4][(e + 2) % 4], r3 = quad[(e + 3) / 4][(e + 3) % 4];
+            const float r = off == 0 ? r0 : off == 1 ? r1 : off == 2 ? r2 : r3;
+            z[e] = kl0 + e < w && n < kb ? r : 0.0f;
+        }
     } else {
-        return t.omega[(t.col_begin + j) * t.ldo + t.n_base + c];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            z[e] = kl0 + e < w && n < kb ? t.omega[(t.col_begin + kl0 + e) * t.ldo + t.n_base + n] : 0.0f;
     }
 }
 
-// Strip sums whose row of A holds an infinity, or whose column of a stored Omega holds
-// infinity or NaN, with FP32 products (the FP16 terms of an infinity would meet zeros
-// and the other sign): row `row` (its first strip element at `a`, the
-// next `stride` further), sketch columns lane, lane + 64, ... below kb that `want` picks.
-template <bool GEN, bool PK, typename Want>
-__device__ __forceinline__ void fix_row(const MTile& t, const TileOut& o, const float* a,
-                                        int64_t stride, int64_t row, int w, int kb, Want want) {
-    for (int c = threadIdx.x & 63; c < kb; c += 64) {
-        if (!want(c)) continue;
-        float v = 0.0f;
-        for (int j = 0; j < w; ++j) v = __builtin_fmaf(a[j * stride], omega_at<GEN, PK>(t, j, c), v);
-        emit(o, row, t.n_base + c, v);
+// The strip sums of one wave's row tiles that `want(tm, column)` picks, with the FP32
+// matrix instruction: what the FP16 terms cannot hold (a row of A with an infinity, whose
+// terms would meet zeros and the other sign, a non-finite column of a stored Omega).
+// load(x, c) gives chunk c of A as ALoads does, row_of(tm) the lane's row of tile tm.
+// Each wave reads Omega for itself, up to four N-tiles at a time from the packed plane, one
+// at a time (A read again for each) where a lane generates its values.  The product of each 32
+// columns is eight MFMAs in the order of the contraction index 8 g + e, so that the sums do
+// not depend on the tile or on A's storage order.
+template <int NT, int TM, bool GEN, bool PK, typename Load, typename RowOf, typename Want>
+__device__ __forceinline__ void f32_sums(const MTile& t, const TileOut& o, int nchunks, int w, int kb,
+                                         int g, int i16, Load load, RowOf row_of, Want want) {
+    constexpr int NP = PK ? (NT < 4 ? NT : 4) : 1;   // four fit the registers of the main loop
+#pragma unroll 1
+    for (int nt0 = 0; nt0 < NT; nt0 += NP) {
+        bool any = false;
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+            for (int u = 0; u < NP; ++u)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) any = any || want(tm, (nt0 + u) * 16 + 4 * g + r);
+        if (!__any(any)) continue;
+        v4f acc[TM][NP];
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+            for (int u = 0; u < NP; ++u) acc[tm][u] = v4f{0.f, 0.f, 0.f, 0.f};
+        float x[TM][8];
+        load(x, 0);
+#pragma unroll 1
+        for (int c = 0; c < nchunks; ++c) {
+            float nx[TM][8];
+            load(nx, min(c + 1, nchunks - 1));
+            float z[NP][8];
+#pragma unroll
+            for (int u = 0; u < NP; ++u) omega8<GEN, PK>(t, c, g, (nt0 + u) * 16 + i16, w, kb, z[u]);
+#pragma unroll
+            for (int u = 0; u < NP; ++u)
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+#pragma unroll
+                    for (int tm = 0; tm < TM; ++tm)
+                        acc[tm][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(z[u][e], x[tm][e], acc[tm][u],
+                                                                          0, 0, 0);
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) x[tm][e] = nx[tm][e];
+        }
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) {
+            const int64_t row = row_of(tm);
+            if (row >= t.m) continue;
+#pragma unroll
+            for (int u = 0; u < NP; ++u)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int c = (nt0 + u) * 16 + 4 * g + r;
+                    if (c < kb && want(tm, c)) emit(o, row, t.n_base + c, acc[tm][u][r]);
+                }
+        }
     }
 }
 
@@ -495,7 +565,7 @@ __device__ __forceinline__ void omega_exponents(const MTile& t, int* ecol, int w
                 const int it = min(it0 + u * TH, total - 1);
                 const int j = it / kb;
                 n[u] = it - j * kb;
-                x[u] = omega_at<false, PK>(t, j, n[u]);
+                x[u] = t.omega[(t.col_begin + j) * t.ldo + t.n_base + n[u]];
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) atomicMax(&ecol[n[u]], __float_as_int(x[u]) & 0x7FFFFFFF);
@@ -872,32 +942,24 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT, tile_grou
                   stored ? &L.ecol[nt * 16 + 4 * g] : nullptr);
     }
     // ---- non-finite entries, with FP32 products ---------------------------------------
-    bool any_inf = false;
+    bool redo = false;
 #pragma unroll
-    for (int tm = 0; tm < TM; ++tm) any_inf = any_inf || inf[tm];
-    uint64_t done = 0;            // rows (of the wave's 16 TM) evaluated whole
-    if (__any(any_inf)) {
+    for (int tm = 0; tm < TM; ++tm) redo = redo || inf[tm];
+    if (stored)
+        for (int n = lane; n < kb; n += 64) redo = redo || L.ecol[n] == kBadCol;
+    if (__any(redo)) {
+        f32_sums<NT, TM, GEN, PK>(
+            t, o, nchunks, w, kb, g, i16,
+            [&](float (&x)[TM][8], int c) {
+                v4f r[TM][2];
+                A.load(r, c);
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm) {
-            done |= (__ballot(inf[tm]) & 0xFFFFu) << (16 * tm);
-            for (uint64_t rows = __ballot(inf[tm]) & 0xFFFFu; rows != 0; rows &= rows - 1) {
-                const int64_t row = row_base + tm * 16 + __builtin_ctzll(rows);
-                if (row >= t.m) break;
-                fix_row<GEN, PK>(t, o, reinterpret_cast<const float*>(t.A) + row * t.lda + t.col_begin,
-                                 1, row, w, kb, [](int) { return true; });
-            }
-        }
-    }
-    if (stored) {
-        bool bad = false;
-        for (int n = lane; n < kb; n += 64) bad = bad || L.ecol[n] == kBadCol;
-        if (__any(bad)) {
-            for (int64_t row = row_base; row < min<int64_t>(row_base + TM * 16, t.m); ++row)
-                if (!((done >> (row - row_base)) & 1))
-                    fix_row<GEN, PK>(t, o,
-                                     reinterpret_cast<const float*>(t.A) + row * t.lda + t.col_begin,
-                                     1, row, w, kb, [&](int c) { return L.ecol[c] == kBadCol; });
-        }
+                for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) x[tm][e] = r[tm][e >> 2][e & 3];
+            },
+            [&](int tm) { return row_base + tm * 16 + i16; },
+            [&](int tm, int c) { return inf[tm] || (stored && L.ecol[c] == kBadCol); });
     }
 }
 
@@ -1063,30 +1125,6 @@ __device__ __forceinline__ TileOut cm_out(const CmMArgs& a, int strip) {
     return o;
 }
 
-// Rows of row set q (row 4j + q of lane j, from row r0 of the wave) that hold an infinity
-// (see fix_row).
-template <bool PK = true>
-__device__ __forceinline__ void cm_fix_rows(const CmMArgs& a, const TileOut& o, int strip,
-                                            int n_base, bool inf, int64_t first, int w, int kb) {
-    MTile t{};
-    t.row0 = a.row0;
-    t.col_begin = (int64_t)strip * kMfmaStrip;
-    t.n_base = n_base;
-    t.key0 = a.key0;
-    t.key1 = a.key1;
-    t.col0 = a.col0;
-    t.dist = a.dist;
-    t.strip = strip;
-    t.kpad = a.kpad;
-    t.fpack = a.fpack;
-    for (uint64_t rows = __ballot(inf) & 0xFFFFu; rows != 0; rows &= rows - 1) {
-        const int64_t row = first + 4 * __builtin_ctzll(rows);
-        if (row >= a.m) break;
-        fix_row<true, PK>(t, o, a.A + t.col_begin * a.lda + row, a.lda, row, w, kb,
-                          [](int) { return true; });
-    }
-}
-
 template <int NT, int kKC, bool FULL, bool ROWS4>
 __global__ __launch_bounds__(kThreads) void k_gemm_cm_mfma(const CmMArgs a) {
     constexpr int BN = 16 * NT;
@@ -1218,8 +1256,8 @@ __global__ __launch_bounds__(kThreads) void k_gemm_cm_mfma(const CmMArgs a) {
     }
     lds_barrier_m();
 
-    h8 a0[4], a1[4], a0s[4];
-    auto split = [&](v4f* x) {
+    // a cut group's rows, loaded as the last four
+    auto shift_cut = [&](v4f* x) {
         if constexpr (FULL && !ROWS4) {
             if (cut == 1) {
 #pragma unroll
@@ -1232,6 +1270,10 @@ __global__ __launch_bounds__(kThreads) void k_gemm_cm_mfma(const CmMArgs a) {
                 for (int e = 0; e < 8; ++e) x[e] = v4f{x[e][1], x[e][2], x[e][3], 0.f};
             }
         }
+    };
+    h8 a0[4], a1[4], a0s[4];
+    auto split = [&](v4f* x) {
+        shift_cut(x);
         float y[4][8];
         float mx = 0.0f;
 #pragma unroll
@@ -1353,8 +1395,22 @@ __global__ __launch_bounds__(kThreads) void k_gemm_cm_mfma(const CmMArgs a) {
             emit4(o, rl + q, t.n_base + nt * 16 + 4 * g, t.n_base + kb, acc[q][nt], sc[q], nullptr);
     }
     if (__any(inf[0] || inf[1] || inf[2] || inf[3])) {
+        t.strip = strip;
+        t.m = a.m;
+        t.kpad = a.kpad;
+        t.fpack = a.fpack;
+        f32_sums<NT, 4, true, PK>(
+            t, o, nchunks, w, kb, g, j,
+            [&](float (&x)[4][8], int c) {
+                v4f r[kNS];
+                load_a(r, c);
+                shift_cut(r);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) cm_fix_rows<PK>(a, o, strip, t.n_base, inf[q], r0 + q, w, kb);
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) x[q][e] = r[e][q];
+            },
+            [&](int q) { return rl + q; }, [&](int q, int) { return inf[q]; });
     }
 }
 
@@ -1538,7 +1594,24 @@ __global__ __launch_bounds__(kSkThreads) void k_gemm_cm_mfma_skinny(const CmMArg
     const TileOut o = cm_out(a, strip);
     const int64_t row = rl + q;
     if (row < a.m && !inf) emit4(o, row, n_base + 4 * g, n_base + kb, acc, sc, nullptr);
-    cm_fix_rows(a, o, strip, n_base, inf, q, w, kb);
+    if (__any(inf)) {
+        MTile t{};
+        t.m = a.m;
+        t.n_base = n_base;
+        t.strip = strip;
+        t.kpad = a.kpad;
+        t.fpack = a.fpack;
+        f32_sums<1, 1, true, true>(
+            t, o, nchunks, w, kb, g, j,
+            [&](float (&x)[1][8], int c) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int kl = c * kKC + 8 * g + e;
+                    x[0][e] = kl < w && row < a.m ? a.A[(col_begin + kl) * a.lda + row] : 0.0f;
+                }
+            },
+            [&](int) { return row; }, [&](int, int) { return inf; });
+    }
 }
 
 template <int NT, int KC>

@@ -221,3 +221,30 @@ def test_non_finite_entries_add_to_y_once(n, k, y_dtype):
                               equal_nan=True), r
         if r in bad:
             assert np.array_equal(Yh[r, keep], want[r][keep], equal_nan=True), r
+
+
+def test_cost_of_infinite_rows():
+    """A matrix with an infinity in every row is multiplied by the FP32 instruction: at 1/16 of
+    the rate for two of the FP16 instruction's four products, eight times the matrix-core time
+    in addition to the first pass; 16 leaves room for generation in every wave (the server)."""
+    m, n, k = 4096, 8192, 64
+    A = to_dev(normal_matrix(m, n, seed=1))
+    B = A.clone()
+    B[:, 77] = float("inf")
+    Acm, Bcm = cm_dev(A.cpu().numpy()), cm_dev(B.cpu().numpy())
+
+    def ms(f):
+        times = []
+        for _ in range(4):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            f()
+            e1.record()
+            torch.cuda.synchronize()
+            times.append(e0.elapsed_time(e1))
+        return min(times[1:])
+
+    for f, x, y in [(sk.sketch_gen_matmul, A, B), (sk.sketch_gen_matmul_cm, Acm, Bcm)]:
+        for kk in (24, k):
+            clean, inf = ms(lambda: f(x, 3, kk)), ms(lambda: f(y, 3, kk))
+            assert inf <= 16 * clean, (f.__name__, kk, clean, inf)
