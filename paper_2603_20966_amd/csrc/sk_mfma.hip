@@ -224,21 +224,19 @@ __device__ __forceinline__ void omega_zero_pad(_Float16 (*om)[BN][kSplitRow], in
 
 // Chunks c0 .. c0 + G - 1 (those below nchunks) of the tile's strip, sketch columns
 // n_base .. n_base + kb - 1, split into LDS slots slot0 .. (slot0 + G - 1); zeros past
-// the strip's end.  Generated from the seed, or read from a stored Omega (scaled by
-// 2^-ecol).  With few sketch columns one chunk has too few Philox quads to occupy the
+// the strip's end.  Generated from the seed, or read from a stored Omega.  With few sketch columns one chunk has too few Philox quads to occupy the
 // workgroup, G of them do.  A chunk's first Omega row is aligned as the strip's (chunk
 // widths are multiples of 4), so every chunk has the same quad count.
 template <int BN, int TH, int G, bool GEN>
 __device__ __forceinline__ void omega_group(const MTile& t, _Float16 (*om)[BN][kSplitRow],
-                                            int slot0, int c0, int nchunks, int w, int kb,
-                                            const int* ecol) {
+                                            int slot0, int c0, int nchunks, int w, int kb) {
     constexpr int KC = kSplitKC;
     const int cnt = min(G, nchunks - c0);
+    const float sc = __builtin_ldexpf(1.0f, kOmegaExp);
     if constexpr (GEN) {
         const int64_t gb = t.row0 + t.col_begin;                     // Omega row of strip column 0
         const int nq = (int)(((gb + KC - 1) >> 2) - (gb >> 2) + 1);   // KC/4, or one more if unaligned
         const int per = nq * kb;
-        const float sc = __builtin_ldexpf(1.0f, kOmegaExp);
         for (int it = threadIdx.x; it < cnt * per; it += TH) {
             const int ci = it / per;
             const int r = it - ci * per;
@@ -273,7 +271,7 @@ __device__ __forceinline__ void omega_group(const MTile& t, _Float16 (*om)[BN][k
             float z = 0.0f;
             if (c * KC + kl < w)
                 z = t.omega[(t.col_begin + (int64_t)c * KC + kl) * t.ldo + t.n_base + n];
-            split_store1(om[slot0 + ci][n], kl, z, __builtin_ldexpf(1.0f, kOmegaExp - ecol[n]));
+            split_store1(om[slot0 + ci][n], kl, z, sc);
         }
     }
 }
@@ -375,6 +373,12 @@ struct TileOut {
     void* Y;
     int64_t k, ldy;
     int y_trans, y_f64, beta;
+    // runs of four sketch columns lie 16-byte aligned and are only stored
+    __device__ __forceinline__ bool vec() const {
+        return !scales && (partials ? (k & 3) == 0
+                                    : !(y_trans || y_f64 || beta) && (ldy & 3) == 0 &&
+                                          ((uintptr_t)Y & 15) == 0);
+    }
 };
 __device__ __forceinline__ void emit(const TileOut& o, int64_t row, int64_t col, float v) {
     if (o.scales) v *= o.scales[row >> 7];
@@ -395,194 +399,288 @@ __device__ __forceinline__ void emit(const TileOut& o, int64_t row, int64_t col,
     }
 }
 
-// Exponent of a stored Omega's column that holds an infinity or NaN (see omega_exponents).
-constexpr int kBadCol = 0x7FFF;
-
-// Sketch columns col .. col + 3 of a row, those below `end` (the lane's accumulator of
-// one 16 x 16 tile of Y^T).  Columns that f32_sums evaluates are left to it: with one strip
-// and beta = 1 a second store would add to the first.
-__device__ __forceinline__ void emit4(const TileOut& o, int64_t row, int64_t col, int64_t end,
-                                      const v4f v, float s, const int* ecol) {
-    v4f u;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) u[r] = unscale(v[r], s, ecol ? ecol[r] : 0);
-    bool bad[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) bad[r] = ecol && ecol[r] == kBadCol;
-    if (o.partials && !o.scales && (o.k & 3) == 0 && col + 3 < end &&
-        !(bad[0] || bad[1] || bad[2] || bad[3])) {
-        *reinterpret_cast<v4f*>(o.partials + row * o.k + col) = u;   // k, col multiples of 4
+// Sketch columns col .. col + 3 (col a multiple of 4) of a row, those below `end` that
+// `skip` leaves.
+__device__ __forceinline__ void emit4(const TileOut& o, bool vec, int64_t row, int64_t col,
+                                      int64_t end, const v4f u, const bool (&skip)[4]) {
+    if (vec && col + 3 < end && !(skip[0] || skip[1] || skip[2] || skip[3])) {
+        float* p = o.partials ? o.partials + row * o.k : static_cast<float*>(o.Y) + row * o.ldy;
+        *reinterpret_cast<v4f*>(p + col) = u;
         return;
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-        if (col + r < end && !bad[r]) emit(o, row, col + r, u[r]);
+        if (col + r < end && !skip[r]) emit(o, row, col + r, u[r]);
 }
 
-// Omega rows 32 c + 8 g .. + 7 of the tile's strip, sketch column n_base + n, wherever the
-// tile takes them from; zeros past the strip's end and past kb columns.
-template <bool GEN, bool PK>
-__device__ __forceinline__ void omega8(const MTile& t, int c, int g, int n, int w, int kb,
-                                       float (&z)[8]) {
+// The lane's accumulator of one 16 x 16 tile of Y^T, of a row with scale s.  Columns that
+// f32_sums evaluates (f32col, of a stored Omega) are left to it: with one strip and beta = 1
+// a second store would add to the first.
+__device__ __forceinline__ void emit_split(const TileOut& o, bool vec, int64_t row, int64_t col,
+                                           int64_t end, const v4f v, float s, const int* f32col) {
+    v4f u;
+    bool skip[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        u[r] = unscale(v[r], s);
+        skip[r] = f32col && f32col[r];
+    }
+    emit4(o, vec, row, col, end, u, skip);
+}
+
+constexpr int kF32Row = kSplitKC + 4;   // floats per LDS column of an FP32 chunk
+template <int TH, bool GEN>
+__device__ __forceinline__ void omega_chunk_f32(const MTile& t, float (*om)[kF32Row], int c, int w,
+                                                int kb, int first) {
+    // thread `first` takes the first item
+    const int start = (int)threadIdx.x >= first ? (int)threadIdx.x - first
+                                                : (int)threadIdx.x - first + TH;
     constexpr int KC = kSplitKC;
-    const int kl0 = c * KC + 8 * g;
-    if constexpr (PK) {                       // the plane holds those zeros
-        const float* p = t.fpack + ((t.strip * (kMfmaStrip / KC) + c) * t.kpad + t.n_base + n) * KC + 8 * g;
+    const int kvalid = min(KC, w - c * KC);
+    if constexpr (GEN) {
+        const int64_t g0 = t.row0 + t.col_begin + (int64_t)c * KC;   // global Omega row of local 0
+        const int64_t q_lo = g0 >> 2;
+        const int nq = (int)(((g0 + KC - 1) >> 2) - q_lo + 1);        // KC/4, or one more if unaligned
+        for (int it = start; it < nq * kb; it += TH) {
+            const int qi = it / kb;
+            const int n = it - qi * kb;
+            const float4 z = omega4_dist((uint64_t)(q_lo + qi), t.col0 + (uint32_t)(t.n_base + n),
+                                         t.key0, t.key1, t.dist);
+            const int kl0 = (int)(4 * (q_lo + qi) - g0);
+            if (kl0 >= 0 && (kl0 & 3) == 0 && kl0 + 3 < kvalid) {
+                *reinterpret_cast<float4*>(&om[n][kl0]) = z;
+            } else {
+                const float zz[4] = {z.x, z.y, z.z, z.w};
 #pragma unroll
-        for (int v = 0; v < 2; ++v) {
-            const v4f x = *reinterpret_cast<const v4f*>(p + 4 * v);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) z[4 * v + u] = x[u];
-        }
-    } else if constexpr (GEN) {
-        const int off = (int)((t.row0 + t.col_begin) & 3);   // the same in every lane
-        const uint64_t q = (uint64_t)((t.row0 + t.col_begin + kl0) >> 2);
-        const uint32_t col = t.col0 + (uint32_t)(t.n_base + n);
-        v4f quad[3] = {};
-#pragma unroll
-        for (int v = 0; v < 3; ++v) {
-            if (v == 2 && off == 0) break;             // not needed
-            const float4 x = omega4_dist(q + v, col, t.key0, t.key1, t.dist);
-            quad[v] = v4f{x.x, x.y, x.z, x.w};
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float r0 = quad[e / 4][e % 4], r1 = quad[(e + 1) / 4][(e + 1) % 4];
-            const float r2 = quad[(e + 2) / 4][(e + 2) % 4], r3 = quad[(e + 3) / 4][(e + 3) % 4];
-            const float r = off == 0 ? r0 : off == 1 ? r1 : off == 2 ? r2 : r3;
-            z[e] = kl0 + e < w && n < kb ? r : 0.0f;
+                for (int u = 0; u < 4; ++u) {
+                    const int kl = kl0 + u;
+                    if (kl >= 0 && kl < KC) om[n][kl] = (kl < kvalid) ? zz[u] : 0.0f;
+                }
+            }
         }
     } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            z[e] = kl0 + e < w && n < kb ? t.omega[(t.col_begin + kl0 + e) * t.ldo + t.n_base + n] : 0.0f;
+        for (int it = start; it < KC * kb; it += TH) {
+            const int kl = it / kb;
+            const int n = it - kl * kb;
+            om[n][kl] = (kl < kvalid)
+                            ? t.omega[(t.col_begin + (int64_t)c * KC + kl) * t.ldo + t.n_base + n]
+                            : 0.0f;
+        }
     }
 }
 
-// The strip sums of one wave's row tiles that `want(tm, column)` picks, with the FP32
-// matrix instruction: what the FP16 terms cannot hold (a row of A with an infinity, whose
-// terms would meet zeros and the other sign, a non-finite column of a stored Omega).
-// load(x, c) gives chunk c of A as ALoads does, row_of(tm) the lane's row of tile tm.
-// Each wave reads Omega for itself, up to four N-tiles at a time from the packed plane, one
-// at a time (A read again for each) where a lane generates its values.  The product of each 32
-// columns is eight MFMAs in the order of the contraction index 8 g + e, so that the sums do
-// not depend on the tile or on A's storage order.
-template <int NT, int TM, bool GEN, bool PK, typename Load, typename RowOf, typename Want>
-__device__ __forceinline__ void f32_sums(const MTile& t, const TileOut& o, int nchunks, int w, int kb,
-                                         int g, int i16, Load load, RowOf row_of, Want want) {
-    constexpr int NP = PK ? (NT < 4 ? NT : 4) : 1;   // four fit the registers of the main loop
-#pragma unroll 1
-    for (int nt0 = 0; nt0 < NT; nt0 += NP) {
-        bool any = false;
+// The strip sums of a tile's rows with row_f32[tm] (the lane's row of its row tile tm) and
+// columns with f32col (nullptr: none), or all of them, with the FP32 matrix instruction: what
+// the FP16 terms cannot hold (a row of A with an infinity, whose terms would meet zeros and
+// the other sign, and the columns of stored_columns), and strips narrower than a chunk, whose
+// few FP32 roundings are less than what the terms leave out (1 to 15 columns of N(0,1):
+// 2.5e-8 to 7e-8 against 7e-8).
+// Every wave of the workgroup takes part; `rows`: this one has rows.  load(x, c) gives chunk
+// c of A as ALoads does, row_of(tm) the lane's row of tile tm.  Omega's chunks go through LDS
+// (`om`, two halves of 16 NT columns) as in mfma_tile; the product of 32 columns is eight
+// MFMAs in the order of the contraction index 8 g + e, so that the sums depend neither on the
+// tile nor on A's storage order.
+template <int NT, int TM, int TH, bool GEN, bool PK, typename Load, typename RowOf>
+__device__ __forceinline__ void f32_sums(const MTile& t, const TileOut& o, float* om_lds, int w, int kb,
+                                         bool rows, Load load, RowOf row_of, bool all,
+                                         const bool (&row_f32)[TM], const int* f32col) {
+    constexpr int KC = kSplitKC, BN = 16 * NT;
+    // copied Omega: 16-byte pieces of the packed plane, or single values of a stored one (row
+    // by row), OPT per thread; values past the strip's end or k columns are zeros
+    constexpr int PPL = PK ? BN * KC / 4 : BN * KC, OPT = (PPL + TH - 1) / TH;
+    using Piece = std::conditional_t<PK, v4f, float>;
+    constexpr bool COPY = PK || !GEN;
+    float (*om)[BN][kF32Row] = reinterpret_cast<float (*)[BN][kF32Row]>(om_lds);
+    const int tid = threadIdx.x, g = (tid & 63) >> 4, i16 = tid & 15;
+    const int nchunks = (w + KC - 1) / KC;
+    auto om_load = [&](Piece* r, int c) {
+        if constexpr (PK) {
+            const float* p = t.fpack + ((t.strip * (kMfmaStrip / KC) + min(c, nchunks - 1)) * t.kpad + t.n_base) * KC;
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm)
+            for (int j = 0; j < OPT; ++j) r[j] = *reinterpret_cast<const v4f*>(p + 4 * min(tid + j * TH, PPL - 1));
+        } else if constexpr (COPY) {
 #pragma unroll
-            for (int u = 0; u < NP; ++u)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) any = any || want(tm, (nt0 + u) * 16 + 4 * g + r);
-        if (!__any(any)) continue;
-        v4f acc[TM][NP];
-#pragma unroll
-        for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-            for (int u = 0; u < NP; ++u) acc[tm][u] = v4f{0.f, 0.f, 0.f, 0.f};
-        float x[TM][8];
-        load(x, 0);
-#pragma unroll 1
-        for (int c = 0; c < nchunks; ++c) {
-            float nx[TM][8];
-            load(nx, min(c + 1, nchunks - 1));
-            float z[NP][8];
-#pragma unroll
-            for (int u = 0; u < NP; ++u) omega8<GEN, PK>(t, c, g, (nt0 + u) * 16 + i16, w, kb, z[u]);
-#pragma unroll
-            for (int u = 0; u < NP; ++u)
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-#pragma unroll
-                    for (int tm = 0; tm < TM; ++tm)
-                        acc[tm][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(z[u][e], x[tm][e], acc[tm][u],
-                                                                          0, 0, 0);
-#pragma unroll
-            for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) x[tm][e] = nx[tm][e];
+            for (int j = 0; j < OPT; ++j) {
+                const int q = tid + j * TH, kl = c * KC + q / BN, n = q % BN;
+                r[j] = t.omega[(t.col_begin + min(kl, w - 1)) * t.ldo + t.n_base + min(n, kb - 1)];
+                r[j] = kl < w && n < kb ? r[j] : 0.0f;
+            }
         }
+    };
+    auto om_store = [&](const Piece* r, int c) {
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm) {
-            const int64_t row = row_of(tm);
-            if (row >= t.m) continue;
+        for (int j = 0; j < OPT; ++j) {
+            const int q = min(tid + j * TH, PPL - 1);
+            if constexpr (PK) *reinterpret_cast<v4f*>(&om[c & 1][q / (KC / 4)][(q % (KC / 4)) * 4]) = r[j];
+            else om[c & 1][q % BN][q / BN] = r[j];
+        }
+    };
+    v4f acc[TM][NT];
 #pragma unroll
-            for (int u = 0; u < NP; ++u)
+    for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int c = (nt0 + u) * 16 + 4 * g + r;
-                    if (c < kb && want(tm, c)) emit(o, row, t.n_base + c, acc[tm][u][r]);
+        for (int nt = 0; nt < NT; ++nt) acc[tm][nt] = v4f{0.f, 0.f, 0.f, 0.f};
+    float x0[TM][8], x1[TM][8];
+    static_assert(PK || PPL % TH == 0, "whole values per thread");
+    Piece r[COPY ? OPT : 1];
+    if constexpr (COPY) {
+        om_load(r, 0);
+        if (rows) load(x0, 0);
+        om_store(r, 0);
+        om_load(r, 1);
+        if (rows) load(x1, min(1, nchunks - 1));
+    } else {
+        if (rows) load(x0, 0);
+        if (rows) load(x1, min(1, nchunks - 1));
+        for (int it = tid; it < 2 * BN * kF32Row; it += TH)
+            if ((it / kF32Row) % BN >= kb) (&om[0][0][0])[it] = 0.0f;
+        omega_chunk_f32<TH, true>(t, om[0], 0, w, kb, 0);
+    }
+    lds_barrier_m();
+    auto step = [&](float (&x)[TM][8], int c) {
+        if constexpr (COPY) {
+            om_store(r, c + 1);
+            om_load(r, c + 2);
+        } else if (c + 1 < nchunks) {
+            omega_chunk_f32<TH, true>(t, om[(c + 1) & 1], c + 1, w, kb, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (rows) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int v = 0; v < 2; ++v) {
+                    const v4f z = *reinterpret_cast<const v4f*>(&om[c & 1][nt * 16 + i16][8 * g + 4 * v]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int tm = 0; tm < TM; ++tm)
+                            acc[tm][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(z[e], x[tm][4 * v + e],
+                                                                               acc[tm][nt], 0, 0, 0);
                 }
+            load(x, min(c + 2, nchunks - 1));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        lds_barrier_m();
+    };
+#pragma unroll 1
+    for (int c = 0; c < nchunks; c += 2) {
+        step(x0, c);
+        if (c + 1 < nchunks) step(x1, c + 1);
+    }
+    if (!rows) return;
+    const bool vec = o.vec();
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm) {
+        const int64_t row = row_of(tm);
+        if (row >= t.m) continue;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const int c = nt * 16 + 4 * g;
+            bool skip[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) skip[q] = !(all || row_f32[tm] || (f32col && f32col[c + q]));
+            emit4(o, vec, row, t.n_base + c, t.n_base + kb, acc[tm][nt], skip);
         }
     }
 }
 
-// Exponents of a stored Omega's columns in the tile's strip: ecol[n] scales column n
-// into FP16's range (0 for |omega| <= 6 down to 2^-25, which every generated strip has,
-// so that a stored copy of it multiplies with the same bits); kBadCol marks an
-// infinity or NaN.
+// Which columns of a stored Omega the FP16 terms would not serve in the tile's strip.  The
+// terms of a row of A hold its entries down to 2^-35 of the largest and those of Omega an
+// entry to within 2^-49; under entries like N(0,1) ones that stays below an FP32 sum's
+// rounding, but zeros (sparse or selecting columns) or a wide range can bring out a row's
+// small entries alone.  So the strip's w >= 32 entries of a column have to be such as could
+// have been generated: no zero, none above 6 in modulus (generated ones reach 5.77), at most
+// 8 + w/64 below 2^-10 and 3 below 2^-25.  Generated columns exceed these counts with a
+// probability under 1e-18 each: a stored copy multiplies with the same bits.
+// f32col[n] = kOther for another column: then the tile multiplies all of its columns with
+// f32_sums (65536 x 16384 at k = 64: 1278 us, and 1212 with the FP32 instruction alone, before
+// the terms; 940 to 960 with the terms); kNonFinite for one with an infinity or NaN, which
+// goes there alone.
+constexpr int kOther = 1, kNonFinite = 2;
 template <int BN, int TH, bool PK>
-__device__ __forceinline__ void omega_exponents(const MTile& t, int* ecol, int w, int kb) {
-    for (int n = threadIdx.x; n < BN; n += TH) ecol[n] = 0;
+__device__ __forceinline__ void stored_columns(const MTile& t, int* f32col, int w, int kb) {
+    // counts in one word: entries below 2^-10, below 2^-25, never generated, non-finite
+    constexpr int kSmall = 1, kTiny = 1 << 12, kNever = 1 << 24, kInf = 1 << 25;
+    auto grade = [=](int b) {
+        if (b >= 0x7F800000) return kInf;
+        if (b == 0 || b > __float_as_int(6.0f)) return kNever;
+        return b < __float_as_int(0x1p-25f) ? kSmall + kTiny : b < __float_as_int(0x1p-10f) ? kSmall : 0;
+    };
+    auto add = [=](int sum, int q) { return q >= kNever ? sum | q : sum + q; };
+    for (int n = threadIdx.x; n < BN; n += TH) f32col[n] = 0;
     __syncthreads();
+    auto count = [=](int n, int sum) {
+        const int mark = sum & (kNever | kInf);
+        if (mark & ~f32col[n]) atomicOr(&f32col[n], mark);     // a sparse column has many
+        if (sum & (kNever - 1)) atomicAdd(&f32col[n], sum & (kNever - 1));
+    };
+    // one such column sends the whole tile to f32_sums: no need to look further, and which
+    // column is marked makes no difference
+    auto settled = [=](int sum) {
+        if (sum & kNever) atomicOr(&f32col[0], kNever);
+        return (*(volatile int*)f32col & kNever) != 0;
+    };
     if constexpr (PK) {
-        // a chunk's BN columns are one run of the packed plane (zeros past w and k): thread
-        // tid's V pieces of four values lie in the same columns in every chunk
+        // a chunk's BN columns are one run of the packed plane: thread tid's V pieces of
+        // four values lie in the same columns and rows of every chunk
         constexpr int kPieces = kSplitKC / 4;
         constexpr int V = BN * kPieces / TH;
         static_assert(V * TH == BN * kPieces, "whole pieces per thread");
         constexpr int CPS = kMfmaStrip / kSplitKC;
-        int amax[V];
+        int sum[V], wv[V];                     // wv: the plane holds zeros past kb columns
 #pragma unroll
-        for (int v = 0; v < V; ++v) amax[v] = 0;
+        for (int v = 0; v < V; ++v) {
+            sum[v] = 0;
+            wv[v] = (threadIdx.x + v * TH) / kPieces < kb ? w : 0;
+        }
         const int nch = (w + kSplitKC - 1) / kSplitKC;
+        const int row = 4 * (threadIdx.x % kPieces);       // of the pieces, within a chunk
 #pragma unroll 8
         for (int c = 0; c < nch; ++c) {
             const float* p = t.fpack + ((t.strip * CPS + c) * t.kpad + t.n_base) * kSplitKC;
 #pragma unroll
             for (int v = 0; v < V; ++v) {
                 const v4f x = *reinterpret_cast<const v4f*>(p + 4 * (threadIdx.x + v * TH));
+                int b[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) amax[v] = max(amax[v], __float_as_int(x[u]) & 0x7FFFFFFF);
+                for (int u = 0; u < 4; ++u) b[u] = __float_as_int(x[u]) & 0x7FFFFFFF;
+                if (max(max(b[0], b[1]), max(b[2], b[3])) > __float_as_int(6.0f) ||
+                    min(min(b[0], b[1]), min(b[2], b[3])) < __float_as_int(0x1p-10f)) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (c * kSplitKC + row + u < wv[v]) sum[v] = add(sum[v], grade(b[u]));
+                }
             }
+            if (c % 8 == 7 && settled(sum[0])) break;
         }
 #pragma unroll
-        for (int v = 0; v < V; ++v) atomicMax(&ecol[(threadIdx.x + v * TH) / kPieces], amax[v]);
+        for (int v = 0; v < V; ++v) count((threadIdx.x + v * TH) / kPieces, sum[v]);
     } else {
-        // eight loads in flight per thread; a position past the end repeats the last one
+        // sixteen loads in flight per thread
+        constexpr int L = 16;
         const int total = w * kb;
-        for (int it0 = threadIdx.x; it0 < total; it0 += 8 * TH) {
-            float x[8];
-            int n[8];
+        for (int it0 = threadIdx.x; it0 < total; it0 += L * TH) {
+            float x[L];
+            int n[L];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
+            for (int u = 0; u < L; ++u) {
                 const int it = min(it0 + u * TH, total - 1);
                 const int j = it / kb;
                 n[u] = it - j * kb;
                 x[u] = t.omega[(t.col_begin + j) * t.ldo + t.n_base + n[u]];
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) atomicMax(&ecol[n[u]], __float_as_int(x[u]) & 0x7FFFFFFF);
+            for (int u = 0; u < L; ++u)
+                if (it0 + u * TH < total) count(n[u], grade(__float_as_int(x[u]) & 0x7FFFFFFF));
+            if (settled(0)) break;
         }
     }
     __syncthreads();
-    for (int n = threadIdx.x; n < BN; n += TH) {
-        const int b = ecol[n];
-        int e = 0;
-        if (b >= 0x7F800000) {
-            e = kBadCol;
-        } else if (b > __float_as_int(6.0f) || (b != 0 && b < __float_as_int(0x1p-25f))) {
-            int x;
-            (void)frexpf(__int_as_float(b), &x);   // amax in [2^(x-1), 2^x) -> [2, 4)
-            e = max(x - 2, -110);                   // 2^(13 - e) stays an FP32 number
-        }
-        ecol[n] = e;
+    for (int n = threadIdx.x; n < kb; n += TH) {
+        const int q = f32col[n];
+        const bool many = q % kNever / kTiny > 3 || q % kTiny > 8 + w / 64;
+        f32col[n] = q & kNever ? kOther : q & kInf ? kNonFinite : many ? kOther : 0;
     }
     __syncthreads();
 }
@@ -652,51 +750,10 @@ struct ALoads {
 // k = 16 takes 767 us here and 800 us with split operands.  Same tile, loads and barriers as
 // mfma_tile; A is the A operand, 8 MFMAs per chunk and row tile: component s of 16-byte load
 // v is contraction index g of MFMA 4v + s.  FULL as for mfma_tile.
-constexpr int kF32Row = kSplitKC + 4;   // floats per LDS column of a chunk
 template <int G>
 struct F32Lds {
     float om[2 * G][16][kF32Row];
 };
-
-template <int TH, bool GEN>
-__device__ __forceinline__ void omega_chunk_f32(const MTile& t, float (*om)[kF32Row], int c, int w,
-                                                int kb, int first) {
-    // thread `first` takes the first item
-    const int start = (int)threadIdx.x >= first ? (int)threadIdx.x - first
-                                                : (int)threadIdx.x - first + TH;
-    constexpr int KC = kSplitKC;
-    const int kvalid = min(KC, w - c * KC);
-    if constexpr (GEN) {
-        const int64_t g0 = t.row0 + t.col_begin + (int64_t)c * KC;   // global Omega row of local 0
-        const int64_t q_lo = g0 >> 2;
-        const int nq = (int)(((g0 + KC - 1) >> 2) - q_lo + 1);        // KC/4, or one more if unaligned
-        for (int it = start; it < nq * kb; it += TH) {
-            const int qi = it / kb;
-            const int n = it - qi * kb;
-            const float4 z = omega4_dist((uint64_t)(q_lo + qi), t.col0 + (uint32_t)(t.n_base + n),
-                                         t.key0, t.key1, t.dist);
-            const int kl0 = (int)(4 * (q_lo + qi) - g0);
-            if (kl0 >= 0 && (kl0 & 3) == 0 && kl0 + 3 < kvalid) {
-                *reinterpret_cast<float4*>(&om[n][kl0]) = z;
-            } else {
-                const float zz[4] = {z.x, z.y, z.z, z.w};
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int kl = kl0 + u;
-                    if (kl >= 0 && kl < KC) om[n][kl] = (kl < kvalid) ? zz[u] : 0.0f;
-                }
-            }
-        }
-    } else {
-        for (int it = start; it < KC * kb; it += TH) {
-            const int kl = it / kb;
-            const int n = it - kl * kb;
-            om[n][kl] = (kl < kvalid)
-                            ? t.omega[(t.col_begin + (int64_t)c * KC + kl) * t.ldo + t.n_base + n]
-                            : 0.0f;
-        }
-    }
-}
 
 template <int W, int TM, bool GEN, bool FULL>
 __device__ __forceinline__ void mfma_tile_f32(const MTile& t, F32Lds<tile_group(1, W, TM)>& L) {
@@ -762,8 +819,11 @@ __device__ __forceinline__ void mfma_tile_f32(const MTile& t, F32Lds<tile_group(
 // so waiting for it leaves those in flight.
 template <int NT, int G>
 struct SplitLds {
-    _Float16 om[2 * G][16 * NT][kSplitRow];
-    int ecol[16 * NT];
+    union {
+        _Float16 om[2 * G][16 * NT][kSplitRow];
+        float f32[2][16 * NT][kF32Row];
+    };
+    int f32col[16 * NT];           // of a stored Omega, see stored_columns
 };
 
 template <int NT, int W, int TM, bool GEN, bool FULL = false, bool PK = false>
@@ -774,7 +834,7 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT, tile_grou
     constexpr int KC = kSplitKC;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4;      // contraction group of the lane (both operands)
     const int i16 = lane & 15;    // A row / sketch column within a tile
     _Float16 (*om)[BN][kSplitRow] = L.om;
@@ -788,11 +848,18 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT, tile_grou
 
     const ALoads<TM, FULL> A(t, row_base, g, i16, w);
 
+    // the tile has nothing for the FP16 terms (uniform across the workgroup)
+    bool f32_all = w < KC;
+    if (stored && !f32_all) {
+        stored_columns<BN, TH, PK>(t, L.f32col, w, kb);
+        bool other = false;
+        for (int n = lane; n < kb; n += 64) other = other || L.f32col[n] == kOther;
+        f32_all = __any(other);                      // alike in every wave
+    }
+
     // ---- Omega chunk -> LDS ----------------------------------------------------------
-    if constexpr (!PK) omega_zero_pad<BN, TH>(om, 2 * G, kb);
-    if (stored) omega_exponents<BN, TH, PK>(t, L.ecol, w, kb);
     auto make_group = [&](int c) {
-        omega_group<BN, TH, G, GEN>(t, om, c & (2 * G - 1), c, nchunks, w, kb, L.ecol);
+        omega_group<BN, TH, G, GEN>(t, om, c & (2 * G - 1), c, nchunks, w, kb);
     };
     // packed route: 16-byte pieces of the tile's run of a chunk, OPT per thread;
     // chunk indices past the last are clamped (a re-read of valid memory whose
@@ -811,9 +878,7 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT, tile_grou
 #pragma unroll
         for (int j = 0; j < OPT; ++j) {
             const int p = tid + j * TH;
-            const int n = p / (KC / 4);
-            const float sc = stored ? __builtin_ldexpf(1.0f, kOmegaExp - L.ecol[n]) : 0x1p13f;
-            split_store4(om[buf][n], (p % (KC / 4)) * 4, r[j], sc);
+            split_store4(om[buf][p / (KC / 4)], (p % (KC / 4)) * 4, r[j], 0x1p13f);
         }
     };
 
@@ -881,44 +946,47 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT, tile_grou
         }
     };
 
-    v4f r0[TM][2], r1[TM][2];
-    v4f orr[PK ? OPT : 1];
-    if constexpr (PK) {
-        om_load(orr, 0);
-        A.load(r0, 0);
-        om_store(orr, 0);
-        om_load(orr, 1);
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (!single_a(NT, TM)) A.load(r1, 1);
-    } else {
-        A.load(r0, 0);
-        if constexpr (!single_a(NT, TM)) A.load(r1, 1);
-        make_group(0);
-    }
-    lds_barrier_m();
-
-    // step c: chunk c + 1's Omega to LDS, chunk c's A split, its registers refilled,
-    // chunk c's MFMAs
-    auto step = [&](v4f (*r)[2], int c) {
+    if (!f32_all) {
+        if constexpr (!PK) omega_zero_pad<BN, TH>(om, 2 * G, kb);
+        v4f r0[TM][2], r1[TM][2];
+        v4f orr[PK ? OPT : 1];
         if constexpr (PK) {
-            om_store(orr, c + 1);
-            om_load(orr, c + 2);
+            om_load(orr, 0);
+            A.load(r0, 0);
+            om_store(orr, 0);
+            om_load(orr, 1);
             __builtin_amdgcn_sched_barrier(0);
+            if constexpr (!single_a(NT, TM)) A.load(r1, 1);
         } else {
-            if (c % G == 0 && c + G < nchunks) make_group(c + G);
+            A.load(r0, 0);
+            if constexpr (!single_a(NT, TM)) A.load(r1, 1);
+            make_group(0);
         }
-        split(r);
-        A.load(r, c + (single_a(NT, TM) ? 1 : 2));
-        if constexpr (FULL) __builtin_amdgcn_sched_barrier(0);
-        compute(c);
-        if (c % G == G - 1) lds_barrier_m();
-    };
-    if constexpr (single_a(NT, TM)) {
-        for (int c = 0; c < nchunks; ++c) step(r0, c);
-    } else {
-        for (int c = 0; c < nchunks; c += 2) {
-            step(r0, c);
-            if (c + 1 < nchunks) step(r1, c + 1);
+        lds_barrier_m();
+
+        // step c: chunk c + 1's Omega to LDS, chunk c's A split, its registers refilled,
+        // chunk c's MFMAs
+        auto step = [&](v4f (*r)[2], int c) {
+            if constexpr (PK) {
+                om_store(orr, c + 1);
+                om_load(orr, c + 2);
+                __builtin_amdgcn_sched_barrier(0);
+            } else {
+                if (c % G == 0 && c + G < nchunks) make_group(c + G);
+            }
+            split(r);
+            A.load(r, c + (single_a(NT, TM) ? 1 : 2));
+            if constexpr (FULL) __builtin_amdgcn_sched_barrier(0);
+            compute(c);
+            if (c % G == G - 1) lds_barrier_m();
+        };
+        if constexpr (single_a(NT, TM)) {
+            for (int c = 0; c < nchunks; ++c) step(r0, c);
+        } else {
+            for (int c = 0; c < nchunks; c += 2) {
+                step(r0, c);
+                if (c + 1 < nchunks) step(r1, c + 1);
+            }
         }
     }
 
@@ -932,24 +1000,25 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT, tile_grou
     o.y_trans = 0;
     o.y_f64 = t.y_f64;
     o.beta = t.beta;
+    const bool vec = o.vec();
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
         const int64_t row = row_base + tm * 16 + i16;
-        if (row >= t.m || inf[tm]) continue;
+        if (f32_all || row >= t.m || inf[tm]) continue;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
-            emit4(o, row, n_base + nt * 16 + 4 * g, n_base + kb, acc[tm][nt], s[tm],
-                  stored ? &L.ecol[nt * 16 + 4 * g] : nullptr);
+            emit_split(o, vec, row, n_base + nt * 16 + 4 * g, n_base + kb, acc[tm][nt], s[tm],
+                       stored ? &L.f32col[nt * 16 + 4 * g] : nullptr);
     }
-    // ---- non-finite entries, with FP32 products ---------------------------------------
-    bool redo = false;
+    // ---- rows and columns for FP32 products --------------------------------------------
+    bool redo = f32_all;
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) redo = redo || inf[tm];
     if (stored)
-        for (int n = lane; n < kb; n += 64) redo = redo || L.ecol[n] == kBadCol;
-    if (__any(redo)) {
-        f32_sums<NT, TM, GEN, PK>(
-            t, o, nchunks, w, kb, g, i16,
+        for (int n = lane; n < kb; n += 64) redo = redo || L.f32col[n];
+    if (__syncthreads_or(redo)) {
+        f32_sums<NT, TM, TH, GEN, PK>(
+            t, o, &L.f32[0][0][0], w, kb, true,
             [&](float (&x)[TM][8], int c) {
                 v4f r[TM][2];
                 A.load(r, c);
@@ -958,8 +1027,8 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT, tile_grou
 #pragma unroll
                     for (int e = 0; e < 8; ++e) x[tm][e] = r[tm][e >> 2][e & 3];
             },
-            [&](int tm) { return row_base + tm * 16 + i16; },
-            [&](int tm, int c) { return inf[tm] || (stored && L.ecol[c] == kBadCol); });
+            [&](int tm) { return row_base + tm * 16 + i16; }, f32_all, inf,
+            stored ? L.f32col : nullptr);
     }
 }
 
@@ -1239,23 +1308,6 @@ __global__ __launch_bounds__(kThreads) void k_gemm_cm_mfma(const CmMArgs a) {
         inf[q] = false;
     }
 
-    v4f x0[kNS], x1[kNS];
-    v4f orr[PK ? OPT : 1];
-    if constexpr (PK) {
-        static_assert(!PK || kG == 1, "one chunk per barrier on the packed route");
-        om_load(orr, 0);
-        load_a(x0, 0);
-        om_store(orr, 0);
-        om_load(orr, 1);
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (!single_a(NT)) load_a(x1, 1);
-    } else {
-        load_a(x0, 0);
-        if constexpr (!single_a(NT)) load_a(x1, 1);
-        omega_group<BN, kThreads, kG, true>(t, om, 0, 0, nchunks, w, kb, nullptr);
-    }
-    lds_barrier_m();
-
     // a cut group's rows, loaded as the last four
     auto shift_cut = [&](v4f* x) {
         if constexpr (FULL && !ROWS4) {
@@ -1329,78 +1381,97 @@ __global__ __launch_bounds__(kThreads) void k_gemm_cm_mfma(const CmMArgs a) {
         }
     };
 
-    if constexpr (PK) {
-        // the order of mfma_tile's packed loop
-        auto step = [&](v4f* x, int c) {
-            om_store(orr, (c + 1) & 1);
-            om_load(orr, c + 2);
+    const bool f32_all = w < kKC;             // see f32_sums
+    if (!f32_all) {
+        v4f x0[kNS], x1[kNS];
+        v4f orr[PK ? OPT : 1];
+        if constexpr (PK) {
+            static_assert(!PK || kG == 1, "one chunk per barrier on the packed route");
+            om_load(orr, 0);
+            load_a(x0, 0);
+            om_store(orr, 0);
+            om_load(orr, 1);
             __builtin_amdgcn_sched_barrier(0);
-            consume(x, c, c & 1);
-            lds_barrier_m();
-        };
-        if constexpr (single_a(NT)) {
-            for (int c = 0; c < nchunks; ++c) step(x0, c);
+            if constexpr (!single_a(NT)) load_a(x1, 1);
         } else {
-            for (int c = 0; c < nchunks; c += 2) {
-                step(x0, c);
-                if (c + 1 < nchunks) step(x1, c + 1);
+            load_a(x0, 0);
+            if constexpr (!single_a(NT)) load_a(x1, 1);
+            omega_group<BN, kThreads, kG, true>(t, om, 0, 0, nchunks, w, kb);
+        }
+        lds_barrier_m();
+
+        if constexpr (PK) {
+            // the order of mfma_tile's packed loop
+            auto step = [&](v4f* x, int c) {
+                om_store(orr, (c + 1) & 1);
+                om_load(orr, c + 2);
+                __builtin_amdgcn_sched_barrier(0);
+                consume(x, c, c & 1);
+                lds_barrier_m();
+            };
+            if constexpr (single_a(NT)) {
+                for (int c = 0; c < nchunks; ++c) step(x0, c);
+            } else {
+                for (int c = 0; c < nchunks; c += 2) {
+                    step(x0, c);
+                    if (c + 1 < nchunks) step(x1, c + 1);
+                }
             }
-        }
-    } else if constexpr (single_a(NT)) {
-        for (int c = 0; c < nchunks; ++c) {
-            if (c + 1 < nchunks)
-                omega_group<BN, kThreads, 1, true>(t, om, (c + 1) & 1, c + 1, nchunks, w, kb, nullptr);
-            consume(x0, c, c & 1);
-            lds_barrier_m();
-        }
-    } else if constexpr (kG == 1) {
-        for (int c = 0; c < nchunks; c += 2) {
-            if (c + 1 < nchunks)
-                omega_group<BN, kThreads, 1, true>(t, om, 1, c + 1, nchunks, w, kb, nullptr);
-            consume(x0, c, 0);
-            lds_barrier_m();
-            if (c + 1 < nchunks) {
-                if (c + 2 < nchunks)
-                    omega_group<BN, kThreads, 1, true>(t, om, 0, c + 2, nchunks, w, kb, nullptr);
-                consume(x1, c + 1, 1);
+        } else if constexpr (single_a(NT)) {
+            for (int c = 0; c < nchunks; ++c) {
+                if (c + 1 < nchunks)
+                    omega_group<BN, kThreads, 1, true>(t, om, (c + 1) & 1, c + 1, nchunks, w, kb);
+                consume(x0, c, c & 1);
+                lds_barrier_m();
+            }
+        } else if constexpr (kG == 1) {
+            for (int c = 0; c < nchunks; c += 2) {
+                if (c + 1 < nchunks)
+                    omega_group<BN, kThreads, 1, true>(t, om, 1, c + 1, nchunks, w, kb);
+                consume(x0, c, 0);
+                lds_barrier_m();
+                if (c + 1 < nchunks) {
+                    if (c + 2 < nchunks)
+                        omega_group<BN, kThreads, 1, true>(t, om, 0, c + 2, nchunks, w, kb);
+                    consume(x1, c + 1, 1);
+                    lds_barrier_m();
+                }
+            }
+        } else {
+            // group u of kG chunks sits in slots (u & 1) kG ..; the next group is generated
+            // into the other half while this one is consumed, one barrier per group
+            for (int cb = 0; cb < nchunks; cb += kG) {
+                const int half = (cb / kG) & 1;
+                if (cb + kG < nchunks)
+                    omega_group<BN, kThreads, kG, true>(t, om, (half ^ 1) * kG, cb + kG, nchunks, w, kb);
+#pragma unroll
+                for (int i = 0; i < kG; i += 2) {
+                    if (cb + i < nchunks) consume(x0, cb + i, half * kG + i);
+                    if (cb + i + 1 < nchunks) consume(x1, cb + i + 1, half * kG + i + 1);
+                }
                 lds_barrier_m();
             }
         }
-    } else {
-        // group u of kG chunks sits in slots (u & 1) kG ..; the next group is generated
-        // into the other half while this one is consumed, one barrier per group
-        for (int cb = 0; cb < nchunks; cb += kG) {
-            const int half = (cb / kG) & 1;
-            if (cb + kG < nchunks)
-                omega_group<BN, kThreads, kG, true>(t, om, (half ^ 1) * kG, cb + kG, nchunks, w, kb,
-                                                    nullptr);
-#pragma unroll
-            for (int i = 0; i < kG; i += 2) {
-                if (cb + i < nchunks) consume(x0, cb + i, half * kG + i);
-                if (cb + i + 1 < nchunks) consume(x1, cb + i + 1, half * kG + i + 1);
-            }
-            lds_barrier_m();
-        }
     }
-    if (!active) return;
-
     // ---- lane l holds Y^T rows (sketch columns) 4g .. 4g + 3 of column j of each
     // accumulator tile: Y[rl + q][n_base + 16 nt + 4g + r] = acc[q][nt][r] ---------------
     const TileOut o = cm_out(a, strip);
+    const bool vec = o.vec();
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        if (rl + q >= a.m || inf[q]) continue;
+        if (f32_all || rl + q >= a.m || inf[q]) continue;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
-            emit4(o, rl + q, t.n_base + nt * 16 + 4 * g, t.n_base + kb, acc[q][nt], sc[q], nullptr);
+            emit_split(o, vec, rl + q, t.n_base + nt * 16 + 4 * g, t.n_base + kb, acc[q][nt], sc[q],
+                       nullptr);
     }
-    if (__any(inf[0] || inf[1] || inf[2] || inf[3])) {
+    if (__syncthreads_or(f32_all || inf[0] || inf[1] || inf[2] || inf[3])) {
         t.strip = strip;
         t.m = a.m;
         t.kpad = a.kpad;
         t.fpack = a.fpack;
-        f32_sums<NT, 4, true, PK>(
-            t, o, nchunks, w, kb, g, j,
+        f32_sums<NT, 4, kThreads, true, PK>(
+            t, o, reinterpret_cast<float*>(&om[0][0][0]), w, kb, active,
             [&](float (&x)[4][8], int c) {
                 v4f r[kNS];
                 load_a(r, c);
@@ -1410,7 +1481,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_cm_mfma(const CmMArgs a) {
 #pragma unroll
                     for (int e = 0; e < 8; ++e) x[q][e] = r[e][q];
             },
-            [&](int q) { return rl + q; }, [&](int q, int) { return inf[q]; });
+            [&](int q) { return rl + q; }, f32_all, inf, nullptr);
     }
 }
 
@@ -1565,6 +1636,7 @@ __global__ __launch_bounds__(kSkThreads) void k_gemm_cm_mfma_skinny(const CmMArg
         }
     };
 
+    const bool f32_all = w < kKC;             // see f32_sums; the strip's only chunk
     v4f ra[kAPieces], ro[kOPieces], rb[kAPieces], rbo[kOPieces];
     if (gen_wave) {
         g_load(0, ra, ro);
@@ -1587,22 +1659,21 @@ __global__ __launch_bounds__(kSkThreads) void k_gemm_cm_mfma_skinny(const CmMArg
         iter(gi, ra, ro, rb, rbo);
         if (gi + 1 < ngroups) iter(gi + 1, rb, rbo, ra, ro);
     }
-    if (gen_wave) return;
-
-    // lane (g, j) holds Y^T rows (sketch columns) 4g .. 4g + 3 of column j of the tile:
-    // Y[rl + q][n_base + 4g + r] = acc[r]
+    // lane (g, j) of a chain holds Y^T rows (sketch columns) 4g .. 4g + 3 of column j of
+    // the tile: Y[rl + q][n_base + 4g + r] = acc[r]
     const TileOut o = cm_out(a, strip);
     const int64_t row = rl + q;
-    if (row < a.m && !inf) emit4(o, row, n_base + 4 * g, n_base + kb, acc, sc, nullptr);
-    if (__any(inf)) {
+    if (!gen_wave && row < a.m && !inf && !f32_all)
+        emit_split(o, o.vec(), row, n_base + 4 * g, n_base + kb, acc, sc, nullptr);
+    if (__syncthreads_or(!gen_wave && (f32_all || inf))) {
         MTile t{};
         t.m = a.m;
         t.n_base = n_base;
         t.strip = strip;
         t.kpad = a.kpad;
         t.fpack = a.fpack;
-        f32_sums<1, 1, true, true>(
-            t, o, nchunks, w, kb, g, j,
+        f32_sums<1, 1, kSkThreads, true, true>(
+            t, o, reinterpret_cast<float*>(&om[0][0][0]), w, kb, !gen_wave,
             [&](float (&x)[1][8], int c) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
@@ -1610,7 +1681,7 @@ __global__ __launch_bounds__(kSkThreads) void k_gemm_cm_mfma_skinny(const CmMArg
                     x[0][e] = kl < w && row < a.m ? a.A[(col_begin + kl) * a.lda + row] : 0.0f;
                 }
             },
-            [&](int) { return row; }, [&](int, int) { return inf; });
+            [&](int) { return row; }, f32_all, {inf}, nullptr);
     }
 }
 

@@ -4,12 +4,17 @@
 // v_mfma_f32_16x16x32_f16, so the wide FP32 sketches write both operands as sums of
 // FP16 numbers and multiply those (every FP16 x FP16 product is exact, sums
 // are FP32):
-//   Omega: y = omega 2^(13 - ecol), b0 = fp16(y), b1 = fp16((y - b0) 2^11), b2 the
-//     rest of (y - b0) 2^11: three terms hold the 24 significant bits exactly;
+//   Omega: y = omega 2^13, b0 = fp16(y), b1 = fp16((y - b0) 2^11), b2 the rest of
+//     (y - b0) 2^11: three terms hold the 24 significant bits exactly for |omega| >= 2^-25
+//     and to within 2^-49 below;
 //   A: x = a s with s a power of two, a0 = fp16(x), a1 = fp16(x - a0): 22 to 24
 //     significant bits (|x - a0 - a1| <= 2^-23 |x|, at least 2^-25);
-//   A Omega s 2^(13 - ecol) = sum a1 b0 + (a0 2^-11) b2 + (a0 2^-11) b1 + a0 b0, the
+//   A Omega s 2^13 = sum a1 b0 + (a0 2^-11) b2 + (a0 2^-11) b1 + a0 b0, the
 //     dropped a1 (b1 + b2) being at most 2^-22 of each product, of either sign.
+// So a strip sum is within 2^-21 sum |a omega| + 2^-35 max|a| sum |omega| + 2^-49 sum |a| of
+// the products' sum, besides the rounding of the additions.  The last two terms matter only
+// where Omega brings out a row's small entries; a stored Omega that could is multiplied by
+// the FP32 instruction instead (stored_columns), and so are strips narrower than a chunk.
 // Relative Frobenius error against FP64 (N(0,1) A, 16384 to 32768 columns): 5.2e-7 to
 // 5.4e-7, against 8.1e-7 of the FP32 instruction's chain of 512 additions per strip.
 // Time, k = 64 on 65536 x 16384: 850 us against 1237; k = 256 on 32768^2: 2.23 ms
@@ -48,7 +53,7 @@ constexpr float kRowStart = 0x1p127f;   // scale of a row that has been zero so 
 // 2 mod 4 16-byte units, measured; at 13 units k = 256 on 32768^2 took 0.4% longer)
 constexpr int kSplitRow = 3 * kSplitKC + 16;
 
-// Omega value -> (b0, b1, b2); sc = 2^(kOmegaExp - ecol).
+// Omega value -> (b0, b1, b2); sc = 2^kOmegaExp.
 __device__ __forceinline__ void split_omega(float z, float sc, _Float16& b0, _Float16& b1,
                                             _Float16& b2) {
     const float y = z * sc;
@@ -138,10 +143,10 @@ __device__ __forceinline__ f32x4 split_mfma(const h8 b0, const h8 b1, const h8 b
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(b0, a0, acc, 0, 0, 0);
 }
 
-// Sum of a row with scale s and a sketch column with exponent ecol -> its value.
-__device__ __forceinline__ float unscale(float v, float s, int ecol) {
+// Sum of a row with scale s -> its value.
+__device__ __forceinline__ float unscale(float v, float s) {
     const int es = (int)(__float_as_uint(s) >> 23) - 127;
-    return __builtin_ldexpf(v, ecol - kOmegaExp - es);
+    return __builtin_ldexpf(v, -kOmegaExp - es);
 }
 
 }  // namespace sk

@@ -248,3 +248,81 @@ def test_cost_of_infinite_rows():
         for kk in (24, k):
             clean, inf = ms(lambda: f(x, 3, kk)), ms(lambda: f(y, 3, kk))
             assert inf <= 16 * clean, (f.__name__, kk, clean, inf)
+
+
+def selecting_omega(n, k, seed):
+    """Columns that pick out few entries of a row, or span a wide range."""
+    rng = np.random.default_rng(seed)
+    Om = np.zeros((n, k))
+    for c in range(k):
+        kind = c % 6
+        if kind == 0:                                    # one entry
+            Om[rng.integers(0, n), c] = 1.0
+        elif kind == 1:                                  # sparse signs
+            Om[:, c] = rng.choice([-1.0, 0.0, 1.0], n, p=[.05, .9, .05])
+        elif kind == 2:                                  # wide range
+            Om[:, c] = rng.standard_normal(n) * np.exp2(-rng.integers(0, 60, n).astype(float))
+        elif kind == 3:                                  # one outlier
+            Om[:, c] = rng.standard_normal(n)
+            Om[0, c] = 1e20
+        elif kind == 4:                                  # small everywhere, or large
+            Om[:, c] = rng.standard_normal(n) * (1e-12 if c % 4 else 1e5)
+        else:
+            Om[:, c] = rng.standard_normal(n)
+    return Om.astype(np.float32)
+
+
+@pytest.mark.parametrize("m,n,k", [(70, 4500, 24), (70, 2048, 64), (530, 2100, 130), (65, 40, 40)])
+def test_stored_omega_that_selects_entries(m, n, k):
+    """FP32 products for columns of a stored Omega that bring out single entries of rows of a
+    wide range: the bound of a chain of FP32 additions, with nothing for the terms."""
+    rng = np.random.default_rng(n)
+    A = normal_matrix(m, n, seed=k).astype(np.float64)
+    A[:m // 2] *= np.exp2(-rng.integers(0, 90, (m // 2, n)).astype(float))
+    A[0, :3], A[0, 3:] = (1e12, 1.0009765, np.pi), 0.0
+    A[:, 0] = np.where(np.arange(m) % 2, 0.0, A[:, 0])
+    A[1, :] = np.abs(A[1, :]) * 1e-3
+    A[1, n - 1] = 1e9
+    A = A.astype(np.float32)
+    Om = selecting_omega(n, k, seed=m)
+    Om[:, 6], Om[1, 6] = 0.0, 1.0
+    Om[:, 12], Om[2, 12] = 0.0, 1.0
+    Y = sk.sketch_matmul_omega(to_dev(A), torch.from_numpy(Om).to(DEV), y_dtype=torch.float64).cpu().numpy()
+    ref = A.astype(np.float64) @ Om.astype(np.float64)
+    mag = np.abs(A).astype(np.float64) @ np.abs(Om).astype(np.float64)
+    sel = [c for c in range(k) if c % 6 != 5]            # the others are like generated ones
+    assert (np.abs(Y - ref) <= 2052 * U * mag + U * np.abs(ref) + 2.0 ** -140)[:, sel].all()
+    assert Y[0, 6] == A[0, 1] and Y[0, 12] == A[0, 2]
+    bound = 2052 * U * mag + 2.0 ** -35 * np.abs(A).max(1)[:, None] * np.abs(Om).astype(np.float64).sum(0)
+    bound += 2.0 ** -49 * np.abs(A).astype(np.float64).sum(1)[:, None]
+    assert (np.abs(Y - ref) <= bound + U * np.abs(ref)).all()
+
+
+@pytest.mark.parametrize("n", [1, 5, 31, 2048 + 3])
+@pytest.mark.parametrize("k", [17, 40, 130])
+def test_narrow_strips_are_fp32_sums(n, k):
+    """Strips narrower than a chunk: at most 32 FP32 roundings of the products' sum (the first
+    2048 columns of the last n are zero), the same bits on every route."""
+    m, w = 80, n % 2048
+    A = normal_matrix(m, n, seed=n)
+    A[:, :n - w] = 0.0
+    Ad = to_dev(A)
+    Y = sk.sketch_gen_matmul(Ad, 3, k, y_dtype=torch.float64)
+    Om = oracle.omega_block(3, 0, n, 0, k)
+    ref = A.astype(np.float64) @ Om.astype(np.float64)
+    mag = np.abs(A).astype(np.float64) @ np.abs(Om).astype(np.float64)
+    assert (np.abs(Y.cpu().numpy() - ref) <= (w + 1) * U * mag).all()
+    Y = Y.float()
+    assert torch.equal(Y, served(Ad, 3, k))
+    assert torch.equal(Y, sk.sketch_gen_matmul_cm(cm_dev(A), 3, k))
+    assert torch.equal(Y[:40], sk.sketch_gen_matmul_cm(cm_dev(A)[:40], 3, k))
+    assert torch.equal(Y[:3], sk.sketch_gen_matmul_cm(cm_dev(A)[:3], 3, k))
+    assert torch.equal(Y, sk.sketch_matmul_omega(Ad, torch.from_numpy(Om).to(DEV)))
+
+
+@pytest.mark.parametrize("dist", ["normal", "uniform", "rademacher"])
+@pytest.mark.parametrize("n,k", [(32, 24), (33, 64), (4101, 130)])
+def test_stored_copy_has_the_generated_bits(n, k, dist):
+    A = to_dev(normal_matrix(70, n, seed=4))
+    Om = sk.sketch_gen_omega(9, 0, n, 0, k, dist=dist)
+    assert torch.equal(sk.sketch_matmul_omega(A, Om), sk.sketch_gen_matmul(A, 9, k, dist=dist))
