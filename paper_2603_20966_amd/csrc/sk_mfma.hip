@@ -718,6 +718,7 @@ struct ALoads {
                 for (int v = 0; v < 2; ++v) a[tm][v] = *reinterpret_cast<const v4f*>(p + 16 * v);
             }
             if (c != nfull) return;
+            asm volatile("" : "+s"(c));    // the tail's addresses are formed here, not kept
         }
         const int kl = c * KC + 8 * g;                      // strip column of component 0
         if (c * KC >= w) return;
@@ -869,9 +870,13 @@ __device__ __forceinline__ void mfma_tile(const MTile& t, SplitLds<NT, tile_grou
     static_assert(!PK || PPL % TH == 0, "whole pieces per thread");
     auto om_load = [&](v4f* r, int c) {
         const int cc = c < nchunks ? c : nchunks - 1;
-        const float* src = t.fpack + ((t.strip * (kMfmaStrip / KC) + cc) * t.kpad + n_base) * KC;
+        const char* src = reinterpret_cast<const char*>(
+            t.fpack + ((t.strip * (kMfmaStrip / KC) + cc) * t.kpad + n_base) * KC);
+        // a scalar base and 32-bit lane offsets: a 64-bit base per lane was spilled in the
+        // eight-N-tile loop, and its reload waited for the A loads in flight
 #pragma unroll
-        for (int j = 0; j < OPT; ++j) r[j] = *reinterpret_cast<const v4f*>(src + 4 * (tid + j * TH));
+        for (int j = 0; j < OPT; ++j)
+            r[j] = *reinterpret_cast<const v4f*>(src + 16u * (uint32_t)(tid + j * TH));
     };
     auto om_store = [&](const v4f* r, int c) {
         const int buf = c & 1;
@@ -1220,7 +1225,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_cm_mfma(const CmMArgs a) {
     t.dist = a.dist;
 
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4;
     const int j = lane & 15;
     const int w = (int)min<int64_t>(kMfmaStrip, a.n - t.col_begin);
@@ -1245,6 +1250,7 @@ __global__ __launch_bounds__(kThreads) void k_gemm_cm_mfma(const CmMArgs a) {
             for (int s = 0; s < kNS; ++s)
                 x[s] = *reinterpret_cast<const v4f_a4*>(acol + (int64_t)(cc * kKC + s) * a.lda);
             if (c != nfull || nfull == nchunks) return;
+            asm volatile("" : "+s"(c));    // as ALoads
 #pragma unroll
             for (int s = 0; s < kNS; ++s) {
                 v4f v = {0.f, 0.f, 0.f, 0.f};
@@ -1373,16 +1379,38 @@ __global__ __launch_bounds__(kThreads) void k_gemm_cm_mfma(const CmMArgs a) {
     };
     // chunk c: its A split, its registers refilled, its MFMAs
     auto consume = [&](v4f* x, int c, int slot) {
-        if (FULL || active) {
-            split(x);
-            load_a(x, c + (single_a(NT) ? 1 : 2));
-            if constexpr (FULL) __builtin_amdgcn_sched_barrier(0);
-            compute(slot);
-        }
+        split(x);
+        load_a(x, c + (single_a(NT) ? 1 : 2));
+        if constexpr (FULL) __builtin_amdgcn_sched_barrier(0);
+        compute(slot);
     };
 
     const bool f32_all = w < kKC;             // see f32_sums
-    if (!f32_all) {
+    if (!f32_all && !active) {
+        // a wave without rows forms its share of Omega and leaves the units to the others
+        // (at 65 .. 448 rows it would take as long as they do: tmatmul of 65536 x 80 81 us)
+        if constexpr (PK) {
+            v4f orr[OPT];
+            om_load(orr, 0);
+            om_store(orr, 0);
+            om_load(orr, 1);
+            lds_barrier_m();
+            for (int c = 0; c < nchunks; ++c) {
+                om_store(orr, (c + 1) & 1);
+                om_load(orr, c + 2);
+                lds_barrier_m();
+            }
+        } else {
+            omega_group<BN, kThreads, kG, true>(t, om, 0, 0, nchunks, w, kb);
+            lds_barrier_m();
+            for (int cb = 0; cb < nchunks; cb += kG) {
+                if (cb + kG < nchunks)
+                    omega_group<BN, kThreads, kG, true>(t, om, ((cb / kG) & 1 ? 0 : kG), cb + kG,
+                                                        nchunks, w, kb);
+                lds_barrier_m();
+            }
+        }
+    } else if (!f32_all) {
         v4f x0[kNS], x1[kNS];
         v4f orr[PK ? OPT : 1];
         if constexpr (PK) {

@@ -158,3 +158,27 @@ def test_few_row_kernels_equal_tall_rows(p, k):
     Ys2 = sk.sketch_gen_matmul_cm(Ad[r0:r0 + p], 9, k, omega_row0=2, y_trans=True)
     assert torch.equal(Ys2.t(), Yt[r0:r0 + p])
     check(Ys.double().cpu().numpy(), A[:p], 9, 2, 0, k)
+
+
+def test_waves_without_rows_cost_little():
+    """80 rows occupy two of a tile's eight waves: the call has as many tiles and chunks as at
+    512 rows and has to be clearly faster (both took the same time while every wave did the
+    work of one with rows)."""
+    n, k = 32768, 80
+
+    def ms(m):
+        A = torch.empty((n, m), device=DEV).normal_().t()
+        Y = torch.empty((m, k), device=DEV)
+        times = []
+        for _ in range(6):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(10):
+                sk.sketch_gen_matmul_cm(A, 3, k, Y=Y)
+            e1.record()
+            torch.cuda.synchronize()
+            times.append(e0.elapsed_time(e1))
+        return min(times)
+
+    few, full = ms(80), ms(512)
+    assert few <= 0.9 * full, (few, full)
