@@ -2278,14 +2278,21 @@ hipError_t launch_m_tile(const MArgs& args, hipStream_t s) {
 
 template <int NT, bool GEN>
 hipError_t launch_m(int rows, const MArgs& a, hipStream_t s) {
-    bool full = true, whole = true;
+    bool full = true, whole = true, lines = true;
     for (int b = 0; b < a.P; ++b) {
+        lines = lines && a.blk[b].lda % 32 == 0 && ((uintptr_t)a.blk[b].A & 127) == 0;
         full = full && (a.blk[b].n >= kSplitKC || a.blk[b].n == 0);
         whole = whole && a.blk[b].n % kSplitKC == 0;
     }
     if (full && rows == 64) return launch_m_tile<NT, 4, 1, GEN, true>(a, s);
     if (full && rows == 128) return launch_m_tile<NT, 8, 1, GEN, true>(a, s);
-    if (full && rows == 256) return launch_m_tile<NT, 8, 2, GEN, true>(a, s);
+    // 25 to 32 columns on rows that are not whole 128-byte lines: two 256-row tiles a compute
+    // unit (120 registers) overlap one's generation with the other's twice as many line
+    // requests, one 512-row tile does not (k = 28: 40000 x 7001 448 us against 325, 60000 x
+    // 16388 925 against 881, 20000 x 9988 237 against 220; on whole lines 60000 x 16384 736
+    // against 758)
+    const bool half = NT == 2 && a.k > 24 && !lines;
+    if (full && (rows == 256 || (rows == kBM && half))) return launch_m_tile<NT, 8, 2, GEN, true>(a, s);
     // one N-tile: whole chunks only (with a ragged end the unconditional loads measured
     // 166 us against 158 for the per-lane path, 20011 x 9973 at k = 16)
     return (NT == 1 ? whole : full) ? launch_m_tile<NT, 8, 4, GEN, true>(a, s)

@@ -123,3 +123,19 @@ def test_tile_heights_give_the_same_bits(n, k):
         assert torch.equal(sk.sketch_matmul_omega(A[:rows], Om), Y[:rows]), rows
     Ah = A[:64].cpu().numpy()
     check(Y[:64], np.ascontiguousarray(Ah), 3, 1, 0, k)
+
+
+@pytest.mark.parametrize("n,ld", [(2112, 2116), (2101, 2104), (2112, 2112)])
+def test_rows_off_the_line_boundary(n, ld):
+    """25 to 32 sketch columns: 256-row tiles where rows are not whole 128-byte lines, 512-row
+    ones where they are; the same bits as at 24 + 8 columns and as a stored copy."""
+    m, k = 33000, 32
+    A = torch.empty((m, ld), device=DEV)
+    A.normal_(generator=torch.Generator(device=DEV).manual_seed(n))
+    A = A[:, :n]
+    Y = sk.sketch_gen_matmul(A, 3, k)
+    assert torch.equal(Y[:, :24], sk.sketch_gen_matmul(A, 3, 24))
+    assert torch.equal(Y[:, 8:], sk.sketch_gen_matmul(A, 3, 24, omega_col0=8))
+    assert torch.equal(Y[-100:], sk.sketch_gen_matmul(A[-100:], 3, k))
+    assert torch.equal(Y, sk.sketch_matmul_omega(A, sk.sketch_gen_omega(3, 0, n, 0, k)))
+    check(Y[:64], np.ascontiguousarray(A[:64].cpu().numpy()), 3, 0, 0, k)
