@@ -979,27 +979,36 @@ __device__ __forceinline__ void tile_mfma64(const TX* __restrict__ X, int64_t ld
     store(0);
     __syncthreads();
     int b = 0;
-    for (int64_t l0 = 0; l0 < K; l0 += kDK, b ^= 1) {
-        const bool more = l0 + kDK < K;
-        if (more) load(l0 + kDK);
+    auto multiply = [&](int kk) {
         const double* xb = &L.x[b][g][(wave >> 1) * 64 + j];
         const double* yb = &L.y[b][g][(wave & 1) * 64 + j];
+        double av[4], bv[4];
 #pragma unroll
-        for (int kk = 0; kk < kDK; kk += 4) {
-            double av[4], bv[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                av[t] = xb[kk * kDP + 16 * t];
-                bv[t] = yb[kk * kDP + 16 * t];
-            }
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    acc[a][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[c], acc[a][c], 0, 0, 0);
+        for (int t = 0; t < 4; ++t) {
+            av[t] = xb[kk * kDP + 16 * t];
+            bv[t] = yb[kk * kDP + 16 * t];
         }
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                acc[a][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[c], acc[a][c], 0, 0, 0);
+    };
+    int64_t l0 = 0;
+    for (; l0 + kDK <= K; l0 += kDK, b ^= 1) {
+        const bool more = l0 + kDK < K;
+        if (more) load(l0 + kDK);
+#pragma unroll
+        for (int kk = 0; kk < kDK; kk += 4) multiply(kk);
         if (more) store(b ^ 1);
         __syncthreads();
+    }
+    // the last values, without the zeros after them (r = 20 on n = 3001: 42.2 -> 37.2 us; a test
+    // of the end in the loop above costs 5% at r = 256)
+#pragma unroll
+    for (int kk = 0; kk < kDK; kk += 4) {
+        if (l0 + kk >= K) break;
+        multiply(kk);
     }
 }
 
@@ -1241,8 +1250,13 @@ hipError_t launch_nystrom(const float* A, int64_t lda, const float* B, int64_t n
     double* part = reinterpret_cast<double*>(pp);
     const int64_t t64 = (n + kGT - 1) / kGT;
     // the partial sums of the kDT-wide tiles leave the last 8 bytes of their area free
-    // (r < 64: the product is a small part, every tile reads its own A)
-    int* sym = A && r >= 64 ? reinterpret_cast<int*>(pp + align256((size_t)(t64 * t64) * 16) - 8)
+    // (r < 64: the product is a small part, every tile reads its own A).  Mirrored tiles pay
+    // where they save a round of tiles, two to a compute unit (r = 100: n = 3001 94 us without
+    // them and 76 with them; n = 2048, one round either way, 57.5 and 60.2; n = 4096, two rounds
+    // either way, 108 and 124)
+    const int64_t td = (n + kDT - 1) / kDT, slots = 2 * device_cus();
+    const bool pays = (td * (td + 1) / 2 + slots - 1) / slots < (td * td + slots - 1) / slots;
+    int* sym = A && r >= 64 && pays ? reinterpret_cast<int*>(pp + align256((size_t)(t64 * t64) * 16) - 8)
                             : nullptr;
     const unsigned gr = (unsigned)((r + kDT - 1) / kDT);
     const int64_t mw = A ? n : mr;

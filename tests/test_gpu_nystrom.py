@@ -248,3 +248,24 @@ def test_core_pinv_inverse_special_cores():
     Cp, info = sk.sketch_core_pinv(torch.from_numpy(P).to(DEV), TOL)
     assert info.cpu().tolist()[0] >= 1
     assert np.abs(Cp.cpu().numpy() - P).max() <= 64 * 32 * U64
+
+
+@pytest.mark.parametrize("n,r", [(3001, 64), (2900, 100)])
+def test_mirrored_error_tiles(n, r):
+    """Sizes whose symmetric tiles save a round of tiles (two to a compute unit): the sums of a
+    bitwise symmetric C^+ against the FP64 formula, and against those of a C^+ that is not (one
+    entry off by one unit), within the rounding of FP64 sums."""
+    g = torch.Generator(device=DEV).manual_seed(n)
+    A = torch.randn((n, (n + 3) // 4 * 4), generator=g, device=DEV)[:, :n]
+    B = torch.randn((n, (r + 3) // 4 * 4), generator=g, device=DEV)[:, :r]
+    Cp = torch.randn((r, r), generator=g, device=DEV, dtype=torch.float64)
+    Cp = Cp + Cp.t()
+    got = sk.sketch_nystrom_error(A, B, Cp).cpu().numpy()
+    W = B.double() @ Cp
+    D = A.double() - W @ B.double().t().contiguous()
+    want = np.array([float((D * D).sum()), float((A.double() ** 2).sum())])
+    assert np.abs(got[:2] / want - 1).max() <= 1e-11
+    Cu = Cp.clone()
+    Cu[0, 1] = torch.nextafter(Cu[0, 1], Cu[0, 1] + 1)
+    other = sk.sketch_nystrom_error(A, B, Cu).cpu().numpy()
+    assert np.abs(got / other - 1).max() <= 1e-11
