@@ -643,12 +643,15 @@ __device__ __forceinline__ void tile_accumulate(const TX* __restrict__ X, int64_
 // r = 24 takes 80 us against 259, r = 64 85 against 814, r = 256 214 against 3618 and
 // r = 500 (whose idle sweeps stay separate launches) 1.8 ms against 8.3; a core that needs
 // the sweeps pays for the attempt, 15 us at r = 24 to 300 us at r = 500 (3 to 6%).  X = S^-1 by a block Gauss-Jordan
-// elimination without pivoting, R = I - S X, and the certificate
-//     ||R||_F <= 2^-24   and   tol ||S||_F ||X||_F < 1 / 1.01
-// (then min|lambda| >= (1 - ||R||) / ||X||_F > tol ||S||_F >= tol max|lambda|), after which
-// X + X R is the inverse to FP64 rounding.  A singular, badly scaled or unluckily
-// indefinite S fails it (NaN included), and the sweeps run as they do when the caller asks
-// for the eigenvalues.
+// elimination without pivoting, R = I - S X as computed, and the certificate
+//     ||R||_F <= 2^-24,  rho = ||R||_F + (r + 2) u ||S||_F ||X||_F < 1/2  (u = 2^-53)
+//     and  1.01 tol ||S||_F ||X||_F < 1 - rho.
+// rho bounds the exact residual (the middle term is the rounding of R), so S is not
+// singular, min|lambda| >= (1 - rho) / ||X||_F > tol ||S||_F >= tol max|lambda|, and no
+// eigenvalue is cut; 1.01 covers the rounding of the norms.  X + X R then has a residual of
+// at most ||R||^2 <= 2^-48 besides rounding of order r u ||S|| ||X||, as any inverse.  A
+// singular, badly scaled or unluckily indefinite S fails it (NaN included), and the sweeps
+// run as they do when the caller asks for the eigenvalues.
 
 // Element (i, j) of a matrix of r x r, continued by the identity.
 struct Padded {
@@ -834,7 +837,9 @@ __global__ __launch_bounds__(kJThreads) void k_inv_finish(const Padded X, const 
 #pragma unroll
     for (int c = 0; c < 3; ++c) q[c] = block_sum1(q[c], red);
     const int64_t i = (int64_t)bi * kJT + ti, j0 = (int64_t)bj * kJT + 4 * tj;
-    if (!(q[0] <= 0x1p-48 && tol * sqrt(q[1]) * sqrt(q[2]) * 1.01 < 1.0)) {
+    const double kappa = sqrt(q[1]) * sqrt(q[2]);
+    const double rho = sqrt(q[0]) + (double)(X.r + 2) * 0x1p-53 * kappa;
+    if (!(q[0] <= 0x1p-48 && rho < 0.5 && 1.01 * tol * kappa < 1.0 - rho)) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) V[i * Rp + j0 + u] = i == j0 + u ? 1.0 : 0.0;
         if (bi == 0 && bj == 0)

@@ -269,3 +269,30 @@ def test_mirrored_error_tiles(n, r):
     Cu[0, 1] = torch.nextafter(Cu[0, 1], Cu[0, 1] + 1)
     other = sk.sketch_nystrom_error(A, B, Cu).cpu().numpy()
     assert np.abs(got / other - 1).max() <= 1e-11
+
+
+@pytest.mark.parametrize("tol", [1e-12, 1e-6, 1e-3, 0.05])
+@pytest.mark.parametrize("side", [1 - 1e-3, 1 + 1e-3])
+def test_core_pinv_around_the_cut(tol, side):
+    """The smallest eigenvalue just below or above tol times the largest: cut or kept, whichever
+    way C^+ is formed."""
+    r = 40
+    lam = np.geomspace(1.0, max(10 * tol, 0.1), r)
+    lam[-1] = side * tol
+    Q, _ = np.linalg.qr(np.random.default_rng(7).standard_normal((r, r)))
+    C = (Q * lam) @ Q.T
+    Cp, info = sk.sketch_core_pinv(torch.from_numpy(0.5 * (C + C.T)).to(DEV), tol, max_sweeps=30)
+    assert info.cpu().tolist()[1] == 1
+    mu = np.where(lam > tol, 1.0 / lam, 0.0)
+    want = (Q * mu) @ Q.T
+    kappa = 1.0 / lam[lam > tol].min()
+    assert np.linalg.norm(Cp.cpu().numpy() - want) <= 64 * 64 * U64 * kappa * np.linalg.norm(want)
+
+
+def test_core_pinv_certificate_counts_its_rounding():
+    """With a condition number whose rounding alone could hide a singular core the sweeps run,
+    also at tol = 0 (a diagonal core's computed residual is exactly zero)."""
+    lam = np.array([1.0, 2.0 ** -60])
+    Cp, info = sk.sketch_core_pinv(torch.from_numpy(np.diag(lam)).to(DEV), 0.0)
+    assert info.cpu().tolist()[0] >= 1
+    assert np.array_equal(Cp.cpu().numpy(), np.diag(1.0 / lam))
