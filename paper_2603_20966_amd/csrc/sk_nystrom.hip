@@ -60,7 +60,8 @@ __device__ __forceinline__ int64_t tile_row(int I, int J, int t) {
 struct JacState {
     int converged;      // set once the off-diagonal norm is small enough
     int sweeps;         // sweeps run before convergence
-    int inverse;        // C^+ is the inverse of S (no eigenvalue is cut), left in S
+    int inverse;        // 1: C^+ is the inverse of S (no eigenvalue is cut), left in S;
+                        // -1: the elimination met a pivot that rules it out
     // of k_jac_sweep, zero between sweeps
     unsigned ticket;    // workgroups started
     alignas(128) unsigned solved;    // pair solves done, over all steps so far
@@ -209,9 +210,10 @@ struct SolveLds {
     double rs[kJT / 2];
 };
 
-template <int MODE, bool SH>
+// before_store(): until it returns, Q may still be read.
+template <int MODE, bool SH, typename Wait>
 __device__ __forceinline__ void jac_solve(const double* S, int64_t Rp, double* Q, int nb, int step,
-                                          int pair, SolveLds& L) {
+                                          int pair, SolveLds& L, Wait before_store) {
     double (*al)[kJP] = L.al;
     double (*ql)[kJP] = L.ql;
     double* rc = L.rc;
@@ -269,6 +271,7 @@ __device__ __forceinline__ void jac_solve(const double* S, int64_t Rp, double* Q
         for (int u = 0; u < 2; ++u)
             for (int v = 0; v < 2; ++v) a[u][v] = buf[2 * X + u][2 * Y + v];
     }
+    before_store();
     if (qrole) {        // back at the starting positions: Q in tile-index order
         double* Qp = Q + (int64_t)pair * kJT * kJT;
         for (int u = 0; u < 2; ++u)
@@ -456,19 +459,26 @@ __device__ __forceinline__ void jac_apply(double* S, double* V, int64_t Rp, cons
 // One sweep in one launch (r <= kSweepMaxR): the kFull step, then nb - 1 kCross steps (none
 // if nb == 2), each np solves and nT + nV applied tiles, and at last the convergence test.
 // A workgroup takes the next piece of work in that order when it starts (a ticket), and
-// waits only for pieces before its own: a solve for every tile of the step before, an applied
-// tile for the solves of its step.  Whoever holds a smaller ticket has started already and
-// itself waits only for still smaller ones, so the first unfinished piece always runs and
-// every wait ends, whatever the order or the number of workgroups that the device keeps
-// resident.  Solves count up one counter; applied tiles, of which there are many, each set
-// their own flag (done[b] = steps finished since the first sweep began), as additions to one
-// address come one at a time.
+// waits only for pieces before its own: a solve for the tiles of the step before, an applied
+// tile for these and for the solves of its step.  Whoever holds a smaller ticket has started
+// already and itself waits only for still smaller ones, so the first unfinished piece always
+// runs and every wait ends, whatever the order or the number of workgroups that the device
+// keeps resident.  Solves count up one counter; applied tiles, of which there are many, each
+// set their own flag (done[b] = steps finished since the first sweep began), as additions to
+// one address come one at a time.
+// Hand-over: every access to S, V, Q and the norms is an agent-scope atomic (mem_load,
+// mem_store), which goes to the device's point of coherence; the stores of a wave have arrived
+// there when its s_waitcnt vmcnt(0) ends, the barrier after it collects the waves, and only
+// then does the flag move.  A reader's loads are issued after the flag's value has come back.
+// (A release and an acquire of agent scope say the same to the memory model, but write back
+// and invalidate whole caches: 7.7 ms at r = 256.)
 // After convergence, or when the inverse was taken, a sweep then costs one short launch
 // (2.9 us) instead of 2 nb + 1 of 2.7 us each (r = 256, 16 sweeps: 1.4 ms of the inverse's
-// 1.6).  While sweeps run it takes as long as separate launches (a singular core, the
-// inverse's attempt included: r = 64 943 us against 961, r = 160 2824 against 2817, r = 256
-// 4692 against 4461); with many tiles the tickets take longer than the tiles, and larger
-// cores keep the launches.
+// 1.6).  A core that needs the sweeps pays for the attempt and, with many tiles, for the
+// tickets (separate launches alone, and now): r = 24 307 and 329 us, r = 64 1262 and 1290,
+// r = 128 2687 and 2705, r = 200 4615 and 4820, r = 256 5292 and 5577 (5713 while a solve
+// waited for every tile of the step before).  The tickets' share grows with r, so larger cores
+// keep the launches.
 constexpr int64_t kSweepMaxR = 256;
 
 __device__ __forceinline__ void wait_solved(unsigned* solved, unsigned target, unsigned near) {
@@ -496,6 +506,36 @@ __device__ __forceinline__ void wait_applied(const unsigned* done, unsigned nA, 
         if (__syncthreads_and(ok)) break;
         if (__syncthreads_or(least + 1 < target)) __builtin_amdgcn_s_sleep(127);
         else __builtin_amdgcn_s_sleep(2);
+    }
+}
+
+// The solve of pair (I, J) at kCross step `step` reads the tile of these two blocks, which the
+// step before left in three pieces: wait for those.
+__device__ __forceinline__ void wait_tile(const unsigned* done, int nb, int step, int pair,
+                                          unsigned target) {
+    const int np = nb / 2;
+    int I, J;
+    circle_pair(nb, step - 1, pair, I, J);
+    // the pair a block belonged to in the step before
+    auto owner = [&](int block) {
+        if (step == 1) return block / 2;
+        int p = 0;
+        for (int i = 0; i < np; ++i) {
+            int a, b;
+            circle_pair(nb, step - 2, i, a, b);
+            if (a == block || b == block) p = i;
+        }
+        return p;
+    };
+    const int pi = owner(I), pj = owner(J);
+    const int lo = threadIdx.x == 0 ? pi : threadIdx.x == 1 ? pj : min(pi, pj);
+    const int hi = threadIdx.x == 0 ? pi : threadIdx.x == 1 ? pj : max(pi, pj);
+    const unsigned* flag = done + (lo * np - lo * (lo - 1) / 2 + hi - lo);   // piece (lo, hi)
+    for (;;) {
+        const bool ok = threadIdx.x > 2 ||
+                        __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= target;
+        if (__syncthreads_and(ok)) break;
+        __builtin_amdgcn_s_sleep(2);
     }
 }
 
@@ -530,9 +570,16 @@ __global__ __launch_bounds__(kSolveThreads) void k_jac_sweep(double* S, double* 
             if (off <= tolc * tolc * tot) st->converged = 1;
         }
     } else if (piece < np) {
-        wait_applied(done, nA, base + step);
-        if (step == 0) jac_solve<kFull, true>(S, Rp, Q, nb, 0, (int)piece, lds.solve);
-        else jac_solve<kCross, true>(S, Rp, Q, nb, (int)step - 1, (int)piece, lds.solve);
+        // the pieces of the step before also read the Q that this solve replaces: all of them
+        // have to be done by then, the tile's own at once
+        if (step == 0) {
+            wait_applied(done, nA, base);
+            jac_solve<kFull, true>(S, Rp, Q, nb, 0, (int)piece, lds.solve, [] {});
+        } else {
+            wait_tile(done, nb, (int)step, (int)piece, base + step);
+            jac_solve<kCross, true>(S, Rp, Q, nb, (int)step - 1, (int)piece, lds.solve,
+                                    [&] { wait_applied(done, nA, base + step); });
+        }
         // every wave's stores have reached the point of coherence before the count moves
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
@@ -561,7 +608,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_jac_solve(const double* __res
                                                              int nb, int step, const JacState* st) {
     if (st->converged) return;
     __shared__ SolveLds lds;
-    jac_solve<MODE, false>(S, Rp, Q, nb, step, blockIdx.x, lds);
+    jac_solve<MODE, false>(S, Rp, Q, nb, step, blockIdx.x, lds, [] {});
 }
 
 template <int MODE>
@@ -640,10 +687,11 @@ __device__ __forceinline__ void tile_accumulate(const TX* __restrict__ X, int64_
 // ---- The inverse, where no eigenvalue is cut ----------------------------------------
 // If every |lambda| exceeds tol max|lambda|, V diag(mu) V^T is the inverse of S, which
 // takes Rp/32 short launches instead of a dozen Jacobi sweeps of 2 Rp/16 each.  A call at
-// r = 24 takes 80 us against 259, r = 64 85 against 814, r = 256 214 against 3618 and
-// r = 500 (whose idle sweeps stay separate launches) 1.8 ms against 8.3; a core that needs
-// the sweeps pays for the attempt, 15 us at r = 24 to 300 us at r = 500 (3 to 6%).  X = S^-1 by a block Gauss-Jordan
-// elimination without pivoting, R = I - S X as computed, and the certificate
+// r = 24 takes 70 us against 252, r = 64 85 against 822, r = 256 220 against 3627 and
+// r = 500 (whose idle sweeps stay separate launches, most of its time) 3.1 ms against 8.3; a
+// core that needs the sweeps pays for the attempt, 22 us at r = 24 to 0.4 ms at r = 500 (3 to
+// 7%), less where an early pivot ends it.
+// X = S^-1 by a block Gauss-Jordan elimination without pivoting, R = I - S X as computed, and the certificate
 //     ||R||_F <= 2^-24,  rho = ||R||_F + (r + 2) u ||S||_F ||X||_F < 1/2  (u = 2^-53)
 //     and  1.01 tol ||S||_F ||X||_F < 1 - rho.
 // rho bounds the exact residual (the middle term is the rounding of R), so S is not
@@ -684,9 +732,14 @@ __device__ __forceinline__ void load32(double (*t)[kJP], const Padded& m, int bi
 
 // Step k of the elimination, src -> dst: every workgroup forms one 32 x 32 block and
 // inverts the pivot block for itself (32 pivots, one barrier each).
-__global__ __launch_bounds__(kJThreads) void k_inv_step(const Padded src, const Padded dst, int k) {
+// A pivot of at most tol times the diagonal entry of S in its place ends the attempt: a
+// semidefinite S then has an eigenvalue to cut (the pivot is at least the smallest one, the
+// entry at most the largest), and another S would fail the certificate for the growth of X.
+__global__ __launch_bounds__(kJThreads) void k_inv_step(const Padded src, const Padded dst, int k,
+                                                        const Padded S, double tol, JacState* st) {
     __shared__ double d[kJT][kJP], a[kJT][kJP], b[kJT][kJP];
     __shared__ double prow[2][kJT], pcol[2][kJT];
+    const int ended = st->inverse;         // in flight with the blocks
     const int bi = blockIdx.y, bj = blockIdx.x;
     const int tid = threadIdx.x, ti = tid / 8, tj = tid % 8;
     double e[4], own[4] = {0.0, 0.0, 0.0, 0.0};
@@ -694,11 +747,15 @@ __global__ __launch_bounds__(kJThreads) void k_inv_step(const Padded src, const 
     for (int u = 0; u < 4; ++u) e[u] = src.get((int64_t)k * kJT + ti, (int64_t)k * kJT + 4 * tj + u);
     if (bj != k) load32(b, src, k, bj, ti, tj);
     if (bi != k) load32(a, src, bi, k, ti, tj);
+    const int64_t pk = (int64_t)k * kJT + (tid & (kJT - 1));
+    const double least = tol * fabs(S.get(pk, pk));
+    double pivot = 0.0;                    // of column tid % 32
     if (bi != k && bj != k) {
 #pragma unroll
         for (int u = 0; u < 4; ++u)
             own[u] = src.get((int64_t)bi * kJT + ti, (int64_t)bj * kJT + 4 * tj + u);
     }
+    if (ended < 0) return;
 #pragma unroll
     for (int p = 0; p < kJT; ++p) {
         double* pr = prow[p & 1];
@@ -711,6 +768,7 @@ __global__ __launch_bounds__(kJThreads) void k_inv_step(const Padded src, const 
         __syncthreads();
         const double inv = rcp_nr(pr[p]);
         const double f = pc[ti] * inv;
+        if ((tid & (kJT - 1)) == p) pivot = pr[p];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int j = 4 * tj + u;
@@ -721,7 +779,10 @@ __global__ __launch_bounds__(kJThreads) void k_inv_step(const Padded src, const 
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) d[ti][4 * tj + u] = e[u];
-    __syncthreads();
+    if (__syncthreads_or(!(fabs(pivot) > least))) {        // NaN too
+        if (bi == 0 && bj == 0 && tid == 0) st->inverse = -1;
+        return;
+    }
     double v[4] = {0.0, 0.0, 0.0, 0.0};
     if (bi == k && bj == k) {
 #pragma unroll
@@ -787,7 +848,9 @@ __device__ __forceinline__ double block_sum1(double x, double* red) {
 
 // R = I - S X by blocks; norm[3 t ..] = the block's squares of R, S and X.
 __global__ __launch_bounds__(kJThreads) void k_inv_residual(const Padded S, const Padded X,
-                                                            const Padded R, double* __restrict__ norm) {
+                                                            const Padded R, double* __restrict__ norm,
+                                                            const JacState* st) {
+    if (st->inverse < 0) return;
     __shared__ double a[kJT][kJP], b[kJT][kJP];
     __shared__ double red[kJThreads];
     const int bi = blockIdx.y, bj = blockIdx.x, np = gridDim.x;
@@ -839,7 +902,7 @@ __global__ __launch_bounds__(kJThreads) void k_inv_finish(const Padded X, const 
     const int64_t i = (int64_t)bi * kJT + ti, j0 = (int64_t)bj * kJT + 4 * tj;
     const double kappa = sqrt(q[1]) * sqrt(q[2]);
     const double rho = sqrt(q[0]) + (double)(X.r + 2) * 0x1p-53 * kappa;
-    if (!(q[0] <= 0x1p-48 && rho < 0.5 && 1.01 * tol * kappa < 1.0 - rho)) {
+    if (st->inverse < 0 || !(q[0] <= 0x1p-48 && rho < 0.5 && 1.01 * tol * kappa < 1.0 - rho)) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) V[i * Rp + j0 + u] = i == j0 + u ? 1.0 : 0.0;
         if (bi == 0 && bj == 0)
@@ -852,6 +915,7 @@ __global__ __launch_bounds__(kJThreads) void k_inv_finish(const Padded X, const 
     block_product(X, R, bi, bj, np, ti, tj, a, b, 1.0, acc);
 #pragma unroll
     for (int u = 0; u < 4; ++u) S[i * Rp + j0 + u] = acc[u];
+    // every workgroup has found st->inverse at 0 or 1: neither is below 0
     if (bi == 0 && bj == 0 && tid == 0) {
         st->converged = 1;
         st->inverse = 1;
@@ -868,7 +932,7 @@ __global__ __launch_bounds__(256) void k_pinv_form(const double* __restrict__ S,
                                                    int64_t ldcp, double* __restrict__ eig,
                                                    const JacState* st) {
     constexpr int TM = 32;
-    if (st->inverse) {           // the symmetric part of the inverse
+    if (st->inverse > 0) {       // the symmetric part of the inverse
         for (int e = threadIdx.x; e < TM * TM; e += 256) {
             const int64_t i = (int64_t)blockIdx.y * TM + e / TM, j = (int64_t)blockIdx.x * TM + e % TM;
             if (i < r && j < r) Cp[i * ldcp + j] = 0.5 * (S[i * Rp + j] + S[j * Rp + i]);
@@ -1209,10 +1273,11 @@ hipError_t launch_core_pinv(const void* C, int c_f64, int64_t r, int64_t ldc, do
         const Padded ms{S, Rp, r}, mv{V, Rp, r}, mc{Cp, ldcp, r};
         const dim3 gb((unsigned)np, (unsigned)np);
         for (int k = 0; k < (int)np; ++k)
-            k_inv_step<<<gb, kJThreads, 0, s>>>(k == 0 ? ms : k % 2 ? mv : mc, k % 2 ? mc : mv, k);
+            k_inv_step<<<gb, kJThreads, 0, s>>>(k == 0 ? ms : k % 2 ? mv : mc, k % 2 ? mc : mv, k, ms,
+                                                tol, st);
         const Padded& X = np % 2 ? mv : mc;
         const Padded& R = np % 2 ? mc : mv;
-        k_inv_residual<<<gb, kJThreads, 0, s>>>(ms, X, R, Q);
+        k_inv_residual<<<gb, kJThreads, 0, s>>>(ms, X, R, Q, st);
         k_inv_finish<<<gb, kJThreads, 0, s>>>(X, R, Q, tol, S, V, Rp, done, (int)(nT + nV), st);
     }
     // off-diagonal Frobenius norm at most 8 Rp units of FP64 rounding of ||S||

@@ -296,3 +296,34 @@ def test_core_pinv_certificate_counts_its_rounding():
     Cp, info = sk.sketch_core_pinv(torch.from_numpy(np.diag(lam)).to(DEV), 0.0)
     assert info.cpu().tolist()[0] >= 1
     assert np.array_equal(Cp.cpu().numpy(), np.diag(1.0 / lam))
+
+
+def test_sweeps_beside_other_work():
+    """The one-launch sweeps hand tiles from workgroup to workgroup: the same bits alone and with
+    products running on a second stream, and on two streams at once."""
+    cores = []
+    for r in (40, 100, 256):
+        F = torch.from_numpy(np.random.default_rng(r).standard_normal((r, r // 2))).to(DEV)
+        cores.append(F @ F.t().contiguous())                # half the eigenvalues are cut
+    A = torch.randn((8192, 8192), device=DEV)
+    ws = [[torch.empty(int(sk.lib().sketch_core_pinv_workspace(C.shape[0])), dtype=torch.uint8, device=DEV)
+           for C in cores] for _ in range(2)]
+    alone = [sk.sketch_core_pinv(C, max_sweeps=30) for C in cores]
+    torch.cuda.synchronize()
+    assert all(int(info[0]) >= 1 and int(info[1]) == 1 for _, info in alone)
+    s1, s2, s3 = (torch.cuda.Stream() for _ in range(3))
+    outs = []
+    Y = torch.empty((8192, 64), device=DEV)
+    wp = torch.empty(int(sk.sketch_workspace_size(0, 0, 8192, 8192, 64, 1)), dtype=torch.uint8, device=DEV)
+    torch.cuda.synchronize()
+    for i in range(3):
+        with torch.cuda.stream(s3):
+            for _ in range(20):
+                sk.sketch_gen_matmul(A, 3, 64, Y=Y, workspace=wp)
+        for s, w in ((s1, ws[0]), (s2, ws[1])):
+            with torch.cuda.stream(s):
+                outs.append([sk.sketch_core_pinv(C, max_sweeps=30, workspace=x) for C, x in zip(cores, w)])
+    torch.cuda.synchronize()
+    for got in outs:
+        for (Cp, info), (C0, i0) in zip(got, alone):
+            assert torch.equal(Cp, C0) and torch.equal(info, i0)
