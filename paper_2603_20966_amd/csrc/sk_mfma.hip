@@ -1530,7 +1530,12 @@ constexpr int kSkChainThreads = 256;                       // waves 0..3
 constexpr int kSkGenThreads = 512;                         // waves 4..11
 constexpr int kSkThreads = kSkChainThreads + kSkGenThreads;
 
-template <int kKC, bool ALIGNED>
+// ROWS: kWhole (m a multiple of 4), kCut (the group of four rows that m cuts is loaded as the
+// last four and moved down on its way to LDS: with its four elements loaded one by one, behind
+// branches, C = Omega^T B of 58688 x 42 took 55.5 us instead of 39.8, 50.7 on the FP32
+// instruction) or kFew (m < 4: element by element).
+enum { kWhole, kCut, kFew };
+template <int kKC, int ROWS>
 __global__ __launch_bounds__(kSkThreads) void k_gemm_cm_mfma_skinny(const CmMArgs a) {
     constexpr int BN = 16;
     constexpr int kNS = kKC / 4;
@@ -1570,6 +1575,9 @@ __global__ __launch_bounds__(kSkThreads) void k_gemm_cm_mfma_skinny(const CmMArg
     // the older group only; columns past the strip's end are stored as zeros, rows
     // past m are never stored by the chains.
     const int tg = threadIdx.x - kSkChainThreads;
+    // rows of the thread's group of four (the same in each of its pieces) if m cuts it
+    const int left = (int)a.m - 4 * (tg & 15);
+    const int cut = left > 0 && left < 4 ? left : 0;
     auto g_load = [&](int gi, v4f* xa, v4f* xo) {
 #pragma unroll
         for (int t = 0; t < kAPieces; ++t) {
@@ -1581,16 +1589,14 @@ __global__ __launch_bounds__(kSkThreads) void k_gemm_cm_mfma_skinny(const CmMArg
             const int c = min(gi * kSkG + ci, nchunks - 1);
             const int64_t colg = col_begin + min(c * kKC + col, w - 1);
             const float* src = a.A + colg * a.lda;
-            if constexpr (ALIGNED) {
+            if constexpr (ROWS == kWhole) {
                 xa[t] = *reinterpret_cast<const v4f*>(src + (4 * r4 < a.m ? 4 * r4 : 0));
+            } else if constexpr (ROWS == kCut) {
+                xa[t] = *reinterpret_cast<const v4f_a4*>(src + (cut ? a.m - 4 : 4 * r4 < a.m ? 4 * r4 : 0));
             } else {
                 v4f v = {0.f, 0.f, 0.f, 0.f};
-                if (4 * r4 + 3 < a.m) {
-                    v = *reinterpret_cast<const v4f*>(src + 4 * r4);
-                } else {
-                    for (int e = 0; e < 4; ++e)
-                        if (4 * r4 + e < a.m) v[e] = src[4 * r4 + e];
-                }
+                for (int e = 0; e < 4; ++e)
+                    if (4 * r4 + e < a.m) v[e] = src[4 * r4 + e];
                 xa[t] = v;
             }
         }
@@ -1618,8 +1624,14 @@ __global__ __launch_bounds__(kSkThreads) void k_gemm_cm_mfma_skinny(const CmMArg
             const int r4 = rem & 15;
             const bool inside = (gi * kSkG + ci) * kKC + col < w;
             float* dst = &as[slot0 + ci][col][r4];
+            v4f v = xa[t];
+            if constexpr (ROWS == kCut) {
+                if (cut == 1) v = v4f{v[3], 0.f, 0.f, 0.f};
+                else if (cut == 2) v = v4f{v[2], v[3], 0.f, 0.f};
+                else if (cut == 3) v = v4f{v[1], v[2], v[3], 0.f};
+            }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) dst[16 * e] = inside ? xa[t][e] : 0.0f;
+            for (int e = 0; e < 4; ++e) dst[16 * e] = inside ? v[e] : 0.0f;
         }
 #pragma unroll
         for (int t = 0; t < kOPieces; ++t) {
@@ -2508,12 +2520,13 @@ hipError_t launch_gemm_cm_mfma(const CmLaunch& g) {
     static_assert(chunk_cols(1) == KC && chunk_cols(2) == KC && chunk_cols(4) == KC,
                   "one chunk width for every N-tile count of the row-major kernel");
     if (skinny) {
+        const dim3 grid((unsigned)a.tiles), threads(kSkThreads);
         if (g.m % 4 == 0)
-            hipLaunchKernelGGL((k_gemm_cm_mfma_skinny<KC, true>), dim3((unsigned)a.tiles),
-                               dim3(kSkThreads), 0, g.stream, a);
+            hipLaunchKernelGGL((k_gemm_cm_mfma_skinny<KC, kWhole>), grid, threads, 0, g.stream, a);
+        else if (g.m > 4)
+            hipLaunchKernelGGL((k_gemm_cm_mfma_skinny<KC, kCut>), grid, threads, 0, g.stream, a);
         else
-            hipLaunchKernelGGL((k_gemm_cm_mfma_skinny<KC, false>), dim3((unsigned)a.tiles),
-                               dim3(kSkThreads), 0, g.stream, a);
+            hipLaunchKernelGGL((k_gemm_cm_mfma_skinny<KC, kFew>), grid, threads, 0, g.stream, a);
         e = hipGetLastError();
     } else switch (nt) {
     case 1: e = launch_cm_mfma_nt<1, KC>(a, g.stream); break;

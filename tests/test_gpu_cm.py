@@ -182,3 +182,17 @@ def test_waves_without_rows_cost_little():
 
     few, full = ms(80), ms(512)
     assert few <= 0.9 * full, (few, full)
+
+
+@pytest.mark.parametrize("p", [1, 2, 3, 4, 5, 6, 7, 18, 35, 42, 61, 62, 63])
+def test_few_rows_with_a_cut_group(p):
+    """Rows that are no multiple of four: the group that m cuts is loaded as the last four."""
+    n, k = 4200, 24
+    A = normal_matrix(300, n, seed=p)
+    Ad = cm_dev(A)
+    Y = sk.sketch_gen_matmul_cm(Ad, 9, k)
+    buf = torch.full((n, (p + 3) // 4 * 4), float("nan"), device=DEV)   # a row past m is poison
+    buf[:, :p] = Ad[:p].t()
+    assert torch.equal(sk.sketch_gen_matmul_cm(buf[:, :p].t(), 9, k), Y[:p])
+    assert torch.equal(sk.sketch_gen_matmul_cm(Ad[300 - p // 4 * 4 - 4:][:p], 9, k),
+                       Y[300 - p // 4 * 4 - 4:][:p])
