@@ -1,9 +1,10 @@
 // Matrix-core kernels for Y = A * Omega(seed) with a wide sketch on gfx950.
 //
-// FP32 A (k > 8).  The product is a dense contraction (2k flops per A element);
-// it runs on the FP16 matrix cores with both operands split into FP16 terms
-// (sk_split.hpp: four v_mfma_f32_16x16x32_f16 per 32 contraction columns, FP32
-// sums), whose error against FP64 is below that of an FP32 chain.
+// FP32 A (k > 8).  The product is a dense contraction (2k flops per A element).
+// k = 9 .. 16: v_mfma_f32_16x16x4f32 (mfma_tile_f32).  k > 16: the FP16 matrix cores
+// with both operands split into FP16 terms (sk_split.hpp: four v_mfma_f32_16x16x32_f16
+// per 32 contraction columns, FP32 sums), whose error against FP64 is below that of an
+// FP32 chain on dense data; what the terms cannot hold goes to f32_sums.
 //
 // Tile of one workgroup (64 W threads = W waves): 16 TM W rows of A x a strip of
 // kMfmaStrip contraction columns x BN = 16*NT sketch columns.  Each wave owns
@@ -48,7 +49,6 @@ static_assert(kBM == kMfmaRows, "tile rows");
 // With 8 N-tiles the raw A values are single-buffered (the accumulators take 128
 // registers): they are split before a chunk's 128 MFMAs, which cover the next
 // chunk's load.
-constexpr int chunk_cols(int) { return kSplitKC; }
 constexpr bool single_a(int nt, int tm = kTM) { return nt >= 8 && tm >= kTM; }
 // Chunks of Omega generated per barrier by a tile of W waves x 16 TM rows (one or two
 // N-tiles): one in the 512-row tile, where the other waves' MFMAs cover a chunk's few
@@ -224,9 +224,10 @@ __device__ __forceinline__ void omega_zero_pad(_Float16 (*om)[BN][kSplitRow], in
 
 // Chunks c0 .. c0 + G - 1 (those below nchunks) of the tile's strip, sketch columns
 // n_base .. n_base + kb - 1, split into LDS slots slot0 .. (slot0 + G - 1); zeros past
-// the strip's end.  Generated from the seed, or read from a stored Omega.  With few sketch columns one chunk has too few Philox quads to occupy the
-// workgroup, G of them do.  A chunk's first Omega row is aligned as the strip's (chunk
-// widths are multiples of 4), so every chunk has the same quad count.
+// the strip's end.  Generated from the seed, or read from a stored Omega.  With few sketch
+// columns one chunk has too few Philox quads to occupy the workgroup, G of them do.  A
+// chunk's first Omega row is aligned as the strip's (chunk widths are multiples of 4), so
+// every chunk has the same quad count.
 template <int BN, int TH, int G, bool GEN>
 __device__ __forceinline__ void omega_group(const MTile& t, _Float16 (*om)[BN][kSplitRow],
                                             int slot0, int c0, int nchunks, int w, int kb) {
@@ -281,7 +282,7 @@ __device__ __forceinline__ void omega_group(const MTile& t, _Float16 (*om)[BN][k
 // same Omega chunks, so the call forms them once.  One FP32 plane, chunk
 // gc = strip * (kMfmaStrip / 32) + c, then sketch column n in [0, kpad), then
 // contraction column kl in [0, 32): element (gc * kpad + n) * 32 + kl; the
-// values (zeros past the strip's end and for n >= k) are those omega_chunk
+// values (zeros past the strip's end and for n >= k) are those omega_group
 // writes into LDS, so the sums are the same bit for bit.
 constexpr int kF32PackRows = 16;   // sketch columns per packing workgroup
 constexpr bool mfma_packed(int nt) { return nt >= 4; }
@@ -293,7 +294,7 @@ constexpr int kF32PackChunks = 4;
 
 template <bool GEN>
 __global__ __launch_bounds__(256) void k_f32_pack(const PackArgs a) {
-    constexpr int KC = chunk_cols(4);
+    constexpr int KC = kSplitKC;
     constexpr int CPS = kMfmaStrip / KC;
     constexpr int G = kF32PackChunks;
     static_assert(CPS % G == 0, "groups of chunks inside a strip");
@@ -495,9 +496,11 @@ __device__ __forceinline__ void f32_sums(const MTile& t, const TileOut& o, float
     const int nchunks = (w + KC - 1) / KC;
     auto om_load = [&](Piece* r, int c) {
         if constexpr (PK) {
-            const float* p = t.fpack + ((t.strip * (kMfmaStrip / KC) + min(c, nchunks - 1)) * t.kpad + t.n_base) * KC;
+            const int64_t gc = t.strip * (kMfmaStrip / KC) + min(c, nchunks - 1);
+            const float* p = t.fpack + (gc * t.kpad + t.n_base) * KC;
 #pragma unroll
-            for (int j = 0; j < OPT; ++j) r[j] = *reinterpret_cast<const v4f*>(p + 4 * min(tid + j * TH, PPL - 1));
+            for (int j = 0; j < OPT; ++j)
+                r[j] = *reinterpret_cast<const v4f*>(p + 4 * min(tid + j * TH, PPL - 1));
         } else if constexpr (COPY) {
 #pragma unroll
             for (int j = 0; j < OPT; ++j) {
@@ -1090,9 +1093,9 @@ void k_gemm_mfma(const MArgs args) {
     else mfma_tile<NT, W, TM, GEN, FULL, mfma_packed(NT)>(t, lds);
 }
 
-// A batch of independent requests (serving): the tiles of each request are the
-// ones a call for that request alone would run, walked by a fixed grid in an
-// XCD-grouped order, so each result does not depend on the batch.
+// A batch of independent requests (serving): 512-row tiles of all requests, walked by a
+// fixed grid in an XCD-grouped order, Omega generated in the tile.  A row's sums depend on
+// neither, so each result is that of a call for the request alone.
 template <int NT, bool FULL>
 __global__ __launch_bounds__(kThreads) void k_gemm_mfma_batch(const BatchArgs args) {
     __shared__ __attribute__((aligned(16))) TileLds<NT, kWaves, kTM> lds;
@@ -1172,14 +1175,13 @@ struct CmMArgs {
     int64_t kpad;
 };
 
-// KC = the row-major kernel's chunk for this k (chunk_cols(mfma_ntiles(k))),
-// whatever N-tile count the launch picked, so that the sums are the same.
-// FULL (at least four rows and one whole chunk of columns): every lane of every wave
-// issues the same loads each chunk from a valid address (a lane or wave without rows
-// reads row 0; its sums are never stored; a load past the strip's whole chunks re-reads
+// KC = the row-major kernel's chunk, so that the sums are the same.
+// FULL (one whole chunk of columns; these tiles have 65 rows or more): every lane of a wave
+// with rows issues the same loads each chunk from a valid address (a lane without rows
+// reads row 0, its sums are never stored; a load past the strip's whole chunks re-reads
 // one), so the compiler waits for the chunk in use alone (see mfma_tile).  ROWS4: m is
 // a multiple of 4, so no lane's four rows are cut.
-constexpr bool cm_full(int64_t m, int64_t n) { return m >= 4 && n >= kSplitKC; }
+constexpr bool cm_full(int64_t n) { return n >= kSplitKC; }
 // four floats at any float's alignment
 typedef float v4f_a4 __attribute__((ext_vector_type(4), aligned(4)));
 // Packed Omega on the column-major tiles: four or more N-tiles, except eight
@@ -1728,7 +1730,7 @@ __global__ __launch_bounds__(kSkThreads) void k_gemm_cm_mfma_skinny(const CmMArg
 template <int NT, int KC>
 hipError_t launch_cm_mfma_nt(const CmMArgs& a, hipStream_t s) {
     const dim3 grid((unsigned)(8 * a.tiles8));
-    if (!cm_full(a.m, a.n))
+    if (!cm_full(a.n))
         hipLaunchKernelGGL((k_gemm_cm_mfma<NT, KC, false, false>), grid, dim3(kThreads), 0, s, a);
     else if (a.m % 4 == 0)
         hipLaunchKernelGGL((k_gemm_cm_mfma<NT, KC, true, true>), grid, dim3(kThreads), 0, s, a);
@@ -2401,7 +2403,7 @@ hipError_t launch_gemm_mfma(const GemmLaunch& g) {
     const TraceEvents& tr = g.trace;
     if (tr.begin) (void)hipEventRecord(tr.begin, g.stream);
     if (mfma_packed(nt)) {
-        const dim3 pgrid((unsigned)(S * (kMfmaStrip / chunk_cols(nt)) / kF32PackChunks),
+        const dim3 pgrid((unsigned)(S * (kMfmaStrip / kSplitKC) / kF32PackChunks),
                          (unsigned)((pk.kpad + kF32PackRows - 1) / kF32PackRows));
         if (pk.omega)
             hipLaunchKernelGGL((k_f32_pack<false>), pgrid, dim3(256), 0, g.stream, pk);
@@ -2495,7 +2497,7 @@ hipError_t launch_gemm_cm_mfma(const CmLaunch& g) {
     a.tiles = (int64_t)a.S * a.num_rb * ((g.k + BN - 1) / BN);
     a.tiles8 = (a.tiles + 7) / 8;
     hipError_t e;
-    if (skinny || cm_packed(nt, cm_full(g.m, g.n))) {
+    if (skinny || cm_packed(nt, cm_full(g.n))) {
         // the call's Omega, once (the same plane as the row-major call's); the
         // few-row kernel copies it instead of generating in its workgroups
         PackArgs pk{};
@@ -2508,7 +2510,7 @@ hipError_t launch_gemm_cm_mfma(const CmLaunch& g) {
         pk.dist = a.dist;
         pk.P = 1;
         pk.blk[0] = BlockDesc{g.A, g.n, g.lda, g.row0, nullptr};
-        const dim3 pgrid((unsigned)(S * (kMfmaStrip / chunk_cols(nt)) / kF32PackChunks),
+        const dim3 pgrid((unsigned)(S * (kMfmaStrip / kSplitKC) / kF32PackChunks),
                          (unsigned)((pk.kpad + kF32PackRows - 1) / kF32PackRows));
         hipLaunchKernelGGL((k_f32_pack<true>), pgrid, dim3(256), 0, g.stream, pk);
         e = hipGetLastError();
@@ -2516,9 +2518,7 @@ hipError_t launch_gemm_cm_mfma(const CmLaunch& g) {
         a.fpack = static_cast<const float*>(pk.hi);
         a.kpad = pk.kpad;
     }
-    constexpr int KC = chunk_cols(8);
-    static_assert(chunk_cols(1) == KC && chunk_cols(2) == KC && chunk_cols(4) == KC,
-                  "one chunk width for every N-tile count of the row-major kernel");
+    constexpr int KC = kSplitKC;
     if (skinny) {
         const dim3 grid((unsigned)a.tiles), threads(kSkThreads);
         if (g.m % 4 == 0)

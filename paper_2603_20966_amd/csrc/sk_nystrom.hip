@@ -641,44 +641,31 @@ __global__ __launch_bounds__(kJThreads) void k_jac_flag(const double* __restrict
     }
 }
 
-// Fixed-shape FP64 tile engine: out(i, j) = sum_l X(i, l) Y(j, l) (times mu_l
-// when mu is given), l ascending, for a TM x TM tile per workgroup (256 threads,
-// (TM/16) x (TM/16) outputs each, l in chunks of 16 staged in LDS).
+// 32 x 32 tile at (i0, j0) of V diag(mu) V^T: sum_l V(i, l) V(j, l) mu_l, l ascending, for
+// i, j < r (256 threads, 2 x 2 outputs each, l in chunks of 16 staged in LDS).
 constexpr int kGK = 16;
-constexpr int kGT = 64;            // tile of the workspace rule below
 
-template <int TM, typename TX, typename TY>
-__device__ __forceinline__ void tile_accumulate(const TX* __restrict__ X, int64_t ldx, int64_t mx,
-                                                const TY* __restrict__ Y, int64_t ldy, int64_t my,
-                                                int64_t K, const double* mu, int64_t i0,
-                                                int64_t j0, double acc[TM / 16][TM / 16],
-                                                double (*xs)[TM], double (*ys)[TM]) {
-    constexpr int R = TM / 16;                  // outputs per thread and dimension
+__device__ __forceinline__ void spectral_tile(const double* __restrict__ V, int64_t ldv, int64_t r,
+                                              const double* mu, int64_t i0, int64_t j0,
+                                              double acc[2][2], double (*xs)[kJT], double (*ys)[kJT]) {
     const int tid = threadIdx.x, ty = tid / 16, tx = tid % 16;
-    const int li = tid / (16 / R), lk = (tid % (16 / R)) * R;
-    for (int a = 0; a < R; ++a)
-        for (int c = 0; c < R; ++c) acc[a][c] = 0.0;
-    for (int64_t l0 = 0; l0 < K; l0 += kGK) {
-        for (int w = 0; w < R; ++w) {
+    const int li = tid / 8, lk = (tid % 8) * 2;
+    for (int a = 0; a < 2; ++a)
+        for (int c = 0; c < 2; ++c) acc[a][c] = 0.0;
+    for (int64_t l0 = 0; l0 < r; l0 += kGK) {
+        for (int w = 0; w < 2; ++w) {
             const int64_t l = l0 + lk + w;
             const int64_t gi = i0 + li, gj = j0 + li;
-            xs[lk + w][li] = (gi < mx && l < K) ? (double)X[gi * ldx + l] : 0.0;
-            ys[lk + w][li] = (gj < my && l < K) ? (double)Y[gj * ldy + l] : 0.0;
+            xs[lk + w][li] = (gi < r && l < r) ? V[gi * ldv + l] : 0.0;
+            ys[lk + w][li] = (gj < r && l < r) ? V[gj * ldv + l] : 0.0;
         }
         __syncthreads();
-        const int kk_end = (int)((K - l0) < kGK ? (K - l0) : kGK);
+        const int kk_end = (int)((r - l0) < kGK ? (r - l0) : kGK);
         for (int kk = 0; kk < kk_end; ++kk) {
-            double xv[R], yv[R];
-            for (int a = 0; a < R; ++a) xv[a] = xs[kk][ty * R + a];
-            for (int c = 0; c < R; ++c) yv[c] = ys[kk][tx * R + c];
-            if (mu) {
-                const double m = mu[l0 + kk];
-                for (int a = 0; a < R; ++a)
-                    for (int c = 0; c < R; ++c) acc[a][c] = fma(xv[a] * yv[c], m, acc[a][c]);
-            } else {
-                for (int a = 0; a < R; ++a)
-                    for (int c = 0; c < R; ++c) acc[a][c] = fma(xv[a], yv[c], acc[a][c]);
-            }
+            const double m = mu[l0 + kk];
+            for (int a = 0; a < 2; ++a)
+                for (int c = 0; c < 2; ++c)
+                    acc[a][c] = fma(xs[kk][ty * 2 + a] * ys[kk][tx * 2 + c], m, acc[a][c]);
         }
         __syncthreads();
     }
@@ -691,7 +678,8 @@ __device__ __forceinline__ void tile_accumulate(const TX* __restrict__ X, int64_
 // r = 500 (whose idle sweeps stay separate launches, most of its time) 3.1 ms against 8.3; a
 // core that needs the sweeps pays for the attempt, 22 us at r = 24 to 0.4 ms at r = 500 (3 to
 // 7%), less where an early pivot ends it.
-// X = S^-1 by a block Gauss-Jordan elimination without pivoting, R = I - S X as computed, and the certificate
+// X = S^-1 by a block Gauss-Jordan elimination without pivoting, R = I - S X as computed,
+// and the certificate
 //     ||R||_F <= 2^-24,  rho = ||R||_F + (r + 2) u ||S||_F ||X||_F < 1/2  (u = 2^-53)
 //     and  1.01 tol ||S||_F ||X||_F < 1 - rho.
 // rho bounds the exact residual (the middle term is the rounding of R), so S is not
@@ -960,7 +948,7 @@ __global__ __launch_bounds__(256) void k_pinv_form(const double* __restrict__ S,
     __syncthreads();
     const int64_t i0 = (int64_t)blockIdx.y * TM, j0 = (int64_t)blockIdx.x * TM;
     double acc[2][2];
-    tile_accumulate<TM>(V, Rp, r, V, Rp, r, r, mu, i0, j0, acc, xs, ys);
+    spectral_tile(V, Rp, r, mu, i0, j0, acc, xs, ys);
     const int ty = tid / 16, tx = tid % 16;
     for (int a = 0; a < 2; ++a)
         for (int c = 0; c < 2; ++c) {
@@ -975,7 +963,7 @@ __global__ __launch_bounds__(256) void k_pinv_form(const double* __restrict__ S,
 // doubles, so that the four l of an operand read fall on different banks; the next 16 are
 // loaded while these are multiplied (64 MFMAs of 64 cycles a wave, which hide them).
 // The former tile of 64 x 64 with FP64 FMAs ran at 29 TFLOP/s, two LDS reads for every four
-// FMAs; this one at 58, the matrix cores busy 73% of the time (error at n = 16384, r = 256
+// FMAs; this one at 58, the matrix cores busy 74% of the time (error at n = 16384, r = 256
 // with a C^+ that is not bitwise symmetric: 4.78 -> 2.45 ms; n = 5000, r = 100: 229 -> 177 us;
 // n = 2048, r = 16: 21 us either way).
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -1305,6 +1293,9 @@ hipError_t launch_core_pinv(const void* C, int c_f64, int64_t r, int64_t ldc, do
     if (info) k_jac_info<<<1, 64, 0, s>>>(st, info);
     return hipGetLastError();
 }
+
+// W, then a pair of partial sums for each 64 x 64 tile (more than the kDT-wide tiles fill)
+constexpr int kGT = 64;
 
 size_t nystrom_workspace_bytes(int64_t n, int64_t r) {
     if (n <= 0 || r <= 0) return 0;

@@ -15,10 +15,12 @@
 // the products' sum, besides the rounding of the additions.  The last two terms matter only
 // where Omega brings out a row's small entries; a stored Omega that could is multiplied by
 // the FP32 instruction instead (stored_columns), and so are strips narrower than a chunk.
-// Relative Frobenius error against FP64 (N(0,1) A, 16384 to 32768 columns): 5.2e-7 to
-// 5.4e-7, against 8.1e-7 of the FP32 instruction's chain of 512 additions per strip.
-// Time, k = 64 on 65536 x 16384: 850 us against 1237; k = 256 on 32768^2: 2.23 ms
-// against 4.72; column-major k = 64 on 32768^2: 812 us against 1260.
+// Relative Frobenius error against FP64 (N(0,1) A): 5.2e-7 to 5.4e-7 at 16384 to 32768
+// columns, against 8.1e-7 of the FP32 instruction's chain of 512 additions per strip;
+// 3.5e-7 against 5.7e-7 at 1024, equal at 16 to 31; 2.0e-7 against 1.2e-7 on rows with 2%
+// of non-zeros.
+// Time, k = 64 on 65536 x 16384: 854 us against 1219; k = 256 on 32768^2: 2.19 ms
+// against 4.71; column-major k = 64 on 32768^2: 804 us against 1245.
 // FP16 has 40 binades, so every row of A carries its own scale s: a strip's rows
 // start from the largest |a| of their first non-zero chunk, put in [2^10, 2^11),
 // and a row whose scaled entries pass 2^15 in a later chunk is scaled down again
