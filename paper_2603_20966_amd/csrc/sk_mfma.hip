@@ -533,8 +533,9 @@ __device__ __forceinline__ void f32_sums(const MTile& t, const TileOut& o, float
         om_load(r, 1);
         if (rows) load(x1, min(1, nchunks - 1));
     } else {
+        // (generated: rows with an infinity, or a strip of one chunk: no load without a use)
         if (rows) load(x0, 0);
-        if (rows) load(x1, min(1, nchunks - 1));
+        if (rows && nchunks > 1) load(x1, 1);
         for (int it = tid; it < 2 * BN * kF32Row; it += TH)
             if ((it / kF32Row) % BN >= kb) (&om[0][0][0])[it] = 0.0f;
         omega_chunk_f32<TH, true>(t, om[0], 0, w, kb, 0);
@@ -561,7 +562,7 @@ __device__ __forceinline__ void f32_sums(const MTile& t, const TileOut& o, float
                             acc[tm][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(z[e], x[tm][4 * v + e],
                                                                                acc[tm][nt], 0, 0, 0);
                 }
-            load(x, min(c + 2, nchunks - 1));
+            if (COPY || c + 2 < nchunks) load(x, min(c + 2, nchunks - 1));
             __builtin_amdgcn_sched_barrier(0);
         }
         lds_barrier_m();
