@@ -28,6 +28,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "sk_internal.hpp"
 
 namespace sk {
@@ -1006,7 +1008,10 @@ __device__ __forceinline__ void load8(const float* p, int64_t left, double* v) {
 
 // acc[tm][tn]: register r of lane (g, j) is row 64 (wave / 2) + 16 tm + 4 r + g, column
 // 64 (wave % 2) + 16 tn + j of the tile.  Rows past mx (my) repeat the last one.
-template <typename TX, typename TY>
+// TAIL: K is no multiple of 16; its last values are multiplied after the loop, without the
+// zeros that fill their stage (r = 20 on n = 3001: 42.2 -> 36.4 us).  An instance of its own: with
+// the tail's code behind it the loop takes 2% longer at r = 256, with a test in it 5%.
+template <bool TAIL, typename TX, typename TY>
 __device__ __forceinline__ void tile_mfma64(const TX* __restrict__ X, int64_t ldx, int64_t mx,
                                             const TY* __restrict__ Y, int64_t ldy, int64_t my,
                                             int64_t K, int64_t i0, int64_t j0, v4d (&acc)[4][4],
@@ -1036,9 +1041,7 @@ __device__ __forceinline__ void tile_mfma64(const TX* __restrict__ X, int64_t ld
     store(0);
     __syncthreads();
     int b = 0;
-    auto multiply = [&](int kk) {
-        const double* xb = &L.x[b][g][(wave >> 1) * 64 + j];
-        const double* yb = &L.y[b][g][(wave & 1) * 64 + j];
+    auto multiply = [&](const double* xb, const double* yb, int kk) {
         double av[4], bv[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
@@ -1052,25 +1055,30 @@ __device__ __forceinline__ void tile_mfma64(const TX* __restrict__ X, int64_t ld
                 acc[a][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[c], acc[a][c], 0, 0, 0);
     };
     int64_t l0 = 0;
-    for (; l0 + kDK <= K; l0 += kDK, b ^= 1) {
+    for (; TAIL ? l0 + kDK <= K : l0 < K; l0 += kDK, b ^= 1) {
         const bool more = l0 + kDK < K;
         if (more) load(l0 + kDK);
+        const double* xb = &L.x[b][g][(wave >> 1) * 64 + j];
+        const double* yb = &L.y[b][g][(wave & 1) * 64 + j];
 #pragma unroll
-        for (int kk = 0; kk < kDK; kk += 4) multiply(kk);
+        for (int kk = 0; kk < kDK; kk += 4) multiply(xb, yb, kk);
         if (more) store(b ^ 1);
         __syncthreads();
     }
-    // the last values, without the zeros after them (r = 20 on n = 3001: 42.2 -> 37.2 us; a test
-    // of the end in the loop above costs 5% at r = 256)
+    if constexpr (TAIL) {
+        const double* xb = &L.x[b][g][(wave >> 1) * 64 + j];
+        const double* yb = &L.y[b][g][(wave & 1) * 64 + j];
 #pragma unroll
-    for (int kk = 0; kk < kDK; kk += 4) {
-        if (l0 + kk >= K) break;
-        multiply(kk);
+        for (int kk = 0; kk < kDK; kk += 4) {
+            if (l0 + kk >= K) break;
+            multiply(xb, yb, kk);
+        }
     }
 }
 
 // W = B C^+ (rows [row0, row0 + mw) of B; C^+ symmetric, so W(i, j) =
 // sum_l B(i, l) C^+(j, l)).
+template <bool TAIL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void k_bw(const float* __restrict__ B, int64_t ldb, int64_t mw, int64_t r,
           const double* __restrict__ Cp, int64_t ldcp, double* __restrict__ W, int* sym) {
@@ -1078,7 +1086,7 @@ void k_bw(const float* __restrict__ B, int64_t ldb, int64_t mw, int64_t r,
     if (sym && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *sym = 1;
     const int64_t i0 = (int64_t)blockIdx.y * kDT, j0 = (int64_t)blockIdx.x * kDT;
     v4d acc[4][4];
-    tile_mfma64(B, ldb, mw, Cp, ldcp, r, r, i0, j0, acc, lds);
+    tile_mfma64<TAIL>(B, ldb, mw, Cp, ldcp, r, r, i0, j0, acc, lds);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int a = 0; a < 4; ++a)
@@ -1116,7 +1124,7 @@ __global__ __launch_bounds__(256) void k_symmetric(const double* __restrict__ Cp
 // C^+ (*sym), A~ is symmetric: a tile above the diagonal serves its mirror image too, and
 // the tiles below the diagonal do nothing.  The tile's elements of A are loaded from clamped
 // addresses without a branch, 16 of a lane (32 with the mirror image) in flight.
-template <bool ERR>
+template <bool ERR, bool TAIL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void k_nys_tile(const double* __restrict__ W, int64_t mw, const float* __restrict__ B, int64_t ldb,
                 int64_t n, int64_t r, const float* __restrict__ A, int64_t lda,
@@ -1135,7 +1143,7 @@ void k_nys_tile(const double* __restrict__ W, int64_t mw, const float* __restric
     }
     const int64_t i0 = (int64_t)blockIdx.y * kDT, j0 = (int64_t)blockIdx.x * kDT;
     v4d acc[4][4];
-    tile_mfma64(W, r, mw, B, ldb, n, r, i0, j0, acc, lds);
+    tile_mfma64<TAIL>(W, r, mw, B, ldb, n, r, i0, j0, acc, lds);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int li = (wave >> 1) * 64 + (lane >> 4), lj = (wave & 1) * 64 + (lane & 15);
     if constexpr (!ERR) {
@@ -1324,17 +1332,21 @@ hipError_t launch_nystrom(const float* A, int64_t lda, const float* B, int64_t n
     const float* Bw = A ? B : B + row0 * ldb;
     const unsigned gn = (unsigned)((n + kDT - 1) / kDT);
     const unsigned gm = (unsigned)((mw + kDT - 1) / kDT);
-    k_bw<<<dim3(gr, gm), 256, 0, s>>>(Bw, ldb, mw, r, Cp, ldcp, W, sym);
     const unsigned g32 = (unsigned)((r + 31) / 32);
-    if (sym) k_symmetric<<<dim3(g32, g32), 256, 0, s>>>(Cp, r, ldcp, sym);
-    if (A) {
-        k_nys_tile<true><<<dim3(gn, gm), 256, 0, s>>>(W, mw, B, ldb, n, r, A, lda, nullptr, 0,
-                                                      part, sym);
-        k_err_sum<<<1, kJThreads, 0, s>>>(part, (int64_t)gn * gm, sums);
-    } else {
-        k_nys_tile<false><<<dim3(gn, gm), 256, 0, s>>>(W, mw, B, ldb, n, r, nullptr, 0, out, ldo,
-                                                       nullptr, nullptr);
-    }
+    auto run = [&](auto tail) {
+        constexpr bool TAIL = decltype(tail)::value;
+        k_bw<TAIL><<<dim3(gr, gm), 256, 0, s>>>(Bw, ldb, mw, r, Cp, ldcp, W, sym);
+        if (sym) k_symmetric<<<dim3(g32, g32), 256, 0, s>>>(Cp, r, ldcp, sym);
+        if (A)
+            k_nys_tile<true, TAIL><<<dim3(gn, gm), 256, 0, s>>>(W, mw, B, ldb, n, r, A, lda, nullptr, 0,
+                                                                part, sym);
+        else
+            k_nys_tile<false, TAIL><<<dim3(gn, gm), 256, 0, s>>>(W, mw, B, ldb, n, r, nullptr, 0, out,
+                                                                 ldo, nullptr, nullptr);
+    };
+    if (r % kDK) run(std::true_type{});
+    else run(std::false_type{});
+    if (A) k_err_sum<<<1, kJThreads, 0, s>>>(part, (int64_t)gn * gm, sums);
     return hipGetLastError();
 }
 
